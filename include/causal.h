@@ -259,8 +259,12 @@ cs_status cs_action(const uint64_t *hist, int64_t n, int dim, double eps, double
 
 /* ---------------------------------------------------------------------------------
  * Ensembles: `count` independent 1+1 diamonds of sizes n[k] (2 <= n[k] <= 8192).
- * cs_batch_plan builds a plan (sizes, offsets, work lists, tile choice); its work
+ * cs_batch_plan builds a plan (sizes, offsets, work lists, counting choice); its work
  * tables are uploaded once to device memory that the plan owns (freed by cs_batch_free).
+ * The intervals of a 1+1 diamond are rectangles in (u, v), so instances are counted from
+ * the places of their points in u and v, in O(n^2) operations, the same exact counts for
+ * every `counter`; a tune_cache entry (see cs_autotune) can select the counter's tiles
+ * over the matrix instead.
  * cs_batch_run enqueues the whole pipeline -- sprinkle, matrix, counts, actions --
  * as a fixed sequence of kernels with no host synchronisation and no allocation, so
  * the caller may capture it in a HIP graph.
@@ -294,8 +298,8 @@ cs_status cs_batch_free(cs_batch_plan_handle plan);
 
 /*
  * HIP graph of one cs_batch_run with these buffers, captured on an internal stream and
- * instantiated (so the graph replays the same four launches: sprinkle, which also clears
- * the histograms and the work counters, build, count, action).  graph_exec receives an opaque hipGraphExec_t owned by the caller:
+ * instantiated (so the graph replays the same launches: sprinkle, which also clears the
+ * histograms and the work counters, build, rank tables, count, action).  graph_exec receives an opaque hipGraphExec_t owned by the caller:
  * launch it with cs_batch_graph_launch on any stream, release it with
  * cs_batch_graph_destroy.  The buffers must stay valid while the graph is in use.
  */
@@ -322,9 +326,10 @@ cs_status cs_batch_graph_destroy(void *graph_exec);
  *   counter    CS_COUNT_BITSET, CS_COUNT_MFMA, CS_COUNT_MFMA_FP4, or -1 for all three.
  * The fastest configuration of each (counter, bucket) is stored in the JSON file
  * cache_path (one entry per line, keeping the entries of an existing file that were not
- * re-tuned).  cs_batch_plan reads its own counter's entries from `tune_cache` (may be
- * NULL); without an entry it uses 128 tiles with two workgroups per CU (MFMA) and
- * related-pair tiles with at most 2304 tasks (bitset).  The tuner allocates and
+ * re-tuned), with its time ("ms") and the rank counter's on the same ensemble
+ * ("rank_ms").  cs_batch_plan reads its own counter's entries from `tune_cache` (may be
+ * NULL): an entry whose rank_ms is below its ms, and a bucket without an entry, count by
+ * ranks; an entry without rank_ms keeps its tiles.  The tuner allocates and
  * frees its own device memory and synchronises `stream`.  Every configuration gives
  * identical, exact histograms.
  */

@@ -15,8 +15,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(BUILD, "libcausal.so")
-SOURCES = ["sprinkle.hip", "builder.hip", "count.hip", "action.hip", "batch.hip", "peak.hip",
-           "chain.hip", "noalloc.hip", "api.hip"]
+SOURCES = ["sprinkle.hip", "builder.hip", "count.hip", "action.hip", "batch.hip", "ranks.hip",
+           "peak.hip", "chain.hip", "noalloc.hip", "api.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-ffp-contract=off",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",

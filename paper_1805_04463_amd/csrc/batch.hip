@@ -12,17 +12,18 @@
 // XCD's L2 (a workgroup that runs out of its own queue takes from the others).  Against
 // one queue of row panels sorted by cost across all instances, this fetches 2.5x fewer
 // bytes from HBM per launch.  These tables live in device memory owned
-// by the plan, uploaded once at plan time, so a run only enqueues kernels: fill,
-// sprinkle, build, count (one persistent launch per tile configuration in use), action.
+// by the plan, uploaded once at plan time, so a run only enqueues kernels: sprinkle,
+// build, rank tables, count (one persistent launch per configuration in use), action.
 //
-// Tile configuration per instance: the counter's configuration for the instance's size
-// bucket.  The candidates are, for the MFMA counters, 128x128 tiles with one or two
+// Counting configuration per instance: by ranks (ranks.hip), the default, or the
+// counter's tiles for the instance's size bucket.  The candidates are, for the MFMA counters, 128x128 tiles with one or two
 // workgroups per CU and 256x256 tiles (one per CU); for the bitset counter, the dense
 // product on every tile or the related-pair tiles with two thresholds, two workgroups
 // per CU, and the related-pair tiles with one.  cs_autotune times every candidate on
 // the device per (counter, bucket) and stores the fastest in a JSON cache, one entry per
-// line; cs_batch_plan reads its counter's entries from that file when given its path
-// and falls back to fixed defaults for the rest.
+// line, with the time of the rank counter on the same ensemble; cs_batch_plan reads its
+// counter's entries from that file when given its path and takes the tiles of an entry
+// that shows no faster rank count (a file written without that field keeps its tiles).
 #include <algorithm>
 #include <cstdio>
 #include <cstring>
@@ -61,19 +62,22 @@ bool same_tile(const BatchTile& a, const BatchTile& b) {
 const BatchTile kMfmaCandidates[] = {{2, 2, 0}, {2, 1, 0}, {4, 1, 0}};
 const BatchTile kBitsetCandidates[] = {{0, 2, -1}, {0, 2, 1152}, {0, 2, 2304}, {0, 1, 2304}};
 
-// Defaults without a cache entry: MFMA 128 tiles, two per CU, below 4096 points and 256
-// tiles from there; the bitset counter on related-pair tiles with the largest task list.
-BatchTile default_tile(int counter, int64_t n) {
-  if (counter == CS_COUNT_BITSET) return {0, 2, 2304};
-  (void)n;  // 128-row tiles, two workgroups per CU: the tuner's choice at every size
-  return BatchTile{2, 2, 0};
-}
+// Counting by ranks is one more configuration (mode 1), the same for every counter: O(N^2)
+// operations per instance where the tiles take O(N^3), the same exact counts.
+const BatchTile kRankTile = {1, 2, 0};
 
 struct TuneTable {
   bool have[3][kBuckets] = {};
   BatchTile cfg[3][kBuckets] = {};
   double ms[3][kBuckets] = {};
   int64_t reps[3][kBuckets] = {};  // instances of the probe ensemble
+  double rank_ms[3][kBuckets] = {};  // the rank counter on the same ensemble (0: not timed)
+  // The configuration of an instance of bucket b: the faster of the entry's tiles and the
+  // rank counter, which also serves the buckets without an entry.
+  BatchTile choice(int c, int b) const {
+    const bool tiles = have[c][b] && !(rank_ms[c][b] > 0.0 && rank_ms[c][b] < ms[c][b]);
+    return tiles ? cfg[c][b] : kRankTile;
+  }
 };
 
 int counter_slot(int counter) {
@@ -124,6 +128,8 @@ TuneTable read_tune(const char* path) {
     const long long pmax = field_ll(name, end, "\"pair_max\"", &ok);
     const char* msk = strstr(name, "\"ms\"");
     const double ms = (msk && msk < end) ? atof(strchr(msk, ':') + 1) : 0.0;
+    const char* rk = strstr(name, "\"rank_ms\"");
+    const double rank_ms = (rk && rk < end) ? atof(strchr(rk, ':') + 1) : 0.0;
     int b = -1;
     for (int q = 0; q < kBuckets; ++q)
       if (kBucketLo[q] == lo) b = q;
@@ -134,6 +140,7 @@ TuneTable read_tune(const char* path) {
       t.have[c][b] = true;
       t.cfg[c][b] = {(int)mode, (int)per_cu, (int)pmax};
       t.ms[c][b] = ms;
+      t.rank_ms[c][b] = rank_ms;
       t.reps[c][b] = has_reps ? reps : 0;
     }
     p = end;
@@ -152,10 +159,10 @@ bool write_tune(const char* path, const TuneTable& t) {
       const BatchTile& x = t.cfg[c][b];
       fprintf(f, "%s\n    {\"counter\": \"%s\", \"n_lo\": %lld, \"n_hi\": %lld, \"mode\": %d, "
                  "\"tile\": %d, \"per_cu\": %d, \"pair_max\": %d, \"ms\": %.5f, "
-                 "\"probe_n\": %lld, \"probe_instances\": %lld}",
+                 "\"rank_ms\": %.5f, \"probe_n\": %lld, \"probe_instances\": %lld}",
               first ? "" : ",", kCounterName[c], (long long)kBucketLo[b],
               (long long)kBucketHi[b], x.mode, x.mode == 4 ? 256 : 128, x.per_cu, x.pair_max,
-              t.ms[c][b], (long long)kBucketProbe[b], (long long)t.reps[c][b]);
+              t.ms[c][b], t.rank_ms[c][b], (long long)kBucketProbe[b], (long long)t.reps[c][b]);
       first = false;
     }
   fprintf(f, "\n  ]\n}\n");
@@ -175,9 +182,13 @@ struct cs_batch_plan_t {
   BatchTile slot_cfg[kMaxSlots] = {};
   int64_t n_items[kMaxSlots] = {};
   BatchQueues queues[kMaxSlots] = {};
-  size_t ws_bytes = 0, off_coords = 0, off_bits = 0;
+  size_t ws_bytes = 0, off_coords = 0, off_bits = 0, off_rank = 0;
+  int64_t n_tab = 0;                // (instance, column block) items of the rank tables
+  int rank_units = kRankWaves;      // counting units per item
   void* dev = nullptr;              // device tables
   BatchInst* d_inst = nullptr;
+  RankInst* d_rank = nullptr;
+  uint32_t* d_tab = nullptr;
   double* d_eps = nullptr;
   uint32_t* d_build = nullptr;
   uint32_t* d_items[kMaxSlots] = {};
@@ -192,8 +203,8 @@ size_t take(size_t* off, size_t bytes) {
   return o;
 }
 
-// tune: the cache's choices (entries it lacks use default_tile); force: if not null,
-// every instance takes this configuration (the tuner's candidates).
+// tune: the cache's choices; force: if not null, every instance takes this configuration
+// (the tuner's candidates).
 cs_status build_plan(int64_t count, const int64_t* n, int counter, int n_eps, const double* eps,
                      const TuneTable& tune, const BatchTile* force, cs_batch_plan_t* p) {
   p->count = count;
@@ -207,6 +218,9 @@ cs_status build_plan(int64_t count, const int64_t* n, int counter, int n_eps, co
   };
   std::vector<Item> items[kMaxSlots];
   const int cslot = counter_slot(counter);
+  std::vector<RankInst> rank(count);  // n = 0: counted by tiles
+  std::vector<uint32_t> tab;
+  int64_t roff = 0, units = 0;
   int64_t coff = 0, boff = 0, hoff = 0;
   for (int64_t k = 0; k < count; ++k) {
     BatchInst& d = p->inst[k];
@@ -233,8 +247,7 @@ cs_status build_plan(int64_t count, const int64_t* n, int counter, int n_eps, co
                bj < std::min((pc + 1) * kBuildPatch, nb); bj += kBuildColBlocks)
             bitems[k].push_back((uint32_t)(k << 16 | g << 8 | bj));
     const int b = bucket_of(d.n);
-    const BatchTile cfg = force ? *force
-                          : (tune.have[cslot][b] ? tune.cfg[cslot][b] : default_tile(counter, d.n));
+    const BatchTile cfg = force ? *force : tune.choice(cslot, b);
     int slot = -1;
     for (int q = 0; q < p->nslots; ++q)
       if (same_tile(p->slot_cfg[q], cfg)) slot = q;
@@ -242,6 +255,17 @@ cs_status build_plan(int64_t count, const int64_t* n, int counter, int n_eps, co
       if (p->nslots == kMaxSlots) return CS_ERR_UNSUPPORTED;
       slot = p->nslots++;
       p->slot_cfg[slot] = cfg;
+    }
+    if (cfg.mode == kRankTile.mode) {
+      RankInst& r = rank[k];
+      r.base = roff;
+      r.hist_off = d.hist_off;
+      r.n = (int32_t)d.n;
+      r.nb = (int32_t)nb;
+      roff = (int64_t)align_up((size_t)r.end(), 256);
+      units += r.units();
+      for (int64_t J = 0; J < nb; ++J) tab.push_back((uint32_t)(k << 16 | J));
+      continue;
     }
     const int64_t BM = cfg.mode == 4 ? 256 : 128;
     const int64_t T = ceil_div(d.n, BM);
@@ -278,7 +302,25 @@ cs_status build_plan(int64_t count, const int64_t* n, int counter, int n_eps, co
       std::copy(lists[x].begin(), lists[x].end(), build.begin() + x * len);
   }
   p->n_build = (int64_t)build.size();
+  p->n_tab = (int64_t)tab.size();
   for (int s = 0; s < p->nslots; ++s) {
+    if (p->slot_cfg[s].mode == kRankTile.mode) {
+      // Units in items of one instance, largest instances first.  An item's histogram is
+      // flushed when the workgroup moves to another instance, so items are long, down to
+      // about four per resident workgroup (two per CU), and at least a unit per wavefront.
+      const int64_t per = units / (4 * 2 * (int64_t)device_cu_count()) / kRankWaves * kRankWaves;
+      p->rank_units = (int)std::min<int64_t>(std::max<int64_t>(per, kRankWaves), 8 * kRankWaves);
+      std::vector<int64_t> order;
+      for (int64_t k = 0; k < count; ++k)
+        if (rank[k].n) order.push_back(k);
+      std::stable_sort(order.begin(), order.end(),
+                       [&](int64_t a, int64_t b) { return rank[a].n > rank[b].n; });
+      for (int64_t k : order)
+        for (int64_t c = 0; c * p->rank_units < rank[k].units(); ++c)
+          items[s].push_back({(uint32_t)(k << 16 | c), 0});
+      p->n_items[s] = (int64_t)items[s].size();
+      continue;
+    }
     // One queue per XCD holding whole instances, dealt largest first to the least loaded
     // queue; a queue runs its instances one after another (largest first), each
     // instance's row panels longest first, so the workgroups of one XCD work on the same
@@ -319,17 +361,20 @@ cs_status build_plan(int64_t count, const int64_t* n, int counter, int n_eps, co
     p->n_items[s] = (int64_t)items[s].size();
   }
 
-  // Caller workspace: [tile counters, one per slot][coordinates][matrices].
+  // Caller workspace: [work counters, per slot][coordinates][matrices][rank tables].
   size_t off = 0;
   static_assert(sizeof(unsigned int) * kMaxSlots * kBatchQueues == 256, "work counters");
   take(&off, 256);
   p->off_coords = take(&off, sizeof(double) * (size_t)coff);
   p->off_bits = take(&off, sizeof(uint64_t) * (size_t)boff);
+  p->off_rank = take(&off, (size_t)roff);
   p->ws_bytes = off;
 
   // Device tables owned by the plan.
   size_t doff = 0;
   size_t o_inst = take(&doff, sizeof(BatchInst) * count);
+  size_t o_rank = take(&doff, sizeof(RankInst) * count);
+  size_t o_tab = take(&doff, sizeof(uint32_t) * tab.size());
   size_t o_eps = take(&doff, sizeof(double) * (n_eps > 0 ? n_eps : 1));
   size_t o_build = take(&doff, sizeof(uint32_t) * build.size());
   size_t o_items[kMaxSlots];
@@ -338,10 +383,14 @@ cs_status build_plan(int64_t count, const int64_t* n, int counter, int n_eps, co
   CS_HIP_CHECK(hipMalloc(&p->dev, doff));
   char* b = (char*)p->dev;
   p->d_inst = (BatchInst*)(b + o_inst);
+  p->d_rank = (RankInst*)(b + o_rank);
+  p->d_tab = (uint32_t*)(b + o_tab);
   p->d_eps = (double*)(b + o_eps);
   p->d_build = (uint32_t*)(b + o_build);
   std::vector<char> host(doff, 0);
   memcpy(host.data() + o_inst, p->inst.data(), sizeof(BatchInst) * count);
+  memcpy(host.data() + o_rank, rank.data(), sizeof(RankInst) * count);
+  if (!tab.empty()) memcpy(host.data() + o_tab, tab.data(), sizeof(uint32_t) * tab.size());
   if (n_eps > 0) memcpy(host.data() + o_eps, eps, sizeof(double) * n_eps);
   memcpy(host.data() + o_build, build.data(), sizeof(uint32_t) * build.size());
   for (int s = 0; s < p->nslots; ++s) {
@@ -353,10 +402,20 @@ cs_status build_plan(int64_t count, const int64_t* n, int counter, int n_eps, co
   return CS_OK;
 }
 
-cs_status run_counts(cs_batch_plan_t* p, const uint64_t* bits, uint64_t* hist, unsigned int* ctr,
-                     hipStream_t st) {
+cs_status run_counts(cs_batch_plan_t* p, char* ws, uint64_t* hist, hipStream_t st) {
+  unsigned int* ctr = (unsigned int*)ws;
+  const uint64_t* bits = (const uint64_t*)(ws + p->off_bits);
+  char* rank_base = ws + p->off_rank;
   for (int s = 0; s < p->nslots; ++s) {
     if (!p->n_items[s]) continue;
+    if (p->slot_cfg[s].mode == kRankTile.mode) {
+      cs_status r = launch_rank_tables(p->d_rank, p->d_tab, p->n_tab, rank_base, st);
+      if (r != CS_OK) return r;
+      r = launch_count_ranks(p->d_rank, p->d_items[s], p->n_items[s], p->rank_units, rank_base, hist,
+                             ctr + s * kBatchQueues, st);
+      if (r != CS_OK) return r;
+      continue;
+    }
     cs_status r = launch_count_batch(p->slot_cfg[s], p->counter == CS_COUNT_MFMA_FP4, bits,
                                      p->d_inst, p->d_items[s], p->queues[s], hist,
                                      ctr + s * kBatchQueues, st);
@@ -424,12 +483,13 @@ cs_status cs_batch_run(cs_batch_plan_handle plan, const uint64_t* seeds, uint64_
   uint64_t* bits = (uint64_t*)(ws + plan->off_bits);
   cs_status s;
   // the sprinkle kernel also clears the histograms and the work counters
-  if ((s = launch_sprinkle_batch(seeds, plan->d_inst, plan->count, coords, hist, (uint64_t*)ctr,
+  if ((s = launch_sprinkle_batch(seeds, plan->d_inst, plan->d_rank, plan->count, coords,
+                                 ws + plan->off_rank, hist, (uint64_t*)ctr,
                                  kMaxSlots * kBatchQueues / 2, st)) != CS_OK)
     return s;
   if ((s = launch_build_batch(coords, plan->d_inst, plan->d_build, plan->n_build, bits, st)) != CS_OK)
     return s;
-  if ((s = run_counts(plan, bits, hist, ctr, st)) != CS_OK) return s;
+  if ((s = run_counts(plan, ws, hist, st)) != CS_OK) return s;
   return launch_action_batch(hist, plan->d_inst, plan->count, 2, plan->d_eps, plan->n_eps, actions,
                              st);
 }
@@ -484,7 +544,8 @@ cs_status cs_batch_graph_destroy(void* graph_exec) {
 
 // For each requested (counter, bucket): an ensemble of `reps` diamonds of the bucket's
 // probe size, every tile configuration of the counter's candidates forced on all of them,
-// the counting launches timed (best of three, HIP events); the fastest is stored.
+// the counting launches timed (best of five, HIP events), and the rank counter's; the
+// fastest tiles are stored with both times.
 cs_status cs_autotune(const char* cache_path, int64_t n_bucket, int counter, void* stream) {
   if (!cache_path) return CS_ERR_INVALID_ARG;
   if (counter != -1 && counter != CS_COUNT_BITSET && counter != CS_COUNT_MFMA &&
@@ -519,11 +580,12 @@ cs_status cs_autotune(const char* cache_path, int64_t n_bucket, int counter, voi
       const int64_t plo = 2 * kBucketProbe[b] - kBucketHi[b], phi = kBucketHi[b];
       std::vector<int64_t> sizes(reps);
       for (int64_t k = 0; k < reps; ++k) sizes[k] = plo + (phi - plo) * k / (reps - 1);
-      double best_ms = 1e30;
+      double best_ms = 1e30, rank_ms = 0.0;
       int best = -1;
-      for (int v = 0; v < ncand && status == CS_OK; ++v) {
+      for (int v = 0; v <= ncand && status == CS_OK; ++v) {
         cs_batch_plan_t q;
-        status = build_plan(reps, sizes.data(), c, 0, nullptr, TuneTable{}, &cand[v], &q);
+        status = build_plan(reps, sizes.data(), c, 0, nullptr, TuneTable{},
+                            v < ncand ? &cand[v] : &kRankTile, &q);
         void* ws = nullptr;
         uint64_t* hist = nullptr;
         uint64_t* seeds = nullptr;
@@ -546,7 +608,7 @@ cs_status cs_autotune(const char* cache_path, int64_t n_bucket, int counter, voi
             if (status == CS_OK) status = launch_fill_u64(hist, q.hist_len, 0, st);
             if (status != CS_OK) break;
             (void)hipEventRecord(e0, st);
-            status = run_counts(&q, (uint64_t*)((char*)ws + q.off_bits), hist, ctr, st);
+            status = run_counts(&q, (char*)ws, hist, st);
             (void)hipEventRecord(e1, st);
             if (hipEventSynchronize(e1) != hipSuccess) status = CS_ERR_HIP;
             float ms = 0.f;
@@ -559,7 +621,9 @@ cs_status cs_autotune(const char* cache_path, int64_t n_bucket, int counter, voi
         if (seeds) (void)hipFree(seeds);
         if (q.dev) (void)hipFree(q.dev);
         q.dev = nullptr;
-        if (status == CS_OK && ms_v < best_ms) {
+        if (status == CS_OK && v == ncand) {
+          rank_ms = ms_v;
+        } else if (status == CS_OK && ms_v < best_ms) {
           best_ms = ms_v;
           best = v;
         }
@@ -569,6 +633,7 @@ cs_status cs_autotune(const char* cache_path, int64_t n_bucket, int counter, voi
         table.have[cs_][b] = true;
         table.cfg[cs_][b] = cand[best];
         table.ms[cs_][b] = best_ms;
+        table.rank_ms[cs_][b] = rank_ms;
         table.reps[cs_][b] = reps;
       }
     }

@@ -90,6 +90,31 @@ struct BatchInst {
   int64_t n, ld, coord_off, bits_off, hist_off;
 };
 
+// Tables of an instance counted by ranks (ranks.hip), in the workspace's rank area: n
+// points (0: not counted by ranks), in nb blocks of 64 of the u order.
+//   sigma  uint16[64 nb]  u place by v place          pi  uint16[64 nb]  v place by u place
+//   row    uint32[64 nb]  pi << 16 | 4 D per point, D = its number of predecessors
+//   tab    uint32, row J < nb of 64 J entries: 4 F(64 J, pi_i) for i < 64 J
+//   seg    uint16, row s (1 <= s <= (nb - 1) / 4) of 64 nb entries: F(256 s, pi_j), j >= 256 s
+// where F(a, x) is the number of points with u place below a and v place below x.
+constexpr int kRankSegBlocks = 4;  // row blocks per unit of counting work
+struct RankInst {
+  int64_t base;      // byte offset in the rank area
+  int64_t hist_off;  // uint64 bins
+  int32_t n, nb;
+  __host__ __device__ int64_t sigma_off() const { return base; }
+  __host__ __device__ int64_t pi_off() const { return base + 128ll * nb; }
+  __host__ __device__ int64_t row_off() const { return base + 256ll * nb; }
+  __host__ __device__ int64_t tab_off(int64_t J) const { return base + 512ll * nb + 128 * J * (J - 1); }
+  __host__ __device__ int64_t seg_off(int64_t s) const { return tab_off(nb) + 128ll * nb * (s - 1); }
+  int64_t end() const { return seg_off((nb - 1) / kRankSegBlocks + 1); }
+  // units of counting work: column block J with the segments of its row blocks 0 .. J
+  int64_t units() const {
+    const int64_t q = nb / kRankSegBlocks, r = nb % kRankSegBlocks;
+    return (q + 1) * (kRankSegBlocks / 2 * q + r);
+  }
+};
+
 // Largest instance of an ensemble (its whole histogram fits the LDS bins, its sort
 // fits one workgroup's LDS).
 constexpr int64_t kBatchMaxN = 8192;
@@ -134,9 +159,17 @@ constexpr size_t kScratchBytes = 16384;
 cs_status scratch_for_current_device(void** out);
 
 // Ensemble pieces (1+1 diamonds).
-cs_status launch_sprinkle_batch(const uint64_t* seeds, const BatchInst* inst, int64_t count,
-                                double* coords, uint64_t* hist, uint64_t* zero, int nzero,
-                                hipStream_t st);
+cs_status launch_sprinkle_batch(const uint64_t* seeds, const BatchInst* inst, const RankInst* rank,
+                                int64_t count, double* coords, char* rank_base, uint64_t* hist,
+                                uint64_t* zero, int nzero, hipStream_t st);
+// Rank tables (items: instance << 16 | column block), then the counts from them (items:
+// instance << 16 | chunk of `per_item` units; counter: one work counter, zero at launch).
+cs_status launch_rank_tables(const RankInst* rank, const uint32_t* items, int64_t nitems,
+                             char* rank_base, hipStream_t st);
+cs_status launch_count_ranks(const RankInst* rank, const uint32_t* items, int64_t nitems,
+                             int per_item, const char* rank_base, uint64_t* hist,
+                             unsigned int* counter, hipStream_t st);
+constexpr int kRankWaves = 16;  // wavefronts per workgroup of the rank counter
 cs_status launch_build_batch(const double* coords, const BatchInst* inst,
                              const uint32_t* items, int64_t nitems, uint64_t* bits,
                              hipStream_t st);

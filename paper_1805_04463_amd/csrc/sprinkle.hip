@@ -480,125 +480,162 @@ cs_status bitonic_sort(uint64_t* keys, uint32_t* gens, int64_t P, hipStream_t st
 }
 
 // ---------------------------------------------------------------------------
-// Ensemble of 1+1 diamonds: one workgroup per instance (n <= 8192).  The time order is
-// (key, generation index) with the 54-bit key of the single-instance path.  The LDS sort
-// runs on one 64-bit word per point, the key's top 32 bits above the index, so each
-// compare-exchange moves 16 bytes instead of 24; points whose top key bits tie (about
-// one instance in thirty has such a pair) form runs that a second pass puts in
-// (key, index) order, with the keys regenerated from the indices (the generator is
-// counter-based).  The sorted coordinates are then regenerated the same way, so no raw
-// copy is kept.
+// Ensemble of 1+1 diamonds: one workgroup per instance (n <= 8192).  Each of a point's
+// three places -- in time order (key u + v, then draw index), in u and in v -- comes from a
+// bucket sort in LDS: the keys are draws of known density (uniform, or the triangle of
+// u + v), so with a bucket per power of two at least n a bucket holds a few points.  A
+// point takes an arrival slot of its bucket (LDS atomic), the bucket counts are scanned,
+// and its place is its bucket's start plus the points of the bucket that precede it.
+// The bucket's leading key bits being equal, the remaining ones and the index fit one
+// 64-bit word, so a comparison is exact.  Bound by its barriers and LDS latency (one
+// workgroup per CU, the largest instance ends last).
 // ---------------------------------------------------------------------------
 constexpr int kBatchSortThreads = 1024;
-constexpr int kBatchKeyShift = 22;  // 54-bit keys: the top 32 bits go into the sort word
+constexpr int kBatchSortWaves = kBatchSortThreads / 64;
+constexpr int kBatchPer = (int)(kBatchMaxN / kBatchSortThreads);  // points per thread
 
+struct BucketLds {
+  uint64_t word[kBatchMaxN];       // rest of the key << lg | index, by bucket slot
+  uint32_t start[kBatchMaxN + 4];  // bucket counts, then starts; start[buckets] = n
+  uint32_t wsum[kBatchSortWaves];
+};
+
+// place[e] = number of points before point threadIdx.x + 1024 e in (key, index) order; keys
+// below 2^KB, 2^lg >= n buckets.  tie(g, h): for equal keys, whether g comes first.
+template <int KB, typename Tie>
+__device__ inline void bucket_places(const uint64_t (&key)[kBatchPer], int n, int lg, BucketLds& L,
+                                     uint32_t (&place)[kBatchPer], Tie&& tie) {
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  const int P = 1 << lg, sh = KB - lg;
+  __syncthreads();  // the last use of the buffers is over
+  for (int b = t; b < P; b += kBatchSortThreads) L.start[b] = 0;
+  __syncthreads();
+  uint32_t at[kBatchPer];
+#pragma unroll
+  for (int e = 0; e < kBatchPer; ++e)
+    if (t + e * kBatchSortThreads < n) at[e] = atomicAdd(&L.start[key[e] >> sh], 1u);
+  __syncthreads();
+  {  // exclusive scan of the counts: m consecutive buckets per thread
+    const int m = P > kBatchSortThreads ? P / kBatchSortThreads : 1;
+    uint32_t c[kBatchPer], sum = 0;
+#pragma unroll
+    for (int q = 0; q < kBatchPer; ++q)
+      if (q < m && t * m + q < P) {
+        c[q] = L.start[t * m + q];
+        sum += c[q];
+      }
+    uint32_t x = sum;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const uint32_t y = __shfl_up(x, d);
+      if (lane >= d) x += y;
+    }
+    if (lane == 63) L.wsum[wave] = x;
+    __syncthreads();
+    uint32_t off = x - sum;
+#pragma unroll
+    for (int w = 0; w < kBatchSortWaves; ++w) off += w < wave ? L.wsum[w] : 0u;
+#pragma unroll
+    for (int q = 0; q < kBatchPer; ++q)
+      if (q < m && t * m + q < P) {
+        L.start[t * m + q] = off;
+        off += c[q];
+      }
+    if (t == 0) L.start[P] = (uint32_t)n;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int e = 0; e < kBatchPer; ++e) {
+    const uint32_t g = t + e * kBatchSortThreads;
+    if ((int)g < n)
+      L.word[L.start[key[e] >> sh] + at[e]] = (key[e] & ((1ull << sh) - 1)) << lg | g;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int e = 0; e < kBatchPer; ++e) {
+    const uint32_t g = t + e * kBatchSortThreads;
+    if ((int)g < n) {
+      const uint64_t b = key[e] >> sh;
+      const uint64_t w = (key[e] & ((1ull << sh) - 1)) << lg | g;
+      const uint32_t lo = L.start[b], hi = L.start[b + 1];
+      uint32_t r = lo;
+      for (uint32_t s = lo; s < hi; ++s) {
+        const uint64_t o = L.word[s];
+        bool before = o < w;
+        if ((o >> lg) == (w >> lg) && o != w) before = tie((uint32_t)o & (P - 1u), g);
+        r += before ? 1u : 0u;
+      }
+      place[e] = r;
+    }
+  }
+}
+
+// Also clears the instance's histogram and (workgroup 0) the work counters, which the
+// later launches accumulate into.  Instances counted by ranks (rank[k].n != 0) get their
+// u order: sigma[x] is the u place of the point at v place x, pi its inverse.  Equal
+// coordinates are unrelated, so ties take opposite orders in u and v: equal u by v
+// descending, equal v by u descending, equal points by index one way and the other.
 __global__ __launch_bounds__(kBatchSortThreads) void k_sprinkle_mink2_batch(
     const uint64_t* __restrict__ seeds, const BatchInst* __restrict__ inst,
-    double* __restrict__ coords, uint64_t* __restrict__ hist, uint64_t* __restrict__ zero,
-    int nzero) {
-  __shared__ uint64_t sw[kBatchMaxN];  // key >> kBatchKeyShift << 32 | generation index
+    const RankInst* __restrict__ rank, double* __restrict__ coords, char* __restrict__ rank_base,
+    uint64_t* __restrict__ hist, uint64_t* __restrict__ zero, int nzero) {
+  __shared__ BucketLds L;
   const BatchInst d = inst[blockIdx.x];
-  const int n = (int)d.n;
-  // The pipeline's later kernels accumulate into the instance's histogram and take work
-  // from counters: both start at zero, cleared here instead of by launches of their own.
-  for (int m = threadIdx.x; m < n - 1; m += kBatchSortThreads) hist[d.hist_off + m] = 0;
+  const int n = (int)d.n, t = threadIdx.x;
+  for (int m = t; m < n - 1; m += kBatchSortThreads) hist[d.hist_off + m] = 0;
   if (blockIdx.x == 0)
-    for (int w = threadIdx.x; w < nzero; w += kBatchSortThreads) zero[w] = 0;
-  int P = 2;
-  while (P < n) P <<= 1;
+    for (int w = t; w < nzero; w += kBatchSortThreads) zero[w] = 0;
+  int lg = 1;
+  while ((1 << lg) < n) ++lg;
   const uint64_t skey = sm_stream_key(seeds[blockIdx.x], kStreamMink2);
-  for (int g = threadIdx.x; g < P; g += kBatchSortThreads)
-    sw[g] = g < n ? (mink2_key(skey, (uint64_t)g) >> kBatchKeyShift) << 32 | (uint32_t)g : ~0ull;
-  // One compare-exchange step of distance j in merge stage k through LDS: pairs t,
-  // t + 1024, ... of thread t; with j <= 64 every 128-element block is still worked by
-  // one wave (block b by wave b mod 16), so the step only synchronises the wave.
-  bool wide = true;  // the previous step (or the load) crossed 128-element blocks
-  auto lds_step = [&](int k, int j) {
-    bitonic_step_sync(wide || j >= 128);
-    wide = j >= 128;
-    for (int t = threadIdx.x; t < P / 2; t += kBatchSortThreads) {
-      const int i = 2 * t - (t & (j - 1));
-      const uint64_t x = sw[i], y = sw[i + j];
-      if ((x > y) == ((i & k) == 0)) {
-        sw[i] = y;
-        sw[i + j] = x;
-      }
-    }
-  };
-  // The steps of distance 4, 2 and 1 of stage k (and, with k = 0, the whole of stages
-  // 2, 4 and 8) on 8-element chunks held in registers: one LDS read and write of each
-  // element instead of three steps.  A chunk's 8 elements share the direction bit of
-  // every stage k >= 8.
-  auto chunk_steps = [&](int k) {
-    __syncthreads();
-    for (int c = threadIdx.x; c < P / 8; c += kBatchSortThreads) {
-      uint64_t v[8];
+  uint64_t ku[kBatchPer], kv[kBatchPer], key[kBatchPer];
 #pragma unroll
-      for (int e = 0; e < 8; ++e) v[e] = sw[8 * c + e];
-      auto cx = [&](int e, int j, bool asc) {
-        const uint64_t x = v[e], y = v[e + j];
-        const bool sw_ = (x > y) == asc;
-        v[e] = sw_ ? y : x;
-        v[e + j] = sw_ ? x : y;
-      };
-      if (k == 0) {
-#pragma unroll
-        for (int kk = 2; kk <= 8; kk <<= 1)
-#pragma unroll
-          for (int j = kk >> 1; j > 0; j >>= 1)
-#pragma unroll
-            for (int e = 0; e < 8; ++e)
-              if ((e & j) == 0) cx(e, j, ((8 * c + e) & kk) == 0);
-      } else {
-        const bool asc = ((8 * c) & k) == 0;
-#pragma unroll
-        for (int j = 4; j > 0; j >>= 1)
-#pragma unroll
-          for (int e = 0; e < 8; ++e)
-            if ((e & j) == 0) cx(e, j, asc);
-      }
-#pragma unroll
-      for (int e = 0; e < 8; ++e) sw[8 * c + e] = v[e];
-    }
-    wide = true;
-  };
-  if (P >= 8) {
-    chunk_steps(0);
-    for (int k = 16; k <= P; k <<= 1) {
-      for (int j = k >> 1; j >= 8; j >>= 1) lds_step(k, j);
-      chunk_steps(k);
-    }
-  } else {
-    for (int k = 2; k <= P; k <<= 1)
-      for (int j = k >> 1; j > 0; j >>= 1) lds_step(k, j);
-  }
-  __syncthreads();
-  // Runs of equal top key bits are in index order; put each in (key, index) order.
-  for (int i = threadIdx.x; i < n; i += kBatchSortThreads) {
-    const uint32_t h = (uint32_t)(sw[i] >> 32);
-    const bool start = i == 0 || (uint32_t)(sw[i - 1] >> 32) != h;
-    if (!start || i + 1 >= n || (uint32_t)(sw[i + 1] >> 32) != h) continue;
-    int e = i + 2;
-    while (e < n && (uint32_t)(sw[e] >> 32) == h) ++e;
-    for (int a = i + 1; a < e; ++a) {  // insertion sort of the run [i, e)
-      const uint64_t x = sw[a];
-      const uint64_t kx = mink2_key(skey, (uint32_t)x);
-      int b = a - 1;
-      for (; b >= i; --b) {
-        const uint64_t kb = mink2_key(skey, (uint32_t)sw[b]);
-        if (kb < kx || (kb == kx && (uint32_t)sw[b] < (uint32_t)x)) break;
-        sw[b + 1] = sw[b];
-      }
-      sw[b + 1] = x;
+  for (int e = 0; e < kBatchPer; ++e) {
+    const int g = t + e * kBatchSortThreads;
+    ku[e] = kv[e] = key[e] = 0;
+    if (g < n) {
+      ku[e] = sm_output(skey, 2 * (uint64_t)g) >> 11;
+      kv[e] = sm_output(skey, 2 * (uint64_t)g + 1) >> 11;
+      key[e] = ku[e] + kv[e];
     }
   }
-  __syncthreads();
+  uint32_t place[kBatchPer];
+  bucket_places<54>(key, n, lg, L, place, [](uint32_t a, uint32_t b) { return a < b; });
   double* cu = coords + d.coord_off;
   double* cv = cu + n;
-  for (int i = threadIdx.x; i < n; i += kBatchSortThreads) {
-    const uint64_t g = (uint32_t)sw[i];
-    cu[i] = (double)(sm_output(skey, 2 * g) >> 11) * 0x1.0p-53;
-    cv[i] = (double)(sm_output(skey, 2 * g + 1) >> 11) * 0x1.0p-53;
+#pragma unroll
+  for (int e = 0; e < kBatchPer; ++e)
+    if (t + e * kBatchSortThreads < n) {
+      cu[place[e]] = (double)ku[e] * 0x1.0p-53;
+      cv[place[e]] = (double)kv[e] * 0x1.0p-53;
+    }
+  const RankInst r = rank[blockIdx.x];
+  if (r.n == 0) return;
+  auto draw = [&](uint32_t g, int axis) { return sm_output(skey, 2 * (uint64_t)g + axis) >> 11; };
+  uint32_t pu[kBatchPer], pv[kBatchPer];
+  bucket_places<53>(ku, n, lg, L, pu, [&](uint32_t a, uint32_t b) {
+    const uint64_t va = draw(a, 1), vb = draw(b, 1);
+    return va > vb || (va == vb && a < b);
+  });
+  bucket_places<53>(kv, n, lg, L, pv, [&](uint32_t a, uint32_t b) {
+    const uint64_t ua = draw(a, 0), ub = draw(b, 0);
+    return ua > ub || (ua == ub && a > b);
+  });
+  // Both permutations leave through LDS, in whole lines.
+  uint16_t* perm = (uint16_t*)L.word;  // sigma, then pi
+  __syncthreads();
+#pragma unroll
+  for (int e = 0; e < kBatchPer; ++e)
+    if (t + e * kBatchSortThreads < n) {
+      perm[pv[e]] = (uint16_t)pu[e];
+      perm[kBatchMaxN + pu[e]] = (uint16_t)pv[e];
+    }
+  __syncthreads();
+  uint16_t* sigma = (uint16_t*)(rank_base + r.sigma_off());
+  uint16_t* pi = (uint16_t*)(rank_base + r.pi_off());
+  for (int i = t; i < n; i += kBatchSortThreads) {
+    sigma[i] = perm[i];
+    pi[i] = perm[kBatchMaxN + i];
   }
 }
 
@@ -674,12 +711,12 @@ cs_status launch_sprinkle(int region, double eta0, uint64_t seed, int64_t n, dou
   return CS_OK;
 }
 
-cs_status launch_sprinkle_batch(const uint64_t* seeds, const BatchInst* inst, int64_t count,
-                                double* coords, uint64_t* hist, uint64_t* zero, int nzero,
-                                hipStream_t st) {
+cs_status launch_sprinkle_batch(const uint64_t* seeds, const BatchInst* inst, const RankInst* rank,
+                                int64_t count, double* coords, char* rank_base, uint64_t* hist,
+                                uint64_t* zero, int nzero, hipStream_t st) {
   if (count <= 0) return CS_OK;
   hipLaunchKernelGGL(k_sprinkle_mink2_batch, dim3((unsigned)count), dim3(kBatchSortThreads), 0, st,
-                     seeds, inst, coords, hist, zero, nzero);
+                     seeds, inst, rank, coords, rank_base, hist, zero, nzero);
   CS_LAUNCH_CHECK();
   return CS_OK;
 }
