@@ -183,7 +183,7 @@ struct cs_batch_plan_t {
   int64_t n_items[kMaxSlots] = {};
   BatchQueues queues[kMaxSlots] = {};
   size_t ws_bytes = 0, off_coords = 0, off_bits = 0, off_rank = 0;
-  int64_t n_tab = 0;                // (instance, column block) items of the rank tables
+  int64_t n_tab = 0;                // work items of the rank tables
   int rank_units = kRankWaves;      // counting units per item
   void* dev = nullptr;              // device tables
   BatchInst* d_inst = nullptr;
@@ -264,7 +264,7 @@ cs_status build_plan(int64_t count, const int64_t* n, int counter, int n_eps, co
       r.nb = (int32_t)nb;
       roff = (int64_t)align_up((size_t)r.end(), 256);
       units += r.units();
-      for (int64_t J = 0; J < nb; ++J) tab.push_back((uint32_t)(k << 16 | J));
+      for (int64_t g = 0; g * kTabBlocks < nb; ++g) tab.push_back((uint32_t)(k << 16 | g));
       continue;
     }
     const int64_t BM = cfg.mode == 4 ? 256 : 128;

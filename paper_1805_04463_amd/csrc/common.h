@@ -94,7 +94,7 @@ struct BatchInst {
 // points (0: not counted by ranks), in nb blocks of 64 of the u order.
 //   sigma  uint16[64 nb]  u place by v place          pi  uint16[64 nb]  v place by u place
 //   row    uint32[64 nb]  pi << 16 | 4 D per point, D = its number of predecessors
-//   tab    uint32, row J < nb of 64 J entries: 4 F(64 J, pi_i) for i < 64 J
+//   tab    uint32, row J < nb of 64 J entries: pi_i << 16 | 4 F(64 J, pi_i) for i < 64 J
 //   seg    uint16, row s (1 <= s <= (nb - 1) / 4) of 64 nb entries: F(256 s, pi_j), j >= 256 s
 // where F(a, x) is the number of points with u place below a and v place below x.
 constexpr int kRankSegBlocks = 4;  // row blocks per unit of counting work
@@ -162,7 +162,7 @@ cs_status scratch_for_current_device(void** out);
 cs_status launch_sprinkle_batch(const uint64_t* seeds, const BatchInst* inst, const RankInst* rank,
                                 int64_t count, double* coords, char* rank_base, uint64_t* hist,
                                 uint64_t* zero, int nzero, hipStream_t st);
-// Rank tables (items: instance << 16 | column block), then the counts from them (items:
+// Rank tables (items: instance << 16 | group of kTabBlocks column blocks), then the counts from them (items:
 // instance << 16 | chunk of `per_item` units; counter: one work counter, zero at launch).
 cs_status launch_rank_tables(const RankInst* rank, const uint32_t* items, int64_t nitems,
                              char* rank_base, hipStream_t st);
@@ -170,6 +170,7 @@ cs_status launch_count_ranks(const RankInst* rank, const uint32_t* items, int64_
                              int per_item, const char* rank_base, uint64_t* hist,
                              unsigned int* counter, hipStream_t st);
 constexpr int kRankWaves = 16;  // wavefronts per workgroup of the rank counter
+constexpr int kTabBlocks = 16;  // column blocks per workgroup of the rank tables
 cs_status launch_build_batch(const double* coords, const BatchInst* inst,
                              const uint32_t* items, int64_t nitems, uint64_t* bits,
                              hipStream_t st);

@@ -27,62 +27,93 @@ namespace cs {
 namespace {
 
 // ---------------------------------------------------------------------------
-// Tables: one wavefront per (instance, column block J).  Along the v order the number of
-// points seen with u place < 64 J is F(64 J, x); it is scattered to u order in LDS and
-// written in whole lines.  Work: n steps per column block, n^2 / 64 per instance; bound by
-// latency (0.19 ms for 256 diamonds of 512 to 8192 points, two workgroups per CU).
+// Tables: a workgroup per (instance, group of kTabBlocks column blocks), one wavefront per
+// column block J.  F(64 J, x) is a rank query on the set of v places of the points with u
+// place below 64 J: a bit per v place, with the running count beside every 32 of them.
+// The group's first set comes from sigma (one ballot per 64 places), the others add the
+// preceding blocks' points.  A query is one 8-byte LDS gather and a popcount, about nine
+// operations per table entry; scattering F through LDS from a scan of sigma by every
+// wavefront took 146 us for 256 diamonds of 512 to 8192 points, this takes 70 us (97 MB
+// written).
 // ---------------------------------------------------------------------------
-constexpr int kTabWaves = 4;
-constexpr int kTabUnroll = 4;
+constexpr int kTabThreads = 64 * kTabBlocks;
+constexpr int kTabWords = (int)(kBatchMaxN / 32);
 
-__global__ __launch_bounds__(64 * kTabWaves) void k_rank_tables(const RankInst* __restrict__ rank,
-                                                                const uint32_t* __restrict__ items,
-                                                                int64_t nitems,
-                                                                char* __restrict__ base) {
-  __shared__ uint16_t lds[kTabWaves][kBatchMaxN];
+__global__ __launch_bounds__(kTabThreads) void k_rank_tables(const RankInst* __restrict__ rank,
+                                                             const uint32_t* __restrict__ items,
+                                                             char* __restrict__ base) {
+  __shared__ uint16_t pis[kBatchMaxN] __attribute__((aligned(16)));
+  __shared__ uint32_t first[kTabWords] __attribute__((aligned(16)));
+  __shared__ uint32_t own[kTabBlocks][kTabWords] __attribute__((aligned(16)));
+  __shared__ uint2 sets[kTabBlocks][kTabWords] __attribute__((aligned(16)));  // bits, count below
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const int64_t it = (int64_t)blockIdx.x * kTabWaves + wave;
-  if (it >= nitems) return;  // no workgroup barrier below
-  const uint32_t item = items[it];
+  const uint32_t item = __builtin_amdgcn_readfirstlane(items[blockIdx.x]);
   const RankInst d = rank[item >> 16];
-  const int J = (int)(item & 0xFFFFu), n = d.n, lim = 64 * J;
-  const uint16_t* sigma = (const uint16_t*)(base + d.sigma_off());
-  const uint16_t* pi = (const uint16_t*)(base + d.pi_off());
-  uint16_t* F = lds[wave];  // F[i] = F(64 J, pi_i)
-  uint32_t run = 0;
-  for (int x0 = 0; x0 < n; x0 += 64 * kTabUnroll) {
-    uint32_t s[kTabUnroll];
-#pragma unroll
-    for (int q = 0; q < kTabUnroll; ++q) {
-      const int x = x0 + 64 * q + lane;
-      s[q] = x < n ? sigma[x] : 0xFFFFu;
+  const int J0 = (int)(item & 0xFFFFu) * kTabBlocks, J = J0 + wave;
+  const int n = d.n, lim = 64 * J;
+  const uint16_t* __restrict__ sigma = (const uint16_t*)(base + d.sigma_off());
+  const uint16_t* __restrict__ pi = (const uint16_t*)(base + d.pi_off());
+  for (int r = 8 * threadIdx.x; r < 64 * d.nb; r += 8 * kTabThreads)
+    *(uint4*)(pis + r) = *(const uint4*)(pi + r);
+  for (int w = wave; w < d.nb; w += kTabBlocks) {  // sigma is 0xFFFF past n
+    const uint64_t m = __ballot((int)sigma[64 * w + lane] < 64 * J0);
+    if (lane == 0) *(uint2*)(first + 2 * w) = make_uint2((uint32_t)m, (uint32_t)(m >> 32));
+  }
+  for (int w = 2 * d.nb + threadIdx.x; w < kTabWords; w += kTabThreads) first[w] = 0;
+  *(uint4*)(own[wave] + 4 * lane) = make_uint4(0, 0, 0, 0);
+  const int i = lim + lane;  // the block's own points
+  const uint32_t p = i < n ? pi[i] : 0u;
+  if (i < n) atomicOr(&own[wave][p >> 5], 1u << (p & 31));
+  __syncthreads();
+  if (J >= d.nb) return;  // no barrier below
+  {
+    uint4 v = *(const uint4*)(first + 4 * lane);
+    for (int w = 0; w < wave; ++w) {
+      const uint4 o = *(const uint4*)(own[w] + 4 * lane);
+      v.x |= o.x;
+      v.y |= o.y;
+      v.z |= o.z;
+      v.w |= o.w;
     }
+    const uint32_t c0 = __popc(v.x), c1 = c0 + __popc(v.y), c2 = c1 + __popc(v.z);
+    const uint32_t sum = c2 + __popc(v.w);
+    uint32_t x = sum;
 #pragma unroll
-    for (int q = 0; q < kTabUnroll; ++q) {
-      const uint64_t m = __ballot((int)s[q] < lim);
-      const uint32_t f = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
-                                                   __builtin_amdgcn_mbcnt_lo((uint32_t)m, run));
-      if (s[q] != 0xFFFFu) F[s[q]] = (uint16_t)f;
-      run += (uint32_t)__popcll(m);
+    for (int k = 1; k < 64; k <<= 1) {
+      const uint32_t y = __shfl_up(x, k);
+      if (lane >= k) x += y;
     }
+    x -= sum;
+    *(uint4*)(sets[wave] + 4 * lane) = make_uint4(v.x, x, v.y, x + c0);
+    *(uint4*)(sets[wave] + 4 * lane + 2) = make_uint4(v.z, x + c1, v.w, x + c2);
   }
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  uint32_t* tab = (uint32_t*)(base + d.tab_off(J));
-  for (int i = 2 * lane; i < lim; i += 128) {  // 64 J entries, two per lane
-    const uint32_t f2 = *(const uint32_t*)(F + i);
-    *(uint2*)(tab + i) = make_uint2((f2 & 0xFFFFu) << 2, (f2 >> 16) << 2);
+  auto F = [&](uint32_t x) -> uint32_t {
+    const uint2 w = sets[wave][x >> 5];
+    return w.y + __popc(w.x & ((1u << (x & 31)) - 1u));
+  };
+  auto entry = [&](uint32_t x) -> uint32_t { return x << 16 | F(x) << 2; };
+  uint32_t* __restrict__ tab = (uint32_t*)(base + d.tab_off(J));
+#pragma unroll 2
+  for (int r = 4 * lane; r < lim; r += 256) {  // 64 J entries, four per lane
+    const uint2 q = *(const uint2*)(pis + r);
+    *(uint4*)(tab + r) = make_uint4(entry(q.x & 0xFFFFu), entry(q.x >> 16), entry(q.y & 0xFFFFu),
+                                    entry(q.y >> 16));
   }
   if (J > 0 && J % kRankSegBlocks == 0) {
     uint16_t* seg = (uint16_t*)(base + d.seg_off(J / kRankSegBlocks));
-    for (int i = lim + lane; i < n; i += 64) seg[i] = F[i];
+#pragma unroll 2
+    for (int r = lim + 4 * lane; r < n; r += 256) {
+      const uint2 q = *(const uint2*)(pis + r);
+      *(uint2*)(seg + r) = make_uint2(F(q.x & 0xFFFFu) | F(q.x >> 16) << 16,
+                                      F(q.y & 0xFFFFu) | F(q.y >> 16) << 16);
+    }
   }
-  // The block's own points: D_i = F(64 J, pi_i) + #{64 J <= k < i : pi_k < pi_i}.
-  const int i = lim + lane;
-  const uint32_t p = i < n ? pi[i] : 0u;
-  uint32_t D = i < n ? F[i] : 0u;
+  // D_i = F(64 J, pi_i) + #{64 J <= k < i : pi_k < pi_i}.
+  uint32_t D = F(p);
 #pragma unroll 8
   for (int k = 0; k < 63; ++k) {
     const uint32_t pk = __builtin_amdgcn_readlane(p, k);
@@ -94,36 +125,64 @@ __global__ __launch_bounds__(64 * kTabWaves) void k_rank_tables(const RankInst* 
 // ---------------------------------------------------------------------------
 // Counts.  Persistent workgroups of kRankWaves wavefronts, one LDS histogram each; an item
 // is `per_item` units of one instance, dealt to the wavefronts in turn.  A row costs five
-// VALU operations for 64 pairs and one LDS add on the related lanes (about half), which
-// is the bound: 256 diamonds of 512 to 8192 points (3.1e9 pairs) take 0.73 ms, 8.1 cycles
-// per row and CU, where the fp4 matrix-core tiles took 3.15 ms.
+// VALU and three scalar operations for 64 pairs and one LDS add on the related lanes (about
+// half): 256 diamonds of 512 to 8192 points (3.1e9 pairs) take 0.66 ms, 7.3 cycles per
+// row and CU, where the fp4 matrix-core tiles took 3.15 ms.  Issue is the bound: the VALU
+// is busy 68 % of the time, the scalar unit 62 %, the LDS 59 % (without the adds a copy
+// of the kernel took 0.60 ms; 16 rows per fetch 0.68 ms).
 // ---------------------------------------------------------------------------
 constexpr int kRankThreads = 64 * kRankWaves;
 constexpr int kRankBins = (int)kBatchMaxN - 1;
-constexpr int kRankRows = 8;  // rows per scalar fetch
+constexpr int kRankRows = 8;   // rows per scalar fetch
 
-// One row against the 64 columns of the lanes.  x: pi_i << 16 plus 4 (D_i - F(64 J, pi_i)),
-// a difference in [-4 pi_i, 256], so x < pi_j << 16 is the relation, and its low half,
-// sign-extended, the row's share of the bin's byte address.  H = A_j(i) - lane.
-__device__ __forceinline__ void rank_row(uint32_t x, uint64_t keep, uint32_t pj, int32_t& H,
-                                         uint32_t* hist) {
-  const uint64_t m = __builtin_amdgcn_ballot_w64(x < pj) & keep;
-  const int32_t t = (int32_t)__builtin_amdgcn_mbcnt_hi(
+// One row against the 64 columns of the lanes.  x: pi_i << 16 with low bits of no weight
+// (x < pi_j << 16 is the relation); c = 4 (D_i - F(64 J, pi_i)), the row's share of the bin's
+// byte address; H = A_j(i) - lane.  The add runs on the related lanes only: every lane is
+// active around it, and written out it leaves the rows one straight block of code instead
+// of a branch per row.
+__device__ __forceinline__ void rank_row(uint32_t x, int32_t c, bool keep, uint32_t pj, int32_t& H,
+                                         uint32_t hist, uint32_t one) {
+  const bool rel = (x < pj) & keep;
+  const uint64_t m = __builtin_amdgcn_ballot_w64(rel);
+  const uint32_t t = __builtin_amdgcn_mbcnt_hi(
       (uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, (uint32_t)H));
-  const int32_t addr = (t << 2) + (int32_t)(int16_t)(uint16_t)x;
-  if (__builtin_amdgcn_inverse_ballot_w64(m)) atomicAdd((uint32_t*)((char*)hist + addr), 1u);
-  uint64_t carry_out;  // H + this lane's bit of m, in one add
-  asm("v_addc_co_u32_e64 %0, %1, %2, 0, %3" : "=v"(H), "=s"(carry_out) : "v"(H), "s"(m));
+  const uint32_t addr = (t << 2) + (uint32_t)c + hist;
+  asm volatile("s_mov_b64 exec, %0\n\tds_add_u32 %1, %2\n\ts_mov_b64 exec, -1"
+               :
+               : "s"(m), "v"(addr), "v"(one));
+  H += rel ? 1 : 0;        // a carry-in add of m, kept apart from the next row's:
+  asm("" : "+v"(H));  // combined, the two would take a select more
 }
 
+// kRankRows rows of the point and table arrays (wave-uniform: scalar loads).
+struct RowChunk {
+  uint32_t x[kRankRows], y[kRankRows];
+  __device__ __forceinline__ void fetch(const uint32_t* __restrict__ row,
+                                        const uint32_t* __restrict__ tab, int i) {
+#pragma unroll
+    for (int q = 0; q < kRankRows; ++q) {
+      x[q] = row[i + q];
+      y[q] = tab[i + q];
+    }
+  }
+  // Waits for the fetch here, so that the next one can be issued before these rows are
+  // used (scalar loads return out of order: any wait is for all of them).
+  __device__ __forceinline__ void arrive() {
+    asm volatile("" ::"s"(x[0]), "s"(y[0]) : "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  }
+};
+
+// hist: LDS byte address of the workgroup's bins.
 __device__ inline void rank_unit(const RankInst& d, const char* __restrict__ base, int J, int s,
-                                 uint32_t* hist) {
+                                 uint32_t hist) {
   const int lane = threadIdx.x & 63;
   const int n = d.n, j = 64 * J + lane;
   const uint32_t* __restrict__ row = (const uint32_t*)(base + d.row_off());
   const uint32_t* __restrict__ tab = (const uint32_t*)(base + d.tab_off(J));
   const uint32_t own = j < n ? row[j] : 0u;
   const uint32_t pj = own & 0xFFFF0000u;  // 0 past n: above no row
+  const uint32_t one = 1u;
   const int lo = 64 * kRankSegBlocks * s;
   int hi = lo + 64 * kRankSegBlocks;
   int32_t H = -lane;
@@ -133,18 +192,27 @@ __device__ inline void rank_unit(const RankInst& d, const char* __restrict__ bas
   } else {  // the diagonal block: columns above the row's own, B_i counted from there
     hi = 64 * J;
     const int last = n - hi < 64 ? n - hi : 64;
-    for (int r = last - 1; r >= 0; --r) {
-      const uint32_t pr = __builtin_amdgcn_readlane(pj, r);
-      rank_row(pr + 4u * (uint32_t)(r + 1), r == 63 ? 0ull : ~0ull << (r + 1), pj, H, hist);
+    for (int r = last - 1; r >= 0; --r)
+      rank_row(__builtin_amdgcn_readlane(pj, r), 4 * (r + 1), lane > r, pj, H, hist, one);
+  }
+  auto rows = [&](const RowChunk& c) {
+#pragma unroll
+    for (int q = kRankRows - 1; q >= 0; --q)
+      rank_row(c.x[q], (int32_t)(c.x[q] - c.y[q]), true, pj, H, hist, one);
+  };
+  if (hi > lo) {  // a multiple of 64 rows, two chunks in turn
+    RowChunk a, b;
+    a.fetch(row, tab, hi - kRankRows);
+    for (int i = hi - kRankRows; i > lo; i -= 2 * kRankRows) {
+      a.arrive();
+      b.fetch(row, tab, i - kRankRows);
+      rows(a);
+      b.arrive();
+      a.fetch(row, tab, i - kRankRows > lo ? i - 2 * kRankRows : lo);
+      rows(b);
     }
   }
-  for (int i = hi - kRankRows; i >= lo; i -= kRankRows) {
-    uint32_t x[kRankRows];
-#pragma unroll
-    for (int q = 0; q < kRankRows; ++q) x[q] = row[i + q] - tab[i + q];
-#pragma unroll
-    for (int q = kRankRows - 1; q >= 0; --q) rank_row(x[q], ~0ull, pj, H, hist);
-  }
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the adds have reached LDS
 }
 
 __global__ __launch_bounds__(kRankThreads, 8) void k_count_ranks(
@@ -198,7 +266,7 @@ __global__ __launch_bounds__(kRankThreads, 8) void k_count_ranks(
       const int rest = (int)(u - 2ll * Q * (Q + 1));
       const int J = __builtin_amdgcn_readfirstlane(kRankSegBlocks * Q + rest / (Q + 1));
       const int s = __builtin_amdgcn_readfirstlane(rest % (Q + 1));
-      rank_unit(d, base, J, s, hist);
+      rank_unit(d, base, J, s, (uint32_t)(uintptr_t)hist);
     }
   }
   __syncthreads();
@@ -212,8 +280,8 @@ __global__ __launch_bounds__(kRankThreads, 8) void k_count_ranks(
 cs_status launch_rank_tables(const RankInst* rank, const uint32_t* items, int64_t nitems,
                              char* rank_base, hipStream_t st) {
   if (nitems <= 0) return CS_OK;
-  hipLaunchKernelGGL(k_rank_tables, dim3((unsigned)ceil_div(nitems, kTabWaves)),
-                     dim3(64 * kTabWaves), 0, st, rank, items, nitems, rank_base);
+  hipLaunchKernelGGL(k_rank_tables, dim3((unsigned)nitems), dim3(kTabThreads), 0, st, rank, items,
+                     rank_base);
   CS_LAUNCH_CHECK();
   return CS_OK;
 }

@@ -633,9 +633,9 @@ __global__ __launch_bounds__(kBatchSortThreads) void k_sprinkle_mink2_batch(
   __syncthreads();
   uint16_t* sigma = (uint16_t*)(rank_base + r.sigma_off());
   uint16_t* pi = (uint16_t*)(rank_base + r.pi_off());
-  for (int i = t; i < n; i += kBatchSortThreads) {
-    sigma[i] = perm[i];
-    pi[i] = perm[kBatchMaxN + i];
+  for (int i = t; i < 64 * r.nb; i += kBatchSortThreads) {
+    sigma[i] = i < n ? perm[i] : (uint16_t)0xFFFFu;
+    pi[i] = i < n ? perm[kBatchMaxN + i] : (uint16_t)0u;
   }
 }
 
