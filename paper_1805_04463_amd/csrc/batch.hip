@@ -3,7 +3,7 @@
 // causal sets; here the ensemble is one pipeline of four launches.)
 //
 // Plan: per-instance offsets into three concatenated buffers (coordinates, matrices,
-// histograms), the builder's work lists (items of 4x2 blocks of 64x64, per XCD) and
+// histograms), the builder's work lists (groups of 512 columns, per XCD) and
 // the counters' work lists (one item per row panel I of output tiles, i.e. all tiles
 // (I, J >= I) of an instance, so a workgroup keeps one instance's histogram in LDS for
 // a whole panel), dealt to one queue per XCD: whole instances, largest first to the
@@ -182,7 +182,7 @@ struct cs_batch_plan_t {
   BatchTile slot_cfg[kMaxSlots] = {};
   int64_t n_items[kMaxSlots] = {};
   BatchQueues queues[kMaxSlots] = {};
-  size_t ws_bytes = 0, off_coords = 0, off_bits = 0, off_rank = 0;
+  size_t ws_bytes = 0, off_coords = 0, off_bits = 0, off_uv = 0, off_rank = 0;
   int64_t n_tab = 0;                // work items of the rank tables
   int rank_units = kRankWaves;      // counting units per item
   void* dev = nullptr;              // device tables
@@ -211,7 +211,6 @@ cs_status build_plan(int64_t count, const int64_t* n, int counter, int n_eps, co
   p->counter = counter;
   p->n_eps = n_eps;
   p->inst.resize(count);
-  std::vector<std::vector<uint32_t>> bitems(count);  // builder items of each instance
   struct Item {
     uint32_t packed;
     int64_t cost;
@@ -233,19 +232,6 @@ cs_status build_plan(int64_t count, const int64_t* n, int counter, int n_eps, co
     boff += d.n * d.ld;
     hoff += d.n - 1;
     const int64_t nb = ceil_div(d.n, 64);
-    // Builder items (row group g: row blocks kBuildRowBlocks g + r; column blocks bj0 + c)
-    // in patches of kBuildPatch x kBuildPatch blocks: a patch writes whole 128-byte lines
-    // of its rows' words and of its transposed words, so the lines are complete while the
-    // XCD that builds the instance holds them in its L2.
-    static_assert(kBuildPatch % kBuildRowBlocks == 0 && kBuildPatch % kBuildColBlocks == 0 &&
-                      kBuildRowBlocks % kBuildColBlocks == 0, "builder items tile the patches");
-    constexpr int64_t G = kBuildPatch / kBuildRowBlocks;  // row groups per patch
-    for (int64_t pr = 0; pr * kBuildPatch < nb; ++pr)
-      for (int64_t pc = pr; pc * kBuildPatch < nb; ++pc)
-        for (int64_t g = pr * G; g < pr * G + G && g * kBuildRowBlocks < nb; ++g)
-          for (int64_t bj = std::max(pc * kBuildPatch, g * kBuildRowBlocks);
-               bj < std::min((pc + 1) * kBuildPatch, nb); bj += kBuildColBlocks)
-            bitems[k].push_back((uint32_t)(k << 16 | g << 8 | bj));
     const int b = bucket_of(d.n);
     const BatchTile cfg = force ? *force : tune.choice(cslot, b);
     int slot = -1;
@@ -275,28 +261,27 @@ cs_status build_plan(int64_t count, const int64_t* n, int counter, int n_eps, co
   p->coords_len = coff;
   p->bits_len = boff;
   p->hist_len = hoff;
-  // Builder lists, one per XCD: whole instances dealt largest first to the shortest list,
-  // so that every line of a matrix is written from one L2 (partial lines written back
-  // from several XCDs multiplied the builder's HBM writes).  Workgroup b takes list
-  // b mod 8 (the XCD that the dispatcher gives it), entries kBuildWaves (b div 8) + wave;
-  // lists are padded with kNoBuildItem to one length, a multiple of kBuildWaves.
+  // Builder lists, one per XCD: whole instances dealt largest first to the least loaded
+  // list, so that every line of a matrix is written from one L2 (partial lines written
+  // back from several XCDs multiplied the builder's HBM writes).  Workgroup b takes entry
+  // b div 8 of list b mod 8 (the XCD that the dispatcher gives it): a group of 512 columns
+  // of an instance.  Lists are padded with kNoBuildItem to one length.
   std::vector<uint32_t> build;
   {
     std::vector<int64_t> order(count);
     for (int64_t k = 0; k < count; ++k) order[k] = k;
-    std::stable_sort(order.begin(), order.end(), [&](int64_t a, int64_t b) {
-      return bitems[a].size() > bitems[b].size();
-    });
+    std::stable_sort(order.begin(), order.end(),
+                     [&](int64_t a, int64_t b) { return p->inst[a].n > p->inst[b].n; });
     std::vector<uint32_t> lists[kBatchQueues];
+    int64_t load[kBatchQueues] = {};
     for (int64_t k : order) {
-      int best = 0;
-      for (int x = 1; x < kBatchQueues; ++x)
-        if (lists[x].size() < lists[best].size()) best = x;
-      lists[best].insert(lists[best].end(), bitems[k].begin(), bitems[k].end());
+      const BatchInst& d = p->inst[k];
+      const int best = (int)(std::min_element(load, load + kBatchQueues) - load);
+      load[best] += d.n * d.ld;
+      for (int64_t g = 0; g < d.ld / 8; ++g) lists[best].push_back((uint32_t)(k << 16 | g));
     }
     size_t len = 0;
     for (auto& l : lists) len = std::max(len, l.size());
-    len = (len + kBuildWaves - 1) / kBuildWaves * kBuildWaves;
     build.assign(len * kBatchQueues, kNoBuildItem);
     for (int x = 0; x < kBatchQueues; ++x)
       std::copy(lists[x].begin(), lists[x].end(), build.begin() + x * len);
@@ -361,12 +346,14 @@ cs_status build_plan(int64_t count, const int64_t* n, int counter, int n_eps, co
     p->n_items[s] = (int64_t)items[s].size();
   }
 
-  // Caller workspace: [work counters, per slot][coordinates][matrices][rank tables].
+  // Caller workspace: [work counters, per slot][coordinates][matrices][u and v places][rank
+  // tables].
   size_t off = 0;
   static_assert(sizeof(unsigned int) * kMaxSlots * kBatchQueues == 256, "work counters");
   take(&off, 256);
   p->off_coords = take(&off, sizeof(double) * (size_t)coff);
   p->off_bits = take(&off, sizeof(uint64_t) * (size_t)boff);
+  p->off_uv = take(&off, sizeof(uint32_t) * (size_t)(coff / 2));
   p->off_rank = take(&off, (size_t)roff);
   p->ws_bytes = off;
 
@@ -481,13 +468,14 @@ cs_status cs_batch_run(cs_batch_plan_handle plan, const uint64_t* seeds, uint64_
   unsigned int* ctr = (unsigned int*)ws;
   double* coords = (double*)(ws + plan->off_coords);
   uint64_t* bits = (uint64_t*)(ws + plan->off_bits);
+  uint32_t* uv = (uint32_t*)(ws + plan->off_uv);
   cs_status s;
   // the sprinkle kernel also clears the histograms and the work counters
   if ((s = launch_sprinkle_batch(seeds, plan->d_inst, plan->d_rank, plan->count, coords,
-                                 ws + plan->off_rank, hist, (uint64_t*)ctr,
+                                 uv, ws + plan->off_rank, hist, (uint64_t*)ctr,
                                  kMaxSlots * kBatchQueues / 2, st)) != CS_OK)
     return s;
-  if ((s = launch_build_batch(coords, plan->d_inst, plan->d_build, plan->n_build, bits, st)) != CS_OK)
+  if ((s = launch_build_batch(uv, plan->d_inst, plan->d_build, plan->n_build, bits, st)) != CS_OK)
     return s;
   if ((s = run_counts(plan, ws, hist, st)) != CS_OK) return s;
   return launch_action_batch(hist, plan->d_inst, plan->count, 2, plan->d_eps, plan->n_eps, actions,

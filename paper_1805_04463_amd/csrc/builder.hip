@@ -10,8 +10,7 @@
 // shuffles) turns those row words into the words of rows j for column block bi, so each
 // unordered pair is tested once and both halves of the symmetric matrix are written.
 // Workgroups walk 1024 x 1024-point patches, one XCD per patch (k_build).  The ensemble
-// builder gives each wave several row blocks against one column block, so that each
-// column point read from LDS serves several rows of a lane.
+// builder takes its words from the points' places in u and v instead (k_build_batch).
 //
 // Arithmetic: fp64, in the order written, no contraction (built with
 // -ffp-contract=off and explicit round-to-nearest intrinsics); on CDNA4 fp64 VALU
@@ -237,18 +236,18 @@ __device__ __attribute__((always_inline)) inline void row_words(
   for (int r = 0; r < RB; ++r) out[r] = ((uint64_t)half[r][1] << 32) | half[r][0];
 }
 
-// One wave: the 64x64 blocks (bi0 + r, bj0 + c), r < RB, c < CB, of an n-point matrix S
-// with stride ld, those with bi0 + r <= bj0 + c < nb (bi0 <= bj0; both wave-uniform).
-// Lane l owns rows i = 64 (bi0 + r) + l and collects their row words for the 64 column
-// points of each block bj0 + c.  The transposed words (rows of block bj0 + c, columns of
-// block bi0 + r) come from a 64x64 bit transpose of each row word, so each unordered pair
-// is tested once.  Blocks below the diagonal are tested but not written.  The wave owning
-// the last column block of a row block also zeroes that row block's padding words
-// [nb, ld), so every word of S is written exactly once.
-template <int R, int RB, int CB>
+// One wave: the 64x64 blocks (bi0 + r, bj), r < RB, of an n-point matrix S with stride ld,
+// those with bi0 + r <= bj (bi0 <= bj; both wave-uniform).  Lane l owns rows
+// i = 64 (bi0 + r) + l and collects their row words for the 64 column points of block bj.
+// The transposed words (rows of block bj, columns of block bi0 + r) come from a 64x64 bit
+// transpose of each row word, so each unordered pair is tested once.  Blocks below the
+// diagonal are tested but not written.  The wave owning the last column block of a row
+// block also zeroes that row block's padding words [nb, ld), so every word of S is written
+// exactly once.
+template <int R, int RB>
 __device__ __attribute__((always_inline)) inline void build_block(
     const double* __restrict__ coords, int64_t n, uint64_t* __restrict__ S, int64_t ld, int64_t nb,
-    int64_t bi0, int64_t bj0, Pt<R>* cols) {
+    int64_t bi0, int64_t bj, Pt<R>* cols) {
   const int lane = threadIdx.x & 63;
   Pt<R> pi[RB];
 #pragma unroll
@@ -256,83 +255,55 @@ __device__ __attribute__((always_inline)) inline void build_block(
     const int64_t i = (bi0 + r) * 64 + lane;
     pi[r] = load_pt(coords, n, i < n ? i : n - 1, (Pt<R>*)nullptr);
   }
-  uint64_t rows[CB][RB];
-  if (bj0 * 64 + 64 <= n) row_words<R, true, RB>(coords, n, bj0 * 64, pi, cols, rows[0]);
-  else row_words<R, false, RB>(coords, n, bj0 * 64, pi, cols, rows[0]);
-  if constexpr (CB == 2) {
-    const int64_t bj = bj0 + 1;
-    if (bj < nb) {
-      if (bj * 64 + 64 <= n) row_words<R, true, RB>(coords, n, bj * 64, pi, cols, rows[1]);
-      else row_words<R, false, RB>(coords, n, bj * 64, pi, cols, rows[1]);
-    }
-  }
+  uint64_t rows[RB];
+  if (bj * 64 + 64 <= n) row_words<R, true, RB>(coords, n, bj * 64, pi, cols, rows);
+  else row_words<R, false, RB>(coords, n, bj * 64, pi, cols, rows);
+  const int64_t j = bj * 64 + lane;
+  const bool jv = j < n;
+  const int64_t ncols = n - bj * 64;  // valid columns of the block (>= 1)
   if constexpr (RB == 4) {
-    if (bi0 + RB - 1 < bj0 && bj0 + CB - 1 < nb) {
+    if (bi0 + RB - 1 < bj) {
       // Every block lies above the diagonal and every row is valid: a lane's four
       // transposed words of row j (column blocks bi0 .. bi0 + 3) are contiguous and 16-byte
-      // aligned (bi0 is a multiple of 4, rows start on 64-byte boundaries), and so are its
-      // two row words of row i with two column blocks (bj0 even), so they go out as 16-byte
-      // stores instead of 8-byte ones.
-#pragma unroll
-      for (int c = 0; c < CB; ++c) {
-        const int64_t ncols = n - (bj0 + c) * 64;  // valid columns of the block (>= 1)
-        if (ncols < 64)
-#pragma unroll
-          for (int r = 0; r < RB; ++r) rows[c][r] &= (1ull << ncols) - 1ull;
-      }
+      // aligned (bi0 is a multiple of 4, rows start on 64-byte boundaries), so they go out
+      // as 16-byte stores instead of 8-byte ones.
+      uint64_t cw[RB];
 #pragma unroll
       for (int r = 0; r < RB; ++r) {
+        if (ncols < 64) rows[r] &= (1ull << ncols) - 1ull;
         const int64_t i = (bi0 + r) * 64 + lane;
-        if constexpr (CB == 2)
-          *(uint4*)(S + i * ld + bj0) = make_uint4((uint32_t)rows[0][r], (uint32_t)(rows[0][r] >> 32),
-                                                   (uint32_t)rows[1][r], (uint32_t)(rows[1][r] >> 32));
-        else
-          S[i * ld + bj0] = rows[0][r];
-        if (bj0 + CB - 1 == nb - 1)
+        S[i * ld + bj] = rows[r];
+        if (bj == nb - 1)
           for (int64_t w = nb; w < ld; ++w) S[i * ld + w] = 0;
+        cw[r] = wave_transpose64(rows[r]);
       }
-#pragma unroll
-      for (int c = 0; c < CB; ++c) {
-        uint64_t cw[RB];
-#pragma unroll
-        for (int r = 0; r < RB; ++r) cw[r] = wave_transpose64(rows[c][r]);
-        const int64_t j = (bj0 + c) * 64 + lane;
-        if (j < n) {
-          uint4* dst = (uint4*)(S + j * ld + bi0);
-          dst[0] = make_uint4((uint32_t)cw[0], (uint32_t)(cw[0] >> 32), (uint32_t)cw[1], (uint32_t)(cw[1] >> 32));
-          dst[1] = make_uint4((uint32_t)cw[2], (uint32_t)(cw[2] >> 32), (uint32_t)cw[3], (uint32_t)(cw[3] >> 32));
-        }
+      if (jv) {
+        uint4* dst = (uint4*)(S + j * ld + bi0);
+        dst[0] = make_uint4((uint32_t)cw[0], (uint32_t)(cw[0] >> 32), (uint32_t)cw[1], (uint32_t)(cw[1] >> 32));
+        dst[1] = make_uint4((uint32_t)cw[2], (uint32_t)(cw[2] >> 32), (uint32_t)cw[3], (uint32_t)(cw[3] >> 32));
       }
       return;
     }
   }
 #pragma unroll
-  for (int c = 0; c < CB; ++c) {
-    const int64_t bj = bj0 + c;
-    if (c > 0 && bj >= nb) break;
-    const int64_t j = bj * 64 + lane;
-    const bool jv = j < n;
-    const int64_t ncols = n - bj * 64;  // valid columns of this block (>= 1)
-#pragma unroll
-    for (int r = 0; r < RB; ++r) {
-      const int64_t bi = bi0 + r;
-      if (bi > bj) break;  // this and the later row blocks lie below the diagonal
-      const int64_t i = bi * 64 + lane;
-      const bool iv = i < n;
-      uint64_t row = rows[c][r];
-      if (ncols < 64) row &= (1ull << ncols) - 1ull;
-      if (bi == bj) row &= lane == 63 ? 0ull : (~0ull << (lane + 1));  // only j > i
-      if (!iv) row = 0;
-      const uint64_t col = wave_transpose64(row);  // lane l: row j's bits for columns of bi
-      if (bi == bj) {
-        if (iv) S[i * ld + bi] = row | col;
-      } else {
-        if (iv) S[i * ld + bj] = row;
-        if (jv) S[j * ld + bi] = col;
-      }
-      if (bj == nb - 1 && iv)
-        for (int64_t w = nb; w < ld; ++w) S[i * ld + w] = 0;
+  for (int r = 0; r < RB; ++r) {
+    const int64_t bi = bi0 + r;
+    if (bi > bj) break;  // this and the later row blocks lie below the diagonal
+    const int64_t i = bi * 64 + lane;
+    const bool iv = i < n;
+    uint64_t row = rows[r];
+    if (ncols < 64) row &= (1ull << ncols) - 1ull;
+    if (bi == bj) row &= lane == 63 ? 0ull : (~0ull << (lane + 1));  // only j > i
+    if (!iv) row = 0;
+    const uint64_t col = wave_transpose64(row);  // lane l: row j's bits for columns of bi
+    if (bi == bj) {
+      if (iv) S[i * ld + bi] = row | col;
+    } else {
+      if (iv) S[i * ld + bj] = row;
+      if (jv) S[j * ld + bi] = col;
     }
+    if (bj == nb - 1 && iv)
+      for (int64_t w = nb; w < ld; ++w) S[i * ld + w] = 0;
   }
 }
 
@@ -380,32 +351,123 @@ __global__ __launch_bounds__(256) void k_build(const double* __restrict__ coords
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int64_t bj = (px * kGroups + l % kGroups) * kWavesPerBlock + wave;
   if (bi >= nb || bj >= nb || bj < bi) return;  // wave-uniform exit; no block barriers below
-  build_block<R, RB, 1>(coords, n, S, ld, nb, bi, bj, cols[kScalarColumns<R> ? 0 : wave]);
+  build_block<R, RB>(coords, n, S, ld, nb, bi, bj, cols[kScalarColumns<R> ? 0 : wave]);
 }
 
-// Ensemble of 1+1 diamonds.  Work items are packed as instance << 16 | g << 8 | bj0: row
-// blocks kBuildRowBlocks g + r against column blocks bj0 + c, c < kBuildColBlocks, with
-// bj0 >= kBuildRowBlocks g a multiple of kBuildColBlocks.  Each column point read from LDS
-// serves kBuildRowBlocks rows of the lane, which takes the blocks off the LDS bound of one
-// row per lane, and the words of whole groups leave in 16-byte stores.  The items form kBatchQueues lists of
-// equal length (one per XCD, padded with kNoBuildItem); wave w of workgroup b takes
-// entry kBuildWaves (b div kBatchQueues) + w of list b mod kBatchQueues.
-static_assert(kWavesPerBlock == kBuildWaves, "ensemble builder lists are dealt per workgroup");
-__global__ __launch_bounds__(256) void k_build_batch(const double* __restrict__ coords,
-                                                     const BatchInst* __restrict__ inst,
-                                                     const uint32_t* __restrict__ items,
-                                                     int64_t nitems, uint64_t* __restrict__ bits) {
-  __shared__ Pt<CS_MINK2_DIAMOND> cols[kWavesPerBlock][64];
+// Ensemble of 1+1 diamonds, from the points' places in u and v (uv: u place << 16 | v place
+// per point, in time order; equal coordinates hold opposite orders in the two, as they are
+// unrelated).  Two points are related exactly when their places compare the same way in u
+// and v, so the word of a row for a block of 64 columns is the XNOR of two masks: the
+// block's points above the row's in u, and in v.  Each mask depends only on how many of
+// the block's points lie below the row's place: that count is a rank query (a bit per
+// place with running counts, as in the rank tables) and picks one of 65 precomputed
+// masks.  Four 8-byte LDS gathers and a dozen operations give 64 pairs of one row, against
+// 192 operations for testing the pairs, and rows below the diagonal need no transpose: 256
+// diamonds of 512 to 8192 points take 0.19 ms for 0.82 GB of matrices (4.3 TB/s; the LDS is
+// busy 35 % of the time, the VALU 16 %), against 0.41 ms with the pair tests.
+//
+// A workgroup takes kBuildBlocks column blocks of an instance (512 columns: a lane's words
+// of a row are 64 contiguous bytes, padding words included) against all its rows.  The
+// items (instance << 16 | column group) form kBatchQueues lists of equal length, one per
+// XCD, padded with kNoBuildItem: workgroup b takes entry b div kBatchQueues of list
+// b mod kBatchQueues, the XCD that the dispatcher gives it, whose L2 completes the lines.
+constexpr int kBuildBlocks = 8;
+constexpr int kBuildTables = 2 * kBuildBlocks;  // (block, axis); one wavefront each
+constexpr int kBuildThreads = 64 * kBuildTables;
+constexpr int kBuildWords = (int)(kBatchMaxN / 32);
+
+__global__ __launch_bounds__(kBuildThreads, 8) void k_build_batch(
+    const uint32_t* __restrict__ uvs, const BatchInst* __restrict__ inst,
+    const uint32_t* __restrict__ items, int64_t nitems, uint64_t* __restrict__ bits) {
+  __shared__ uint2 sets[kBuildTables][kBuildWords] __attribute__((aligned(16)));  // bits, count below
+  __shared__ uint64_t above[kBuildTables][66];  // [c]: columns with at least c of the block below
+  const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const int64_t per_list = nitems / kBatchQueues;
-  const int64_t t = (int64_t)(blockIdx.x % kBatchQueues) * per_list +
-                    (int64_t)(blockIdx.x / kBatchQueues) * kWavesPerBlock + wave;
-  const uint32_t it = items[t];
-  if (it == kNoBuildItem) return;
+  const uint32_t it = items[(int64_t)(blockIdx.x % kBatchQueues) * (nitems / kBatchQueues) +
+                            blockIdx.x / kBatchQueues];
+  if (it == kNoBuildItem) return;  // the whole workgroup
   const BatchInst d = inst[it >> 16];
-  build_block<CS_MINK2_DIAMOND, kBuildRowBlocks, kBuildColBlocks>(
-      coords + d.coord_off, d.n, bits + d.bits_off, d.ld, ceil_div(d.n, 64),
-      (int64_t)((it >> 8) & 255u) * kBuildRowBlocks, it & 255u, cols[wave]);
+  const uint32_t* __restrict__ uv = uvs + d.coord_off / 2;
+  const int n = (int)d.n, nb = (n + 63) / 64, b0 = (int)(it & 0xFFFFu) * kBuildBlocks;
+  auto query = [&](int a, uint32_t x) -> uint32_t {  // points of table a with place below x
+    const uint2 w = sets[a][x >> 5];
+    return w.y + __popc(w.x & ((1u << (x & 31)) - 1u));
+  };
+  auto wave_sync = [] {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  };
+  {  // wavefront 2 b + axis: the tables of column block b0 + b
+    const int j = 64 * (b0 + (wave >> 1)) + lane;
+    const bool valid = j < n;
+    const uint32_t t = valid ? uv[j] : 0u;
+    const uint32_t place = (wave & 1) ? t & 0xFFFFu : t >> 16;
+    uint4* s4 = (uint4*)(sets[wave] + 4 * lane);
+    s4[0] = make_uint4(0, 0, 0, 0);
+    s4[1] = make_uint4(0, 0, 0, 0);
+    above[wave][lane] = 0;
+    if (lane < 2) above[wave][64 + lane] = 0;
+    wave_sync();
+    if (valid) atomicOr(&sets[wave][place >> 5].x, 1u << (place & 31));
+    wave_sync();
+    const uint4 p0 = s4[0], p1 = s4[1];
+    const uint32_t c0 = __popc(p0.x), c1 = c0 + __popc(p0.z), c2 = c1 + __popc(p1.x);
+    const uint32_t sum = c2 + __popc(p1.z);
+    uint32_t x = sum;
+#pragma unroll
+    for (int k = 1; k < 64; k <<= 1) {
+      const uint32_t y = __shfl_up(x, k);
+      if (lane >= k) x += y;
+    }
+    x -= sum;
+    s4[0] = make_uint4(p0.x, x, p0.z, x + c0);
+    s4[1] = make_uint4(p1.x, x + c1, p1.z, x + c2);
+    wave_sync();
+    if (valid) above[wave][query(wave, place)] = 1ull << lane;
+    wave_sync();
+    uint64_t m = above[wave][lane];
+#pragma unroll
+    for (int k = 1; k < 64; k <<= 1) {  // suffix OR over the lanes
+      const uint32_t lo = __shfl_down((uint32_t)m, k), hi = __shfl_down((uint32_t)(m >> 32), k);
+      if (lane + k < 64) m |= (uint64_t)hi << 32 | lo;
+    }
+    above[wave][lane] = m;
+  }
+  __syncthreads();
+  // Four lanes per row, two words each: a store instruction writes 16 whole 64-byte
+  // segments.  (With a row per lane, its eight words in four stores, L2 took four partial
+  // requests per segment: 0.25 ms.)
+  const int quarter = lane & 3, own = 2 * quarter;  // this lane's blocks: b0 + own, + 1
+  const bool edge = 64 * (b0 + kBuildBlocks) > n;   // columns past n in this group
+  uint64_t* __restrict__ S = bits + d.bits_off + b0 + own;
+  for (int rb = wave; rb < nb; rb += kBuildTables) {
+    uint32_t t[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int i = 64 * rb + 16 * k + (lane >> 2);
+      t[k] = i < n ? uv[i] : 0u;
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int i = 64 * rb + 16 * k + (lane >> 2);
+      const uint32_t pu = t[k] >> 16, pv = t[k] & 0xFFFFu;
+      uint64_t w[2];
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        const int a = 2 * (own + e);
+        w[e] = ~(above[a][query(a, pu)] ^ above[a + 1][query(a + 1, pv)]);
+        if (rb - b0 == own + e) w[e] &= ~(1ull << (i & 63));  // not related to itself
+        if (edge) {
+          const int left = n - 64 * (b0 + own + e);
+          w[e] &= left >= 64 ? ~0ull : (left <= 0 ? 0ull : (1ull << left) - 1ull);
+        }
+      }
+      if (i < n)
+        *(uint4*)(S + (int64_t)i * d.ld) = make_uint4((uint32_t)w[0], (uint32_t)(w[0] >> 32),
+                                                      (uint32_t)w[1], (uint32_t)(w[1] >> 32));
+    }
+  }
 }
 
 template <int R, int RB>
@@ -446,12 +508,12 @@ cs_status launch_causal_matrix(int region, const double* coords, int64_t n, uint
   }
 }
 
-cs_status launch_build_batch(const double* coords, const BatchInst* inst, const uint32_t* items,
+cs_status launch_build_batch(const uint32_t* uv, const BatchInst* inst, const uint32_t* items,
                              int64_t nitems, uint64_t* bits, hipStream_t st) {
   if (nitems <= 0) return CS_OK;
-  if (nitems % (kBatchQueues * kWavesPerBlock) != 0) return CS_ERR_INVALID_ARG;
-  hipLaunchKernelGGL(k_build_batch, dim3((unsigned)(nitems / kWavesPerBlock)),
-                     dim3(64 * kWavesPerBlock), 0, st, coords, inst, items, nitems, bits);
+  if (nitems % kBatchQueues != 0) return CS_ERR_INVALID_ARG;
+  hipLaunchKernelGGL(k_build_batch, dim3((unsigned)nitems), dim3(kBuildThreads), 0, st, uv, inst,
+                     items, nitems, bits);
   CS_LAUNCH_CHECK();
   return CS_OK;
 }

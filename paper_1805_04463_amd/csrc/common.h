@@ -85,7 +85,7 @@ inline int coord_planes(int region) {
 
 // One instance of an ensemble: size, row stride (uint64 words) and offsets of its
 // coordinates (doubles), matrix (uint64 words) and histogram (uint64 bins) in the
-// concatenated buffers.
+// concatenated buffers.  Its u and v places (uint32) are at coord_off / 2.
 struct BatchInst {
   int64_t n, ld, coord_off, bits_off, hist_off;
 };
@@ -118,12 +118,7 @@ struct RankInst {
 // Largest instance of an ensemble (its whole histogram fits the LDS bins, its sort
 // fits one workgroup's LDS).
 constexpr int64_t kBatchMaxN = 8192;
-// Ensemble builder: row and column blocks of 64 points per work item, blocks per patch
-// side, waves per workgroup, and the padding entry of its per-XCD item lists.
-constexpr int kBuildRowBlocks = 4;
-constexpr int kBuildColBlocks = 2;
-constexpr int kBuildPatch = 16;
-constexpr int kBuildWaves = 4;
+// Padding entry of the ensemble builder's per-XCD item lists.
 constexpr uint32_t kNoBuildItem = 0xFFFFFFFFu;
 
 // ---------------------------------------------------------------------------
@@ -160,8 +155,8 @@ cs_status scratch_for_current_device(void** out);
 
 // Ensemble pieces (1+1 diamonds).
 cs_status launch_sprinkle_batch(const uint64_t* seeds, const BatchInst* inst, const RankInst* rank,
-                                int64_t count, double* coords, char* rank_base, uint64_t* hist,
-                                uint64_t* zero, int nzero, hipStream_t st);
+                                int64_t count, double* coords, uint32_t* uv, char* rank_base,
+                                uint64_t* hist, uint64_t* zero, int nzero, hipStream_t st);
 // Rank tables (items: instance << 16 | group of kTabBlocks column blocks), then the counts from them (items:
 // instance << 16 | chunk of `per_item` units; counter: one work counter, zero at launch).
 cs_status launch_rank_tables(const RankInst* rank, const uint32_t* items, int64_t nitems,
@@ -171,9 +166,8 @@ cs_status launch_count_ranks(const RankInst* rank, const uint32_t* items, int64_
                              unsigned int* counter, hipStream_t st);
 constexpr int kRankWaves = 16;  // wavefronts per workgroup of the rank counter
 constexpr int kTabBlocks = 16;  // column blocks per workgroup of the rank tables
-cs_status launch_build_batch(const double* coords, const BatchInst* inst,
-                             const uint32_t* items, int64_t nitems, uint64_t* bits,
-                             hipStream_t st);
+cs_status launch_build_batch(const uint32_t* uv, const BatchInst* inst, const uint32_t* items,
+                             int64_t nitems, uint64_t* bits, hipStream_t st);
 // Launch configuration of an ensemble counter: mode 0 is the bitset counter (128 tiles;
 // tiles with more than pair_max related-pair tasks take the dense product, pair_max < 0:
 // every tile), modes 2 / 4 the MFMA counter with 128 / 256 tiles on the int8 or (fp4 =

@@ -571,14 +571,15 @@ __device__ inline void bucket_places(const uint64_t (&key)[kBatchPer], int n, in
 }
 
 // Also clears the instance's histogram and (workgroup 0) the work counters, which the
-// later launches accumulate into.  Instances counted by ranks (rank[k].n != 0) get their
-// u order: sigma[x] is the u place of the point at v place x, pi its inverse.  Equal
-// coordinates are unrelated, so ties take opposite orders in u and v: equal u by v
-// descending, equal v by u descending, equal points by index one way and the other.
+// later launches accumulate into.  uv: each point's places in u and v, in time order, for
+// the builder.  Instances counted by ranks (rank[k].n != 0) also get their u order:
+// sigma[x] is the u place of the point at v place x, pi its inverse.  Equal coordinates
+// are unrelated, so ties take opposite orders in u and v: equal u by v descending, equal
+// v by u descending, equal points by index one way and the other.
 __global__ __launch_bounds__(kBatchSortThreads) void k_sprinkle_mink2_batch(
     const uint64_t* __restrict__ seeds, const BatchInst* __restrict__ inst,
-    const RankInst* __restrict__ rank, double* __restrict__ coords, char* __restrict__ rank_base,
-    uint64_t* __restrict__ hist, uint64_t* __restrict__ zero, int nzero) {
+    const RankInst* __restrict__ rank, double* __restrict__ coords, uint32_t* __restrict__ uv,
+    char* __restrict__ rank_base, uint64_t* __restrict__ hist, uint64_t* __restrict__ zero, int nzero) {
   __shared__ BucketLds L;
   const BatchInst d = inst[blockIdx.x];
   const int n = (int)d.n, t = threadIdx.x;
@@ -609,8 +610,6 @@ __global__ __launch_bounds__(kBatchSortThreads) void k_sprinkle_mink2_batch(
       cu[place[e]] = (double)ku[e] * 0x1.0p-53;
       cv[place[e]] = (double)kv[e] * 0x1.0p-53;
     }
-  const RankInst r = rank[blockIdx.x];
-  if (r.n == 0) return;
   auto draw = [&](uint32_t g, int axis) { return sm_output(skey, 2 * (uint64_t)g + axis) >> 11; };
   uint32_t pu[kBatchPer], pv[kBatchPer];
   bucket_places<53>(ku, n, lg, L, pu, [&](uint32_t a, uint32_t b) {
@@ -621,6 +620,12 @@ __global__ __launch_bounds__(kBatchSortThreads) void k_sprinkle_mink2_batch(
     const uint64_t ua = draw(a, 0), ub = draw(b, 0);
     return ua > ub || (ua == ub && a > b);
   });
+  uint32_t* place_uv = uv + d.coord_off / 2;
+#pragma unroll
+  for (int e = 0; e < kBatchPer; ++e)
+    if (t + e * kBatchSortThreads < n) place_uv[place[e]] = pu[e] << 16 | pv[e];
+  const RankInst r = rank[blockIdx.x];
+  if (r.n == 0) return;
   // Both permutations leave through LDS, in whole lines.
   uint16_t* perm = (uint16_t*)L.word;  // sigma, then pi
   __syncthreads();
@@ -712,11 +717,11 @@ cs_status launch_sprinkle(int region, double eta0, uint64_t seed, int64_t n, dou
 }
 
 cs_status launch_sprinkle_batch(const uint64_t* seeds, const BatchInst* inst, const RankInst* rank,
-                                int64_t count, double* coords, char* rank_base, uint64_t* hist,
-                                uint64_t* zero, int nzero, hipStream_t st) {
+                                int64_t count, double* coords, uint32_t* uv, char* rank_base,
+                                uint64_t* hist, uint64_t* zero, int nzero, hipStream_t st) {
   if (count <= 0) return CS_OK;
   hipLaunchKernelGGL(k_sprinkle_mink2_batch, dim3((unsigned)count), dim3(kBatchSortThreads), 0, st,
-                     seeds, inst, rank, coords, rank_base, hist, zero, nzero);
+                     seeds, inst, rank, coords, uv, rank_base, hist, zero, nzero);
   CS_LAUNCH_CHECK();
   return CS_OK;
 }
