@@ -9,28 +9,31 @@
 // elements h links above i, and j goes last: the number of rounds is the number of links
 // of the longest chain from i to j.
 //
-// Each round tests, for every element k still in X, whether any element of its past is
-// still in X.  Each k keeps a witness: the latest past element still in X that a scan of
-// its row, from k downward, last found.  Words above the witness's word were seen empty
-// (of remaining elements) and stay empty, because X only shrinks.  A round is two
-// launches; the first has one wavefront per 64-element word of X (blockIdx.y = the pair):
-//   - R_t[w] (the members left) is formed from R_{t-1} and last round's removals P_{t-1};
-//   - a member whose witness is not in P_{t-1} is done without touching the matrix;
-//   - otherwise its lane reads the next four words of its row, from the witness's word
-//     down: a hit gives the new witness (the latest element in the word), and a member
-//     with no word left below is removed;
-//   - the members with a longer row left are queued (64 sub-queues, one counter add per
-//     wave); a second launch gives each of them a wavefront, which scans 64 words, then
-//     256, then 1024 words per step (16 coalesced loads per lane), and records the next
-//     witness or removes the member.  The graded steps keep a witness found near the
-//     top (the common case, e.g. every first witness of round 0) from paying a full
-//     1024-word fetch.
-// The first launch's wave owns R_t[w] and P_t[w] (the second only sets bits of queued
-// members in P_t, with atomicOr).  Over all rounds every
-// row word is read about once.  Membership and removals are double-buffered by round
-// parity; per pair the rows of R and P have W = ceil(n/64) words.  A member without a
-// witness holds -(resume word) - 1 instead.  The host launches rounds in batches; after
-// each batch one small launch counts the members left.
+// A member k is minimal when no element of its past is left, so each k keeps a witness: the
+// latest past element still in X that a scan of its row, from k downward, last found.  A
+// round tests one bit per member, whether its witness is still there, and scans on, from
+// the witness's word down, only for the members that lost theirs.  Words above it were
+// seen empty of remaining elements and stay empty, because X only shrinks; a hit is the
+// new witness, and no hit down to the lowest word that holds a member (which rises with
+// the rounds) makes k minimal.  Over a whole 3+1 order an element is scanned 2.4 times, the
+// last time to be removed, and half of its row is read.
+//
+// Rounds are a chain of dependent steps, so what counts is the latency of one.  Two forms:
+//   - k_chain_round, a launch per round: a workgroup owns the 64 elements of one word of a
+//     pair's X, collects those that lost their witness in LDS and deals their scans to its
+//     wavefronts.  Removals stay unseen in their round: each word of X is rewritten by its
+//     owner into the bitmap that the next round tests.  The host launches rounds in batches
+//     over the words that still have members and surveys them after each batch.  Round 0,
+//     every element's first search, is bandwidth (75 us for the 3+1 order of 131072
+//     elements); the others take 6 to 30 us, of which 5 are launch and bookkeeping.  The
+//     order's 41 rounds take 0.93 ms, against 1.67 ms with two launches per round and
+//     scans of one wavefront down to word 0.
+//   - k_chain_pair, for many rounds on a set that fits the LDS: one workgroup runs the rest
+//     of one pair's rounds with X, the witnesses and the work list in LDS, so a round
+//     costs two barriers and the latency of its row reads, and no launch (100 pairs of a
+//     1+1 diamond of 16384 points, 245 rounds: 4.0 us a round; the call 1.40 ms, against
+//     7.5 to 9.1 ms).  After each batch the host takes the form that the costs below say
+//     is faster for the rounds left.
 #include <math.h>
 
 #include <algorithm>
@@ -43,199 +46,409 @@ namespace {
 
 constexpr int kChainBlock = 256;  // four wavefronts
 constexpr int kChainWaves = kChainBlock / kWave;
-constexpr int kNear = 4;          // words from a lost witness down that each lane tries
-constexpr int kScanMid = 4;       // 64-word loads of the second scan step
-constexpr int kScanDepth = 16;    // 64-word loads in flight per wave in a long scan step
-constexpr int kLeftBlocks = 256;  // blocks of the "members left" count
-constexpr int kQueues = 64;       // long-scan sub-queues (spreads the counter adds)
-constexpr int kScanBlocksPerQueue = 32;  // 128 wavefronts per sub-queue
+constexpr int kPairThreads = 1024;   // of k_chain_pair
+constexpr int kPairWaves = kPairThreads / kWave;
+constexpr int kScanDepth = 4;        // 64-word loads in flight per wave in a long scan step
+constexpr unsigned long long kWideWords = 2048;  // 16 wavefronts per word up to here, then four
+// Costs that decide between the two forms after each batch, in us: a round's launch, plus
+// so much per word that it visits; a round of k_chain_pair, plus so much per member of
+// the largest pair for the scans of its one workgroup.  (Fitted to both forms alone on 1+1,
+// 2+1 and 3+1 diamonds of 2000 to 32768 points and 1 to 200 pairs: rounds of the whole 3+1
+// order of 32768 points take 0.37 ms, the workgroup alone 2.9 ms; 200 pairs of the 1+1 one
+// 12 to 99 ms and 3.2 ms.)
+constexpr double kRoundUs = 5.0, kWordUs = 6e-4, kPairRoundUs = 3.5, kPairMemberUs = 0.03;
+constexpr uint64_t kNoWord = ~0ull;  // unused entry of the word list
+// Up to this many words in all, round 0 is launched over every one before the first look at
+// the members (entries past the list's end return at once): a host round trip costs more.
+constexpr int64_t kBlindWords = 4096;
+constexpr int64_t kPairMaxN = 32768;  // k_chain_pair: 16-bit indices, 140 KiB of LDS
 
-__device__ __forceinline__ uint64_t below_mask(int lane) {
-  return lane ? (~0ull >> (kWave - lane)) : 0ull;
-}
-
-// R_0, written into R[1] where round 0 reads it as "R_{-1}" (with P_{-1} = P[1] = 0):
-// X = {k : lo ≺ k and (k ≺ hi or k = hi)}, lo = -1 / hi = n being the virtual elements
-// below / above everything.  No member has a witness yet: each resumes at its own word.
-__global__ __launch_bounds__(kChainBlock) void k_chain_init(
-    const uint64_t* __restrict__ bits, int64_t n, int64_t ld, int64_t W,
-    const int32_t* __restrict__ lohi, uint64_t* __restrict__ R1, uint64_t* __restrict__ P1,
-    int32_t* __restrict__ wit, int32_t* __restrict__ height, int32_t* __restrict__ maxh) {
-  const int s = blockIdx.y;
-  const int lane = threadIdx.x & (kWave - 1);
-  const int64_t w = (int64_t)blockIdx.x * kChainWaves + (threadIdx.x >> 6);
-  if (blockIdx.x == 0 && threadIdx.x == 0) maxh[s] = 0;
-  if (w >= W) return;
-  const int64_t lo = lohi[2 * s], hi = lohi[2 * s + 1];
+// Members of pair s in word w, one lane per element: lo ≺ k and (k ≺ hi or k = hi), lo = -1
+// / hi = n being the virtual elements below / above everything.
+__device__ __forceinline__ bool chain_member(const uint64_t* __restrict__ bits, int64_t n,
+                                             int64_t ld, int64_t lo, int64_t hi, int64_t w,
+                                             int lane) {
   const int64_t k = w * kWave + lane;
   bool in = k < n && k > lo && k <= hi;
   if (in && lo >= 0) in = (bits[lo * ld + w] >> lane) & 1;              // lo ≺ k
   if (in && hi < n && k < hi) in = (bits[hi * ld + w] >> lane) & 1;     // k ≺ hi
-  const uint64_t word = __ballot(in);
-  if (lane == 0) {
-    R1[(int64_t)s * W + w] = word;
-    P1[(int64_t)s * W + w] = 0;
-  }
-  if (k < n) {
-    wit[(int64_t)s * n + k] = (int32_t)(-w - 1);
-    height[(int64_t)s * n + k] = 0;
-  }
+  return in;
 }
 
-// Round t.  Rp/Pp: R_{t-1} and P_{t-1}; Rt/Pt: this round's buffers.
-__global__ __launch_bounds__(kChainBlock) void k_chain_round(
+// X_0, zero heights and an empty word list.
+__global__ __launch_bounds__(kChainBlock) void k_chain_init(
     const uint64_t* __restrict__ bits, int64_t n, int64_t ld, int64_t W,
-    const int32_t* __restrict__ lohi, const uint64_t* __restrict__ Rp,
-    const uint64_t* __restrict__ Pp, uint64_t* __restrict__ Rt, uint64_t* __restrict__ Pt,
-    int32_t* __restrict__ wit, int32_t* __restrict__ height,
-    unsigned long long* __restrict__ qcount, uint64_t* __restrict__ queue, int64_t qcap,
-    int32_t t) {
+    const int32_t* __restrict__ lohi, uint64_t* __restrict__ X0, int32_t* __restrict__ height,
+    uint64_t* __restrict__ list) {
   const int s = blockIdx.y;
   const int lane = threadIdx.x & (kWave - 1);
   const int64_t w = (int64_t)blockIdx.x * kChainWaves + (threadIdx.x >> 6);
   if (w >= W) return;
-  const int64_t base = (int64_t)s * W;
-  const uint64_t* rp = Rp + base;
-  const uint64_t* pp = Pp + base;
-  const uint64_t rw = rp[w] & ~pp[w];  // R_t[w]
-  if (lane == 0) Rt[base + w] = rw;
-  if (rw == 0) return;
-  const int64_t lo = lohi[2 * s];
-  const int64_t wlo = lo < 0 ? 0 : (lo + 1) >> 6;  // no member of X lies below this word
+  const uint64_t word =
+      __ballot(chain_member(bits, n, ld, lohi[2 * s], lohi[2 * s + 1], w, lane));
   const int64_t k = w * kWave + lane;
-  int32_t* wk = wit + (int64_t)s * n + k;
-  bool gone = false, longscan = false;
-  int64_t resume = 0;
-  if ((rw >> lane) & 1) {
-    const int32_t m = *wk;
-    if (m < 0 || ((pp[m >> 6] >> (m & 63)) & 1)) {  // no witness, or removed last round
-      const int64_t r = m >= 0 ? (int64_t)(m >> 6) : (int64_t)(-m - 1);
-      const uint64_t* row = bits + k * ld;
-      uint64_t v[kNear];
-#pragma unroll
-      for (int j = 0; j < kNear; ++j) {  // words r, r-1, ..., all loaded at once
-        const int64_t q = r - j;
-        uint64_t x = q >= wlo ? (row[q] & rp[q] & ~pp[q]) : 0ull;
-        if (q == w) x &= below_mask(lane);  // own word: the past only
-        v[j] = x;
-      }
-      int32_t nm = -1;
-#pragma unroll
-      for (int j = kNear - 1; j >= 0; --j)
-        if (v[j]) nm = (int32_t)((r - j) * kWave + 63 - __builtin_clzll(v[j]));
-      if (nm >= 0) {
-        *wk = nm;
-      } else if (r - kNear >= wlo) {
-        longscan = true;  // words r-kNear+1 .. r hold none: go on from r-kNear
-        resume = r - kNear;
-      } else {
-        gone = true;  // no member of its past is left: k is minimal in R_t
-      }
-    }
-  }
-  const uint64_t removed = __ballot(gone);
-  if (gone) height[(int64_t)s * n + k] = t + 1;
-  if (lane == 0) Pt[base + w] = removed;  // the scan launch adds the queued members' bits
-  // Longer rows go to one of kQueues sub-queues (by block), one counter add per wave.
-  const uint64_t todo = __ballot(longscan);
-  if (todo == 0) return;
-  if (longscan) wit[(int64_t)s * n + k] = (int32_t)(-resume - 1);
-  const int64_t blk = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
-  const int g = (int)(blk % kQueues);
-  unsigned long long slot = 0;
-  if (lane == 0) slot = atomicAdd(&qcount[g], (unsigned long long)__popcll(todo));
-  slot = __shfl(slot, 0);
-  if (longscan) {
-    const uint64_t rank = __popcll(todo & ((1ull << lane) - 1));
-    queue[(int64_t)g * qcap + (int64_t)slot + rank] = ((uint64_t)s << 32) | (uint64_t)k;
+  if (k < n) height[(int64_t)s * n + k] = 0;
+  if (lane == 0) {
+    X0[(int64_t)s * W + w] = word;
+    list[(int64_t)s * W + w] = kNoWord;
   }
 }
 
-// Highest word q in [wlo, top] of row k holding a member of R_t, looking at J * 64 words
-// (lane l, load j: word top - l - 64 j); -1 if none of them has one.  top lies below k's
-// own word, so no bit needs masking.
+// What a batch of rounds starts from, one workgroup per pair: the members left in all and
+// in the largest pair, the list of words with a member (pair << 32 | word << 1 | whether it
+// is the pair's lowest) and each pair's lowest.  Words without members leave the other
+// bitmap too, as no round visits them again.  (Counting removals in the rounds instead, an
+// add per workgroup to one address, cost each round several us.)
+struct Survey {
+  unsigned long long left, most, active, unused;
+};
+constexpr int kSurveyThreads = 1024;
+__global__ __launch_bounds__(kSurveyThreads) void k_chain_survey(
+    const uint64_t* __restrict__ R, uint64_t* __restrict__ other, int64_t W,
+    int32_t* __restrict__ low, uint64_t* __restrict__ list, Survey* __restrict__ out) {
+  __shared__ uint32_t left, lowest, active;
+  __shared__ unsigned long long first;
+  const int s = blockIdx.x;
+  const int lane = threadIdx.x & (kWave - 1);
+  const uint64_t* r = R + (int64_t)s * W;
+  if (threadIdx.x == 0) {
+    left = active = 0;
+    lowest = (uint32_t)W;
+  }
+  __syncthreads();
+  uint32_t members = 0, words = 0, mine = (uint32_t)W;
+  for (int64_t w = threadIdx.x; w < W; w += kSurveyThreads) {
+    const uint64_t x = r[w];
+    if (x == 0) {
+      other[(int64_t)s * W + w] = 0;
+      continue;
+    }
+    members += (uint32_t)__popcll(x);
+    ++words;
+    mine = min(mine, (uint32_t)w);
+  }
+  for (int off = kWave / 2; off > 0; off >>= 1) {
+    members += __shfl_xor(members, off);
+    words += __shfl_xor(words, off);
+    mine = min(mine, (uint32_t)__shfl_xor(mine, off));
+  }
+  if (lane == 0 && words) {
+    atomicAdd(&left, members);
+    atomicAdd(&active, words);
+    atomicMin(&lowest, mine);
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    low[s] = (int32_t)lowest;
+    if (left) {
+      first = atomicAdd(&out->active, (unsigned long long)active);
+      atomicAdd(&out->left, (unsigned long long)left);
+      atomicMax(&out->most, (unsigned long long)left);
+    }
+    active = 0;
+  }
+  __syncthreads();
+  if (left == 0) return;
+  for (int64_t w0 = threadIdx.x & ~(kWave - 1); w0 < W; w0 += kSurveyThreads) {
+    const int64_t w = w0 + lane;
+    const bool some = w < W && r[w] != 0;
+    const uint64_t m = __ballot(some);
+    if (m == 0) continue;
+    uint32_t at = 0;
+    if (lane == 0) at = atomicAdd(&active, (uint32_t)__popcll(m));
+    at = __shfl(at, 0) + (uint32_t)__popcll(m & ((1ull << lane) - 1));
+    if (some) list[first + at] = (uint64_t)s << 32 | (uint64_t)w << 1 | (w == (int64_t)lowest ? 1u : 0u);
+  }
+}
+
+// Highest word q in [wlo, top] of row k holding a member of R, looking at J * 64 words
+// (lane l, load j: word top - l - 64 j), and that word's members in *hit; -1 if none of
+// them has one.  first: mask of the word `top` (the past part of k's own word).
 template <int J>
 __device__ __forceinline__ int64_t scan_step(const uint64_t* __restrict__ row,
                                              const uint64_t* __restrict__ R, int64_t top,
-                                             int64_t wlo, int lane) {
+                                             int64_t wlo, int lane, uint64_t first, uint64_t* hit) {
   uint64_t v[J];
 #pragma unroll
   for (int j = 0; j < J; ++j) {
     const int64_t q = top - lane - (int64_t)kWave * j;
     v[j] = q >= wlo ? (row[q] & R[q]) : 0ull;
   }
+  if (lane == 0) v[0] &= first;
 #pragma unroll
   for (int j = 0; j < J; ++j) {
-    const uint64_t hit = __ballot(v[j] != 0);
-    if (hit) return top - (int64_t)__builtin_ctzll(hit) - (int64_t)kWave * j;
+    const uint64_t m = __ballot(v[j] != 0);
+    if (m) {
+      const int src = __builtin_ctzll(m);
+      const uint32_t l = __builtin_amdgcn_readlane((uint32_t)v[j], src);
+      const uint32_t h = __builtin_amdgcn_readlane((uint32_t)(v[j] >> 32), src);
+      *hit = (uint64_t)h << 32 | l;
+      return top - (int64_t)src - (int64_t)kWave * j;
+    }
   }
   return -1;
 }
 
-// Round t, second half: one wavefront per queued member; blockIdx.y = the sub-queue.  Also
-// clears the counters the next round will fill (last read by the previous round).
-__global__ __launch_bounds__(kChainBlock) void k_chain_scan(
-    const uint64_t* __restrict__ bits, int64_t n, int64_t ld, int64_t W,
-    const int32_t* __restrict__ lohi, const uint64_t* __restrict__ Rt, uint64_t* __restrict__ Pt,
-    int32_t* __restrict__ wit, int32_t* __restrict__ height,
-    const unsigned long long* __restrict__ qcount, unsigned long long* __restrict__ qnext,
-    const uint64_t* __restrict__ queue, int64_t qcap, int32_t t) {
-  const int lane = threadIdx.x & (kWave - 1);
-  const int g = blockIdx.y;
-  if (blockIdx.x == 0 && threadIdx.x == 0) qnext[g] = 0;
-  const int64_t gw = (int64_t)blockIdx.x * kChainWaves + (threadIdx.x >> 6);
-  const int64_t nw = (int64_t)gridDim.x * kChainWaves;
-  const int64_t items = (int64_t)qcount[g];
-  const uint64_t* q = queue + (int64_t)g * qcap;
-  for (int64_t i = gw; i < items; i += nw) {
-    const uint64_t item = q[i];
-    const int s = (int)(item >> 32);
-    const int64_t k = (int64_t)(item & 0xffffffffull);
-    const int64_t lo = lohi[2 * s];
-    const int64_t wlo = lo < 0 ? 0 : (lo + 1) >> 6;
-    const int64_t base = (int64_t)s * W;
-    const uint64_t* R = Rt + base;
-    const uint64_t* row = bits + k * ld;
-    int32_t* wk = wit + (int64_t)s * n + k;
-    int64_t top = -(int64_t)(*wk) - 1;  // resume word, below k's own word
-    int64_t found = scan_step<1>(row, R, top, wlo, lane);  // a witness nearby is common
-    top -= kWave;
-    if (found < 0 && top >= wlo) {  // then 256 words before the 1024-word steps
-      found = scan_step<kScanMid>(row, R, top, wlo, lane);
-      top -= (int64_t)kWave * kScanMid;
-    }
-    while (found < 0 && top >= wlo) {
-      found = scan_step<kScanDepth>(row, R, top, wlo, lane);
-      top -= (int64_t)kWave * kScanDepth;
-    }
-    if (lane == 0) {
-      if (found >= 0) {
-        *wk = (int32_t)(found * kWave + 63 - __builtin_clzll(row[found] & R[found]));
-      } else {
-        height[(int64_t)s * n + k] = t + 1;
-        atomicOr(&Pt[base + (k >> 6)], 1ull << (k & 63));
-      }
-    }
+// One wavefront: k's first witness, the latest member of R in its past, from word w (its own)
+// down to word wlo, or -1.  It is usually found about a hundred words down, so the steps
+// grow: 64, 128, then 256 words.
+__device__ __forceinline__ int64_t first_witness(const uint64_t* __restrict__ row,
+                                                 const uint64_t* __restrict__ R, int64_t w,
+                                                 int64_t wlo, int lane, uint64_t mask) {
+  uint64_t hit = 0;
+  int64_t q = scan_step<1>(row, R, w, wlo, lane, mask, &hit), top = w - kWave;
+  if (q < 0 && top >= wlo) {
+    q = scan_step<2>(row, R, top, wlo, lane, ~0ull, &hit);
+    top -= 2 * kWave;
   }
+  for (; q < 0 && top >= wlo; top -= (int64_t)kWave * kScanDepth)
+    q = scan_step<kScanDepth>(row, R, top, wlo, lane, ~0ull, &hit);
+  return q < 0 ? -1 : q * kWave + 63 - __builtin_clzll(hit);
 }
 
-// count += the members left after a round, the bits of R & ~P (that round's membership and
-// removals); one counter add per block.
-__global__ __launch_bounds__(kChainBlock) void k_chain_left(const uint64_t* __restrict__ R,
-                                                           const uint64_t* __restrict__ P,
-                                                           int64_t words,
-                                                           unsigned long long* __restrict__ count) {
-  __shared__ unsigned long long part[kChainWaves];
-  unsigned long long mine = 0;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < words;
-       i += (int64_t)gridDim.x * blockDim.x)
-    mine += __popcll(R[i] & ~P[i]);
-  for (int off = kWave / 2; off > 0; off >>= 1) mine += __shfl_xor(mine, off);
-  if ((threadIdx.x & (kWave - 1)) == 0) part[threadIdx.x >> 6] = mine;
+// Round t for the 64 elements of one listed word.  R: the members (read only); R_next: the
+// members without this round's minimal elements.
+template <int THREADS>
+__global__ __launch_bounds__(THREADS, 8) void k_chain_round(
+    const uint64_t* __restrict__ bits, int64_t n, int64_t ld, int64_t W,
+    const uint64_t* __restrict__ list, const uint64_t* __restrict__ R, uint64_t* __restrict__ R_next,
+    int32_t* __restrict__ wit, int32_t* __restrict__ height, const int32_t* __restrict__ low,
+    int32_t* __restrict__ low_next, int32_t t) {
+  constexpr int kWaves = THREADS / kWave;
+  __shared__ int32_t todo[kWave], top_of[kWave];  // element of the word; word to resume at
+  __shared__ int32_t best[kWave];                 // its witness found this round, or -1
+  __shared__ uint64_t removed;
+  __shared__ int ntodo;
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const uint64_t entry = list[blockIdx.x];
+  if (entry == kNoWord) return;  // the whole workgroup
+  const int s = (int)(entry >> 32);
+  const int64_t w = (int64_t)((uint32_t)entry >> 1);
+  const uint64_t* r = R + (int64_t)s * W;
+  const int64_t wlo = low[s];
+  uint64_t word = 0;
+  if (wave == 0) {
+    const int64_t k = w * kWave + lane;
+    word = r[w];
+    // read beside the word, not after it: a stale entry of a former member is not used
+    const int32_t m = t > 0 && k < n ? wit[(int64_t)s * n + k] : 0;
+    bool need = (word >> lane) & 1;
+    int64_t top = w;
+    if (need && t > 0) {
+      top = m >> 6;
+      need = !((r[top] >> (m & 63)) & 1);
+    }
+    const uint64_t mask = __ballot(need);
+    if (need) {
+      const int at = __popcll(mask & ((1ull << lane) - 1));
+      todo[at] = lane;
+      top_of[at] = (int32_t)top;
+      best[at] = -1;
+    }
+    if (lane == 0) {
+      ntodo = __popcll(mask);
+      removed = 0;
+    }
+  }
   __syncthreads();
+  const int items = ntodo;
+  // After round 0 most scans end in removal, all the way down to wlo, so a scan is cut into
+  // pieces of 256 words, each a wavefront's single step; the pieces of all items are dealt
+  // to the wavefronts and the highest hit counts.
+  constexpr int kPiece = kWave * kScanDepth;
+  const int pieces = t == 0 ? 1 : (int)((w - wlo) / kPiece) + 1;
+  for (int x = wave; x < items * pieces; x += kWaves) {
+    const int i = x % items, u = x / items;
+    const int64_t k = w * kWave + __builtin_amdgcn_readfirstlane(todo[i]);
+    const int64_t top = (int64_t)__builtin_amdgcn_readfirstlane(top_of[i]) - (int64_t)u * kPiece;
+    if (top < wlo) continue;
+    const uint64_t mask = top == w ? (1ull << (k & 63)) - 1ull : ~0ull;
+    const uint64_t* row = bits + k * ld;
+    int64_t m = -1;
+    if (t == 0) {
+      m = first_witness(row, r, top, wlo, lane, mask);
+    } else {
+      uint64_t hit = 0;
+      const int64_t q = scan_step<kScanDepth>(row, r, top, wlo, lane, mask, &hit);
+      if (q >= 0) m = q * kWave + 63 - __builtin_clzll(hit);
+    }
+    if (m >= 0 && lane == 0) atomicMax(&best[i], (int32_t)m);
+  }
+  if ((entry & 1) && wave == kWaves - 1) {  // the lowest word with a member of R
+    int64_t q = wlo;
+    for (; q < W; q += kWave) {
+      const uint64_t m = __ballot(q + lane < W && r[q + lane] != 0);
+      if (m) {
+        q += __builtin_ctzll(m);
+        break;
+      }
+    }
+    if (lane == 0) low_next[s] = (int32_t)(q < W ? q : W);
+  }
+  __syncthreads();
+  if (wave != 0) return;
+  if (lane < items) {
+    const int e = todo[lane];
+    const int64_t at = (int64_t)s * n + w * kWave + e;
+    const int32_t m = best[lane];
+    if (m >= 0) {
+      wit[at] = m;
+    } else {
+      height[at] = t + 1;
+      atomicOr((unsigned long long*)&removed, 1ull << e);
+    }
+  }
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  if (lane == 0) R_next[(int64_t)s * W + w] = word & ~removed;
+}
+
+// The rounds from t on of pair blockIdx.x (t >= 1: every member has a witness), with the
+// members X0 and witnesses left by the rounds before; n <= kPairMaxN.  Dynamic LDS: two bitmaps of the members
+// (W words each: a round tests one, and its removals are cleared in the other, which the
+// next round tests), the round's removals (W words, cleared in the first bitmap a round
+// later), witnesses and work list (n 16-bit entries each).  A round is two phases with a
+// barrier each: list the members that lost their witness, scan for each.  A scan takes a
+// group of 8 lanes and 64 words per step, so a wavefront serves 8 members at once.
+constexpr int kPairGroup = 8;    // lanes per scan
+constexpr int kPairUnroll = 4;   // words per wavefront and check step; loads per scan step
+
+__global__ __launch_bounds__(kPairThreads) void k_chain_pair(
+    const uint64_t* __restrict__ bits, int64_t n, int64_t ld, int64_t W64,
+    const uint64_t* __restrict__ X0, const int32_t* __restrict__ wit0,
+    const int32_t* __restrict__ low0, int32_t* __restrict__ height, int t) {
+  extern __shared__ uint64_t chain_lds[];
+  const int W = (int)W64;
+  uint64_t* X = chain_lds;      // bitmap c at X + c W
+  uint64_t* gone = X + 2 * W;
+  uint16_t* wit = (uint16_t*)(gone + W);
+  uint16_t* todo = wit + W * kWave;
+  __shared__ int ntodo[2], left, low[2];
+  const int s = blockIdx.x;
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  int32_t* h = height + (int64_t)s * n;
   if (threadIdx.x == 0) {
-    for (int i = 1; i < kChainWaves; ++i) mine += part[i];
-    if (mine) atomicAdd(count, mine);
+    ntodo[0] = ntodo[1] = left = 0;
+    low[t & 1] = low0[s];
+  }
+  __syncthreads();
+  for (int w = wave; w < W; w += kPairWaves) {
+    const uint64_t word = X0[(int64_t)s * W + w];
+    const int64_t k = (int64_t)w * kWave + lane;
+    if (word) wit[k] = (uint16_t)(k < n ? wit0[(int64_t)s * n + k] : 0);
+    if (lane == 0) {
+      X[w] = X[W + w] = word;
+      gone[w] = 0;
+      if (word) atomicAdd(&left, __popcll(word));
+    }
+  }
+  __syncthreads();
+  const int grp = lane / kPairGroup, sub = lane % kPairGroup;
+  // every round removes at least the member of the lowest index: n rounds in all at most
+  for (; t <= n && left > 0; ++t) {
+    const uint64_t* R = X + (t & 1) * W;
+    uint64_t* R_next = X + ((t + 1) & 1) * W;
+    const int wlo = low[t & 1];
+    int* count = &ntodo[t & 1];
+    for (int w0 = wlo + wave; w0 < W; w0 += kPairWaves * kPairUnroll) {
+      uint64_t word[kPairUnroll];
+      uint32_t m[kPairUnroll];
+      uint64_t at_m[kPairUnroll];
+#pragma unroll
+      for (int u = 0; u < kPairUnroll; ++u) {
+        const int w = w0 + u * kPairWaves;
+        word[u] = w < W ? R[w] : 0ull;
+        // (members' entries count; others may hold anything: kept inside the bitmap)
+        m[u] = w < W ? min((uint32_t)wit[w * kWave + lane], (uint32_t)(W * kWave - 1)) : 0u;
+      }
+#pragma unroll
+      for (int u = 0; u < kPairUnroll; ++u) at_m[u] = R[m[u] >> 6];
+#pragma unroll
+      for (int u = 0; u < kPairUnroll; ++u) {
+        const int w = w0 + u * kPairWaves;
+        const bool need = ((word[u] >> lane) & 1) && !((at_m[u] >> (m[u] & 63)) & 1);
+        const uint64_t mask = __ballot(need);
+        if (mask == 0) continue;
+        int at = 0;
+        if (lane == 0) at = atomicAdd(count, __popcll(mask));
+        at = __builtin_amdgcn_readfirstlane(at) + __popcll(mask & ((1ull << lane) - 1));
+        if (need) todo[at] = (uint16_t)(w * kWave + lane);
+      }
+    }
+    for (int w = threadIdx.x; w < W; w += kPairThreads) {  // the last round's removals
+      const uint64_t g = gone[w];
+      if (g) {
+        R_next[w] &= ~g;
+        gone[w] = 0;
+      }
+    }
+    if (wave == kPairWaves - 1) {  // the lowest word with a member, for the next round
+      int w = wlo;
+      for (; w < W; w += kWave) {
+        const uint64_t v = __ballot(w + lane < W && R[w + lane < W ? w + lane : 0] != 0);
+        if (v) {
+          w += __builtin_ctzll(v);
+          break;
+        }
+      }
+      if (lane == 0) low[(t + 1) & 1] = w;
+    }
+    __syncthreads();
+    const int items = *count;
+    if (threadIdx.x == 0) ntodo[(t + 1) & 1] = 0;
+    for (int i = threadIdx.x / kPairGroup; i < items; i += kPairThreads / kPairGroup) {
+      const int k = todo[i];
+      const uint64_t* row = bits + (int64_t)k * ld;
+      int top = wit[k] >> 6;
+      uint64_t first = top == k >> 6 ? (1ull << (k & 63)) - 1ull : ~0ull;
+      int m = -1;
+      for (; top >= wlo && m < 0; top -= 2 * kPairGroup * kPairUnroll) {
+        // two words per lane and load, from the pair of words that holds `top` down
+        const int p0 = (top >> 1) - sub;
+        uint64_t v[kPairUnroll][2];
+#pragma unroll
+        for (int j = 0; j < kPairUnroll; ++j) {
+          const int p = p0 - kPairGroup * j;
+          v[j][0] = v[j][1] = 0;
+          if (2 * p + 1 >= wlo) {
+            const ulonglong2 b = *(const ulonglong2*)(row + 2 * p);  // rows start on 64 bytes
+            const int q = 2 * p;
+            v[j][0] = b.x & R[q];
+            v[j][1] = q + 1 <= top ? b.y & R[q + 1 < W ? q + 1 : q] : 0ull;
+            if (q == top) v[j][0] &= first;
+            if (q + 1 == top) v[j][1] &= first;
+          }
+        }
+        first = ~0ull;
+#pragma unroll
+        for (int j = 0; j < kPairUnroll; ++j) {
+          const uint32_t b = (uint32_t)(__ballot((v[j][0] | v[j][1]) != 0) >> (kPairGroup * grp)) &
+                             ((1u << kPairGroup) - 1u);
+          if (m < 0 && b) {
+            const int src = __builtin_ctz(b);
+            const uint64_t x1 = __shfl((unsigned long long)v[j][1], kPairGroup * grp + src);
+            const uint64_t x0 = __shfl((unsigned long long)v[j][0], kPairGroup * grp + src);
+            const int q = 2 * ((top >> 1) - src - kPairGroup * j);
+            m = x1 ? (q + 1) * kWave + 63 - __builtin_clzll(x1) : q * kWave + 63 - __builtin_clzll(x0);
+          }
+        }
+        top |= 1;  // the next step starts at the pair below the last one read
+      }
+      if (sub == 0) {
+        if (m >= 0) {
+          wit[k] = (uint16_t)m;
+        } else {
+          h[k] = t + 1;
+          atomicAnd((unsigned long long*)&R_next[k >> 6], ~(1ull << (k & 63)));
+          atomicOr((unsigned long long*)&gone[k >> 6], 1ull << (k & 63));
+          atomicSub(&left, 1);
+        }
+      }
+    }
+    __syncthreads();
   }
 }
 
@@ -316,15 +529,15 @@ __global__ __launch_bounds__(kChainBlock) void k_degrees(const uint64_t* __restr
 
 struct ChainWs {
   int32_t* lohi;
-  unsigned long long* left;   // members left: before round 0, then after each batch
-  int32_t* maxh;
-  uint64_t* R[2];
-  uint64_t* P[2];
+  uint64_t* books;  // zeroed at the start, book_words in all:
+  Survey* survey;  //   before round 0, then after each batch
+  int32_t* maxh;   //   largest height of each pair
+  int64_t book_words;
+  int32_t* low[2];
+  uint64_t* X[2];
+  uint64_t* list;  // words with members
   int32_t* wit;
   int32_t* height;  // used when the caller passes none
-  unsigned long long* qcount[2];  // kQueues counters per round parity
-  uint64_t* queue;                // kQueues sub-queues of qcap items
-  int64_t qcap;
   size_t bytes;
 };
 
@@ -340,20 +553,16 @@ ChainWs chain_layout(void* base, int64_t n, int64_t count) {
     return (char*)base + o;
   };
   L.lohi = (int32_t*)take(sizeof(int32_t) * 2 * count);
-  L.left = (unsigned long long*)take(sizeof(unsigned long long) * (max_batches(n) + 1));
+  const size_t book = off;
+  L.books = (uint64_t*)((char*)base + book);
+  L.survey = (Survey*)take(sizeof(Survey) * (max_batches(n) + 1));
   L.maxh = (int32_t*)take(sizeof(int32_t) * count);
-  for (int b = 0; b < 2; ++b) {
-    L.R[b] = (uint64_t*)take(sizeof(uint64_t) * W * count);
-    L.P[b] = (uint64_t*)take(sizeof(uint64_t) * W * count);
-  }
+  L.book_words = (int64_t)((off - book) / sizeof(uint64_t));
+  for (int b = 0; b < 2; ++b) L.low[b] = (int32_t*)take(sizeof(int32_t) * count);
+  for (int b = 0; b < 2; ++b) L.X[b] = (uint64_t*)take(sizeof(uint64_t) * W * count);
+  L.list = (uint64_t*)take(sizeof(uint64_t) * W * count);
   L.wit = (int32_t*)take(sizeof(int32_t) * n * count);
   L.height = (int32_t*)take(sizeof(int32_t) * n * count);
-  for (int b = 0; b < 2; ++b)
-    L.qcount[b] = (unsigned long long*)take(sizeof(unsigned long long) * kQueues);
-  // sub-queue g takes the members of the round launch's blocks numbered g mod kQueues
-  const int64_t blocks = ceil_div(W, kChainWaves) * count;
-  L.qcap = ceil_div(blocks, kQueues) * kChainBlock;
-  L.queue = (uint64_t*)take(sizeof(uint64_t) * L.qcap * kQueues);
   L.bytes = off;
   return L;
 }
@@ -377,51 +586,64 @@ cs_status launch_longest_chain(const uint64_t* bits, int64_t n, int64_t ld, cons
   }
   CS_HIP_CHECK(hipMemcpyAsync(L.lohi, lohi.data(), sizeof(int32_t) * 2 * count,
                               hipMemcpyHostToDevice, st));
-  cs_status s0 = launch_fill_u64((uint64_t*)L.left, max_batches(n) + 1, 0, st);
-  if (s0 == CS_OK) s0 = launch_fill_u64((uint64_t*)L.qcount[0], kQueues, 0, st);
-  if (s0 == CS_OK) s0 = launch_fill_u64((uint64_t*)L.qcount[1], kQueues, 0, st);
+  cs_status s0 = launch_fill_u64(L.books, L.book_words, 0, st);
   if (s0 != CS_OK) return s0;
-  const dim3 grid((unsigned)ceil_div(W, kChainWaves), (unsigned)count);
-  hipLaunchKernelGGL(k_chain_init, grid, dim3(kChainBlock), 0, st, bits, n, ld, W, L.lohi, L.R[1],
-                     L.P[1], L.wit, h, L.maxh);
+  hipLaunchKernelGGL(k_chain_init, dim3((unsigned)ceil_div(W, kChainWaves), (unsigned)count),
+                     dim3(kChainBlock), 0, st, bits, n, ld, W, L.lohi, L.X[0], h, L.list);
   CS_LAUNCH_CHECK();
+  // Round t removes the minimal elements of what the rounds before left; every X is empty
+  // after at most n rounds.  Batches of rounds end with a survey that the host reads; the
+  // next batch is sized from the rate of removal so far, so that few rounds run past the
+  // end, and its launches cover the words that still have members.
   const int64_t words = W * count;
-  const dim3 red((unsigned)std::min<int64_t>(kLeftBlocks, ceil_div(words, kChainBlock)));
-  hipLaunchKernelGGL(k_chain_left, red, dim3(kChainBlock), 0, st, L.R[1], L.P[1], words, L.left);
-  CS_LAUNCH_CHECK();
-  // Round t removes the minimal elements of R_t; every X is empty after at most n rounds.
-  // Batches of rounds end with a count of the members left; the next batch is sized from
-  // the rate of removal so far, so that few rounds run past the end.
-  int64_t t = 0, batch = 8, b = 0;
-  unsigned long long counts[2] = {0, 1};
-  while (t <= n && b < max_batches(n)) {
+  Survey seen[2] = {};  // before the last batch and now
+  Survey& now = seen[1];
+  for (int64_t t = 0, batch = 8, b = 0;; ++b) {
+    // the members before round t; low[] is read by round t from the other parity
+    hipLaunchKernelGGL(k_chain_survey, dim3((unsigned)count), dim3(kSurveyThreads), 0, st, L.X[t & 1],
+                       L.X[(t + 1) & 1], W, L.low[(t + 1) & 1], L.list, L.survey + b);
+    CS_LAUNCH_CHECK();
+    if (t == 0 && words <= kBlindWords) {
+      now.active = (unsigned long long)words;
+    } else {
+      const int64_t from = b > 0 ? b - 1 : 0;
+      CS_HIP_CHECK(hipMemcpyAsync(seen + (b > 0 ? 0 : 1), L.survey + from,
+                                  sizeof(Survey) * (b > 0 ? 2 : 1), hipMemcpyDeviceToHost, st));
+      CS_HIP_CHECK(hipStreamSynchronize(st));
+      if (now.left == 0) break;
+    }
+    if (t > n || b >= max_batches(n)) return CS_ERR_HIP;  // unreachable: a round removes members
+    if (t > 0) {
+      const double rate = (double)(seen[0].left - now.left) / (double)batch;  // >= 1 per round
+      // Layers thin out towards the end, so the rate so far under-estimates the rounds
+      // left; half again as many rounds (a round past the end is a near-empty launch) saves
+      // host round trips.
+      const double rounds = 1.5 * (double)now.left / rate;
+      if (n <= kPairMaxN && rounds * (kRoundUs + kWordUs * (double)now.active) >
+                                rounds * kPairRoundUs + kPairMemberUs * (double)now.most) {
+        const size_t lds = (size_t)W * (3 * sizeof(uint64_t) + 2 * kWave * sizeof(uint16_t));
+        hipLaunchKernelGGL(k_chain_pair, dim3((unsigned)count), dim3(kPairThreads), lds, st, bits, n,
+                           ld, W, L.X[t & 1], L.wit, L.low[(t + 1) & 1], h, (int)t);
+        CS_LAUNCH_CHECK();
+        CS_HIP_CHECK(hipStreamSynchronize(st));
+        break;
+      }
+      batch = std::max<int64_t>(2, std::min<int64_t>(64, (int64_t)ceil(rounds)));
+    }
     const int64_t end = std::min<int64_t>(t + batch, n + 1);
+    batch = end - t;
     for (; t < end; ++t) {
-      const int c = (int)(t & 1), p = c ^ 1;
-      hipLaunchKernelGGL(k_chain_round, grid, dim3(kChainBlock), 0, st, bits, n, ld, W, L.lohi,
-                         L.R[p], L.P[p], L.R[c], L.P[c], L.wit, h, L.qcount[c], L.queue, L.qcap,
-                         (int32_t)t);
-      CS_LAUNCH_CHECK();
-      hipLaunchKernelGGL(k_chain_scan, dim3(kScanBlocksPerQueue, kQueues), dim3(kChainBlock), 0,
-                         st, bits, n, ld, W, L.lohi, L.R[c], L.P[c], L.wit, h,
-                         L.qcount[c], L.qcount[p], L.queue, L.qcap, (int32_t)t);
+      const int c = (int)(t & 1);
+      const dim3 grid((unsigned)now.active);
+      if (now.active <= kWideWords)
+        hipLaunchKernelGGL(k_chain_round<1024>, grid, dim3(1024), 0, st, bits, n, ld, W, L.list, L.X[c],
+                           L.X[c ^ 1], L.wit, h, L.low[c ^ 1], L.low[c], (int32_t)t);
+      else
+        hipLaunchKernelGGL(k_chain_round<256>, grid, dim3(256), 0, st, bits, n, ld, W, L.list, L.X[c],
+                           L.X[c ^ 1], L.wit, h, L.low[c ^ 1], L.low[c], (int32_t)t);
       CS_LAUNCH_CHECK();
     }
-    ++b;  // members left after round t-1: R_{t-1} & ~P_{t-1}
-    hipLaunchKernelGGL(k_chain_left, red, dim3(kChainBlock), 0, st, L.R[(t - 1) & 1],
-                       L.P[(t - 1) & 1], words, L.left + b);
-    CS_LAUNCH_CHECK();
-    CS_HIP_CHECK(hipMemcpyAsync(counts, L.left + b - 1, sizeof(counts), hipMemcpyDeviceToHost, st));
-    CS_HIP_CHECK(hipStreamSynchronize(st));
-    if (counts[1] == 0) break;
-    const double rate = (double)(counts[0] - counts[1]) / (double)batch;  // >= 1 per round
-    // Layers thin out towards the end, so the rate so far under-estimates the rounds
-    // left; half again as many rounds (a round past the end is two near-empty launches)
-    // saves host round trips: 1.76 -> 1.62 ms on the whole 3+1 order at N = 131072.
-    const int64_t want = (int64_t)ceil(1.5 * (double)counts[1] / rate);
-    batch = std::max<int64_t>(2, std::min<int64_t>(64, want));
   }
-  if (counts[1] != 0) return CS_ERR_HIP;  // unreachable for a valid order
   hipLaunchKernelGGL(k_chain_maxh, dim3((unsigned)std::min<int64_t>(64, ceil_div(n, 4096)),
                                         (unsigned)count),
                      dim3(kChainBlock), 0, st, L.lohi, h, n, L.maxh);
