@@ -49,6 +49,15 @@ constexpr int kStageBits = 256;         // K bits per LDS stage
 constexpr int kStageWords = kStageBits / 32;
 constexpr int kHalfRows = 129;  // half-major B stage of related-pair tiles: 128 rows + a zero row
 constexpr int kBinsSingle = 12288;      // LDS histogram bins, single instance (48 KiB)
+// One instance up to kSmallN points takes 128-row tiles, a workgroup per tile, two per CU, with
+// bins for every count; above, 256-row tiles, one persistent workgroup per CU.  With few
+// tiles the 256-row ones leave CUs idle and end in a long last round (2+1 diamonds, fp4 /
+// int8, us: 5000 points 41 / 55 against 28 / 30, 8192 points 74 / 97 against 65 / 81);
+// further up their operand reuse wins (16384 points: 310 / 470 against 400 / 600).  Below
+// 4096 points 128-row tiles used to share one CU each and, from 512 tiles, queues that every
+// workgroup probed before it left: 4096 points 43 / 46 -> 18 / 21.
+constexpr int64_t kSmallN = 8193;
+constexpr int kBinsSmall = (int)kSmallN - 1;  // counts are at most n - 2
 constexpr int kBinsBatch = 8192;        // LDS histogram bins, ensembles (n <= 8192)
 
 // Output tile t (0-based) in longest-first order for a T x T tile triangle:
@@ -1196,7 +1205,7 @@ __device__ inline int xcc_id() {
 }
 
 // ===========================================================================
-// Single-instance kernels: persistent over the T(T+1)/2 tiles, longest first.
+// Single-instance kernels: over the T(T+1)/2 tiles, longest first.
 // ===========================================================================
 template <int BM, int HB>
 struct MfmaLds {
@@ -1218,13 +1227,16 @@ struct BitsetLds {
   int slot;
 };
 
-template <int WM, bool FP4, int EPI>
-__global__ __launch_bounds__(kThreads, 1) void k_count_mfma(const uint64_t* __restrict__ S,
+// WM = 4: one workgroup per CU (its ring fills the LDS), HB bins of possibly larger counts.
+// WM = 2: two per CU; every count fits the HB bins.
+template <int WM, bool FP4, int EPI, int HB>
+__global__ __launch_bounds__(kThreads, WM == 4 ? 1 : 2) void k_count_mfma(const uint64_t* __restrict__ S,
                                                             int64_t n, int64_t ld,
                                                             unsigned long long* __restrict__ hist,
                                                             unsigned int* __restrict__ counter,
                                                             FieldArgs f) {
-  constexpr int BM = 2 * WM * 32, HB = kBinsSingle;
+  constexpr int BM = 2 * WM * 32;
+  constexpr bool FITS = WM == 2;
   __shared__ MfmaLds<BM, HB> L;  // 96 KiB ring + 48 KiB bins + 8 KiB relation bits at WM = 4
   const int64_t T = ceil_div(n, BM);
   if constexpr (EPI == 0)  // the bins a count can reach
@@ -1233,18 +1245,18 @@ __global__ __launch_bounds__(kThreads, 1) void k_count_mfma(const uint64_t* __re
     if (threadIdx.x < 5)
       L.phis[BM + threadIdx.x] = threadIdx.x == 0 ? f.c0 : threadIdx.x == 1 ? f.c1
                                  : threadIdx.x == 2 ? f.c2 : threadIdx.x == 3 ? f.c3 : 0.0;
-  uint32_t tmax = 0;
+  uint32_t tmax = FITS ? (uint32_t)(n - 2) : 0u;  // FITS: flush every bin
   int64_t pairs_in_lds = 0;
   TileArgs ta{(const uint32_t*)S, 2 * ld, n, 0, 0, hist, f};
-  // Rectangle queues per XCD while the table fits and there are enough tiles to share
-  // panels (a workgroup that runs out of work probes every queue once, one global atomic
-  // each, before it exits); otherwise one queue, longest K-range first.
-  const bool rect = rect_sched_fits(T) && T * (T + 1) / 2 >= kRectMinTiles;
+  // 256-row tiles: rectangle queues per XCD while the table fits and there are enough tiles
+  // to share panels (a workgroup that runs out of work probes every queue once, one global
+  // atomic each, before it exits); otherwise one queue, longest K-range first.
+  const bool rect = WM == 4 && rect_sched_fits(T) && T * (T + 1) / 2 >= kRectMinTiles;
   const RectSched rs = rect_sched_make(rect ? T : 1);
   const int x0 = xcc_id();
   const int64_t ntiles = T * (T + 1) / 2;
-  // Small matrices launch a workgroup per tile: each takes the tile of its own index,
-  // without the queue's two atomic round trips.
+  // A workgroup per tile: each takes the tile of its own index, without the queue's two
+  // atomic round trips.
   const bool direct = !rect && ntiles <= (int64_t)gridDim.x;
   bool taken = false;
   int probe = 0;
@@ -1278,7 +1290,7 @@ __global__ __launch_bounds__(kThreads, 1) void k_count_mfma(const uint64_t* __re
     ta.I0 = I * BM;
     ta.J0 = J * BM;
     TileChain none;
-    if (mfma_tile<WM, HB, FP4, EPI>(ta, L.ring, L.rel, L.hist, tmax, L.phis, none))
+    if (mfma_tile<WM, HB, FP4, EPI, FITS>(ta, L.ring, L.rel, L.hist, tmax, L.phis, none))
       pairs_in_lds += (int64_t)BM * BM;
   }
   if constexpr (EPI == 0) flush_hist<HB>(L.hist, hist, n - 1, tmax, &L.maxbin);
@@ -1430,13 +1442,15 @@ cs_status launch_fill_u64(uint64_t* p, int64_t count, uint64_t value, hipStream_
 
 size_t histogram_ws_bytes(int64_t, int) { return 256; }
 
-template <int WM, bool FP4, int EPI = 0>
+template <int WM, bool FP4, int EPI, int HB>
 cs_status launch_mfma(const uint64_t* bits, int64_t n, int64_t ld, uint64_t* hist,
                       unsigned int* ctr, hipStream_t st, FieldArgs f = FieldArgs{}) {
   constexpr int BM = 2 * WM * 32;
   const int64_t T = ceil_div(n, BM);
-  const unsigned grid = (unsigned)std::min<int64_t>(T * (T + 1) / 2, device_cu_count());
-  hipLaunchKernelGGL((k_count_mfma<WM, FP4, EPI>), dim3(grid), dim3(kThreads), 0, st, bits, n, ld,
+  // WM = 2: a workgroup per tile, longest first; no queue
+  const unsigned grid =
+      (unsigned)(WM == 2 ? T * (T + 1) / 2 : std::min<int64_t>(T * (T + 1) / 2, device_cu_count()));
+  hipLaunchKernelGGL((k_count_mfma<WM, FP4, EPI, HB>), dim3(grid), dim3(kThreads), 0, st, bits, n, ld,
                      (unsigned long long*)hist, ctr, f);
   CS_LAUNCH_CHECK();
   return CS_OK;
@@ -1454,14 +1468,14 @@ cs_status launch_histogram(const uint64_t* bits, int64_t n, int64_t ld, int coun
   unsigned int* ctr = (unsigned int*)ws;
   cs_status s = launch_zero2(hist, n - 1, (uint64_t*)ws, 4, st);  // bins, 8 queue counters
   if (s != CS_OK) return s;
-  const bool big = n > 4096;  // 256x256 output tiles above 4096 points, 128x128 below
+  const bool big = n > kSmallN;
   switch (counter) {
     case CS_COUNT_MFMA:
-      return big ? launch_mfma<4, false>(bits, n, ld, hist, ctr, st)
-                 : launch_mfma<2, false>(bits, n, ld, hist, ctr, st);
+      return big ? launch_mfma<4, false, 0, kBinsSingle>(bits, n, ld, hist, ctr, st)
+                 : launch_mfma<2, false, 0, kBinsSmall>(bits, n, ld, hist, ctr, st);
     case CS_COUNT_MFMA_FP4:
-      return big ? launch_mfma<4, true>(bits, n, ld, hist, ctr, st)
-                 : launch_mfma<2, true>(bits, n, ld, hist, ctr, st);
+      return big ? launch_mfma<4, true, 0, kBinsSingle>(bits, n, ld, hist, ctr, st)
+                 : launch_mfma<2, true, 0, kBinsSmall>(bits, n, ld, hist, ctr, st);
     default: {
       const int64_t T = ceil_div(n, 128);
       const unsigned grid = (unsigned)std::min<int64_t>(T * (T + 1) / 2, 2 * device_cu_count());
@@ -1495,13 +1509,13 @@ cs_status launch_dalembertian(const uint64_t* bits, int64_t n, int64_t ld, int c
     K = 4.0 / sqrt(6.0);
     f.c0 = 1.0; f.c1 = -9.0; f.c2 = 16.0; f.c3 = -8.0;
   }
-  const bool big = n > 4096;
+  const bool big = n > kSmallN;
   if (counter == CS_COUNT_MFMA)
-    s = big ? launch_mfma<4, false, 1>(bits, n, ld, nullptr, ctr, st, f)
-            : launch_mfma<2, false, 1>(bits, n, ld, nullptr, ctr, st, f);
+    s = big ? launch_mfma<4, false, 1, 1>(bits, n, ld, nullptr, ctr, st, f)
+            : launch_mfma<2, false, 1, 1>(bits, n, ld, nullptr, ctr, st, f);
   else
-    s = big ? launch_mfma<4, true, 1>(bits, n, ld, nullptr, ctr, st, f)
-            : launch_mfma<2, true, 1>(bits, n, ld, nullptr, ctr, st, f);
+    s = big ? launch_mfma<4, true, 1, 1>(bits, n, ld, nullptr, ctr, st, f)
+            : launch_mfma<2, true, 1, 1>(bits, n, ld, nullptr, ctr, st, f);
   if (s != CS_OK) return s;
   hipLaunchKernelGGL(k_field_finish, dim3((unsigned)ceil_div(n, 256)), dim3(256), 0, st, phi, out, n,
                      K / (ell * ell));
