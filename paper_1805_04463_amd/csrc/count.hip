@@ -49,15 +49,23 @@ constexpr int kStageBits = 256;         // K bits per LDS stage
 constexpr int kStageWords = kStageBits / 32;
 constexpr int kHalfRows = 129;  // half-major B stage of related-pair tiles: 128 rows + a zero row
 constexpr int kBinsSingle = 12288;      // LDS histogram bins, single instance (48 KiB)
-// One instance up to kSmallN points takes 128-row tiles, a workgroup per tile, two per CU, with
-// bins for every count; above, 256-row tiles, one persistent workgroup per CU.  With few
-// tiles the 256-row ones leave CUs idle and end in a long last round (2+1 diamonds, fp4 /
-// int8, us: 5000 points 41 / 55 against 28 / 30, 8192 points 74 / 97 against 65 / 81);
-// further up their operand reuse wins (16384 points: 310 / 470 against 400 / 600).  Below
-// 4096 points 128-row tiles used to share one CU each and, from 512 tiles, queues that every
-// workgroup probed before it left: 4096 points 43 / 46 -> 18 / 21.
-constexpr int64_t kSmallN = 8193;
-constexpr int kBinsSmall = (int)kSmallN - 1;  // counts are at most n - 2
+// One instance takes 128-row tiles, two workgroups per CU, up to the sizes below, and 256-row
+// tiles, one persistent workgroup per CU, above them.  Two workgroups run one's epilogue
+// beside the other's matrix work and spread few tiles evenly; the larger tiles' operand
+// reuse wins further up, earlier for int8 (twice the matrix time per byte saved) and earlier
+// where the epilogue is the histogram's.  128 / 256 rows, us, fp4 and int8:
+//   histogram (2+1)    5000: 29 / 41, 30 / 55;  10007: 92 / 114, 142 / 154;
+//                      16384: 281 / 305, 476 / 446;  28000: 1222 / 1204, 2140 / 1934
+//   d'Alembertian (3+1) 10007: 81 / 122, 126 / 147;  16384: 265 / 331, 443 / 434;
+//                      28000: 1175 / 1290, 2044 / 1891
+// Up to kBinsSmall + 1 points every count fits the bins.  Up to kPerTile tiles (8193
+// points) each tile is a workgroup, longest first; more tiles are taken from one queue by
+// resident workgroups, which flush their bins once instead of per tile (the d'Alembertian
+// has none: a workgroup per tile always).
+constexpr int kBinsSmall = 11776;  // 2 x 80 KiB of LDS per CU
+constexpr int64_t kSmallHistFp4 = 24000, kSmallHistInt8 = kBinsSmall + 1;
+constexpr int64_t kSmallFieldFp4 = 32768, kSmallFieldInt8 = 15000;
+constexpr int64_t kPerTile = 65 * 66 / 2;
 constexpr int kBinsBatch = 8192;        // LDS histogram bins, ensembles (n <= 8192)
 
 // Output tile t (0-based) in longest-first order for a T x T tile triangle:
@@ -794,8 +802,8 @@ __device__ __attribute__((always_inline)) inline bool mfma_tile(const TileArgs& 
     // related rows i with m interior elements.  c_m comes from a table in LDS after the
     // rows' phi, indexed by min(key, 4): entry 4 is 0, for m >= 4 and for unrelated pairs
     // (key 0xFFFFFFFF).  Each row's phi is read once for the WM column blocks.  The two
-    // half-waves hold the same columns and are combined by a lane exchange, and each wave
-    // row adds its partial sums to out[j] with one fp64 atomic per column.
+    // half-waves hold the same columns and are combined by a lane exchange, and 128 rows'
+    // partial sums are added to out[j] with one fp64 atomic per column.
     const double* ctab = phis + BM;
     double part[WM];
 #pragma unroll
@@ -824,11 +832,21 @@ __device__ __attribute__((always_inline)) inline bool mfma_tile(const TileArgs& 
         }
       }
     }
+    // 128-row tiles: the two wave rows meet in LDS (the ring is free), so that a column
+    // takes one addition per 128 rows with either tile size.
+    double* const cols = (double*)ring;
 #pragma unroll
     for (int nb = 0; nb < WM; ++nb) {
-      const double sum = part[nb] + __shfl_xor(part[nb], 32);
-      const int64_t j = J0 + wc * (WM * 32) + nb * 32 + l32;
-      if (hsel == 0 && sum != 0.0 && j < n) atomicAdd(ta.f.out + j, sum);
+      part[nb] += __shfl_xor(part[nb], 32);
+      if (WM == 2 && wr == 1 && hsel == 0) cols[wc * (WM * 32) + nb * 32 + l32] = part[nb];
+    }
+    if constexpr (WM == 2) __syncthreads();
+#pragma unroll
+    for (int nb = 0; nb < WM; ++nb) {
+      const int c = wc * (WM * 32) + nb * 32 + l32;
+      const double sum = WM == 2 && wr == 0 ? part[nb] + cols[c] : part[nb];
+      const int64_t j = J0 + c;
+      if ((WM == 4 || wr == 0) && hsel == 0 && sum != 0.0 && j < n) atomicAdd(ta.f.out + j, sum);
     }
   }
   return true;
@@ -1207,12 +1225,12 @@ __device__ inline int xcc_id() {
 // ===========================================================================
 // Single-instance kernels: over the T(T+1)/2 tiles, longest first.
 // ===========================================================================
-template <int BM, int HB>
+template <int BM, int HB, int EPI = 0>
 struct MfmaLds {
   uint32_t ring[MRing<BM>::value * 2 * BM * kMStageU32] __attribute__((aligned(16)));
   uint32_t rel[BM == 128 ? 1 : BM * BM / 32];  // relation bits of the tile's pairs (i < j);
                                               // 128-row tiles keep theirs in registers
-  double phis[BM + 8];         // phi of the tile's rows, then c_0 .. c_3, 0 (d'Alembertian)
+  double phis[EPI == 1 ? BM + 8 : 1];  // phi of the tile's rows, then c_0 .. c_3, 0 (d'Alembertian)
   uint32_t hist[HB + 64];      // bins, then one spare word per lane (never flushed)
   uint32_t maxbin;
   int slot;
@@ -1227,17 +1245,16 @@ struct BitsetLds {
   int slot;
 };
 
-// WM = 4: one workgroup per CU (its ring fills the LDS), HB bins of possibly larger counts.
-// WM = 2: two per CU; every count fits the HB bins.
-template <int WM, bool FP4, int EPI, int HB>
+// WM = 4: one workgroup per CU (its ring fills the LDS).  WM = 2: two per CU.  FITS: every
+// count is below HB.
+template <int WM, bool FP4, int EPI, int HB, bool FITS>
 __global__ __launch_bounds__(kThreads, WM == 4 ? 1 : 2) void k_count_mfma(const uint64_t* __restrict__ S,
                                                             int64_t n, int64_t ld,
                                                             unsigned long long* __restrict__ hist,
                                                             unsigned int* __restrict__ counter,
                                                             FieldArgs f) {
   constexpr int BM = 2 * WM * 32;
-  constexpr bool FITS = WM == 2;
-  __shared__ MfmaLds<BM, HB> L;  // 96 KiB ring + 48 KiB bins + 8 KiB relation bits at WM = 4
+  __shared__ MfmaLds<BM, HB, EPI> L;  // 96 KiB ring + 48 KiB bins + 8 KiB relation bits at WM = 4
   const int64_t T = ceil_div(n, BM);
   if constexpr (EPI == 0)  // the bins a count can reach
     for (int b = threadIdx.x; b < HB && b < n - 1; b += kThreads) L.hist[b] = 0;
@@ -1442,15 +1459,16 @@ cs_status launch_fill_u64(uint64_t* p, int64_t count, uint64_t value, hipStream_
 
 size_t histogram_ws_bytes(int64_t, int) { return 256; }
 
-template <int WM, bool FP4, int EPI, int HB>
+template <int WM, bool FP4, int EPI, int HB, bool FITS>
 cs_status launch_mfma(const uint64_t* bits, int64_t n, int64_t ld, uint64_t* hist,
                       unsigned int* ctr, hipStream_t st, FieldArgs f = FieldArgs{}) {
   constexpr int BM = 2 * WM * 32;
   const int64_t T = ceil_div(n, BM);
-  // WM = 2: a workgroup per tile, longest first; no queue
-  const unsigned grid =
-      (unsigned)(WM == 2 ? T * (T + 1) / 2 : std::min<int64_t>(T * (T + 1) / 2, device_cu_count()));
-  hipLaunchKernelGGL((k_count_mfma<WM, FP4, EPI, HB>), dim3(grid), dim3(kThreads), 0, st, bits, n, ld,
+  const int64_t tiles = T * (T + 1) / 2;
+  const int64_t resident = (WM == 2 ? 2 : 1) * (int64_t)device_cu_count();
+  const bool per_tile = WM == 2 && (EPI == 1 || tiles <= kPerTile);
+  const unsigned grid = (unsigned)(per_tile ? tiles : std::min(tiles, resident));
+  hipLaunchKernelGGL((k_count_mfma<WM, FP4, EPI, HB, FITS>), dim3(grid), dim3(kThreads), 0, st, bits, n, ld,
                      (unsigned long long*)hist, ctr, f);
   CS_LAUNCH_CHECK();
   return CS_OK;
@@ -1468,14 +1486,18 @@ cs_status launch_histogram(const uint64_t* bits, int64_t n, int64_t ld, int coun
   unsigned int* ctr = (unsigned int*)ws;
   cs_status s = launch_zero2(hist, n - 1, (uint64_t*)ws, 4, st);  // bins, 8 queue counters
   if (s != CS_OK) return s;
-  const bool big = n > kSmallN;
+  const bool fits = n <= kBinsSmall + 1;
   switch (counter) {
     case CS_COUNT_MFMA:
-      return big ? launch_mfma<4, false, 0, kBinsSingle>(bits, n, ld, hist, ctr, st)
-                 : launch_mfma<2, false, 0, kBinsSmall>(bits, n, ld, hist, ctr, st);
+      static_assert(kSmallHistInt8 <= kBinsSmall + 1, "no int8 kernel with larger counts");
+      return n <= kSmallHistInt8
+                 ? launch_mfma<2, false, 0, kBinsSmall, true>(bits, n, ld, hist, ctr, st)
+                 : launch_mfma<4, false, 0, kBinsSingle, false>(bits, n, ld, hist, ctr, st);
     case CS_COUNT_MFMA_FP4:
-      return big ? launch_mfma<4, true, 0, kBinsSingle>(bits, n, ld, hist, ctr, st)
-                 : launch_mfma<2, true, 0, kBinsSmall>(bits, n, ld, hist, ctr, st);
+      return fits ? launch_mfma<2, true, 0, kBinsSmall, true>(bits, n, ld, hist, ctr, st)
+             : n <= kSmallHistFp4
+                 ? launch_mfma<2, true, 0, kBinsSmall, false>(bits, n, ld, hist, ctr, st)
+                 : launch_mfma<4, true, 0, kBinsSingle, false>(bits, n, ld, hist, ctr, st);
     default: {
       const int64_t T = ceil_div(n, 128);
       const unsigned grid = (unsigned)std::min<int64_t>(T * (T + 1) / 2, 2 * device_cu_count());
@@ -1509,13 +1531,12 @@ cs_status launch_dalembertian(const uint64_t* bits, int64_t n, int64_t ld, int c
     K = 4.0 / sqrt(6.0);
     f.c0 = 1.0; f.c1 = -9.0; f.c2 = 16.0; f.c3 = -8.0;
   }
-  const bool big = n > kSmallN;
   if (counter == CS_COUNT_MFMA)
-    s = big ? launch_mfma<4, false, 1, 1>(bits, n, ld, nullptr, ctr, st, f)
-            : launch_mfma<2, false, 1, 1>(bits, n, ld, nullptr, ctr, st, f);
+    s = n <= kSmallFieldInt8 ? launch_mfma<2, false, 1, 1, true>(bits, n, ld, nullptr, ctr, st, f)
+                             : launch_mfma<4, false, 1, 1, true>(bits, n, ld, nullptr, ctr, st, f);
   else
-    s = big ? launch_mfma<4, true, 1, 1>(bits, n, ld, nullptr, ctr, st, f)
-            : launch_mfma<2, true, 1, 1>(bits, n, ld, nullptr, ctr, st, f);
+    s = n <= kSmallFieldFp4 ? launch_mfma<2, true, 1, 1, true>(bits, n, ld, nullptr, ctr, st, f)
+                            : launch_mfma<4, true, 1, 1, true>(bits, n, ld, nullptr, ctr, st, f);
   if (s != CS_OK) return s;
   hipLaunchKernelGGL(k_field_finish, dim3((unsigned)ceil_div(n, 256)), dim3(256), 0, st, phi, out, n,
                      K / (ell * ell));

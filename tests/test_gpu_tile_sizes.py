@@ -1,7 +1,8 @@
-"""GPU parity of the matrix counters and the d'Alembertian where one instance changes from
-128-row tiles (a workgroup per tile, bins for every count, up to 8193 points) to 256-row
-ones, and at the edges of their tiles, against the oracle; a total order makes the counts
-reach the last bin."""
+"""GPU parity of the matrix counters and the d'Alembertian where one instance changes its
+form, and at the edges of the tiles, against the oracle: a workgroup per 128-row tile up to
+8193 points, resident workgroups above, bins for every count up to 11777 points, 256-row
+tiles above 11777 (int8) and 24000 (fp4), for the d'Alembertian above 15000 and 32768.  A
+total order makes the counts reach the last bin."""
 import numpy as np
 import pytest
 
@@ -14,7 +15,8 @@ torch = pytest.importorskip("torch")
 
 
 @pytest.mark.parametrize("counter", [1, 2], ids=["mfma", "mfma_fp4"])
-@pytest.mark.parametrize("n", [129, 3969, 4097, 8065, 8192, 8193, 8194, 8449])
+@pytest.mark.parametrize("n", [129, 3969, 4097, 8065, 8192, 8193, 8320, 8321, 8449, 11777, 11778,
+                               12000])
 def test_histogram_sizes(cs, orc, n, counter):  # noqa: F811
     coords = orc.sprinkle(W.MINK3_DIAMOND, n, 3 * n)
     bits = orc.causal_matrix(W.MINK3_DIAMOND, coords)
@@ -24,7 +26,7 @@ def test_histogram_sizes(cs, orc, n, counter):  # noqa: F811
 
 
 @pytest.mark.parametrize("counter", [1, 2], ids=["mfma", "mfma_fp4"])
-@pytest.mark.parametrize("n", [4096, 8193, 8194])
+@pytest.mark.parametrize("n", [4096, 8193, 8321, 11777, 11778, 11841, 24000, 24001])
 def test_total_order(cs, n, counter):  # noqa: F811
     """N_m = n - 1 - m for m = 0 .. n - 2."""
     u = torch.arange(n, dtype=torch.float64, device="cuda") / n
@@ -35,6 +37,19 @@ def test_total_order(cs, n, counter):  # noqa: F811
 
 
 @pytest.mark.parametrize("counter", [1, 2], ids=["mfma", "mfma_fp4"])
-@pytest.mark.parametrize("n", [8193, 8194])
+@pytest.mark.parametrize("n", [8193, 15000, 15001])
 def test_dalembertian_sizes(cs, orc, n, counter):  # noqa: F811
     check(cs, orc, W.MINK2_DIAMOND, 2, n, 5 + n, counter)
+
+
+@pytest.mark.parametrize("n", [32768, 32769])
+def test_dalembertian_large_total_order(cs, n):  # noqa: F811
+    """phi = 1 on a total order: L_m(j) holds one element for m <= j, so 2 (-1 + 2 - 4 + 2)
+    = -2 from j = 3 on, and the first elements lack the layers below them."""
+    u = torch.arange(n, dtype=torch.float64, device="cuda") / n
+    b = cs.cs_causal_matrix(W.MINK2_DIAMOND, torch.stack([u, u]).contiguous())
+    phi = torch.ones(n, dtype=torch.float64, device="cuda")
+    got = cs.cs_dalembertian(b, n, 2, 1.0, phi).cpu().numpy()
+    want = np.full(n, -2.0)
+    want[:3] = [-2.0, 2.0, -6.0]
+    assert np.array_equal(got, want)
