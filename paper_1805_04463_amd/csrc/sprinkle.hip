@@ -2,11 +2,11 @@
 // Sec. 3.2 "Pairwise Relations": label elements so that no later index precedes
 // an earlier one).
 //
-// Pipeline per call: generate raw SoA coordinates + a 64-bit time key per point
-// -> bitonic sort of (key, generation index) pairs (LDS chunks of 2048 + global
-// merge steps) -> gather the coordinate planes into sorted order.  Sets of at most
-// 8192 points skip the sort and the gather: each point's rank is counted over all
-// keys and its planes are written there.
+// Pipeline per call: generate raw SoA coordinates, a 64-bit time key and a bucket per point
+// -> scan the bucket counts -> scatter the points to their buckets -> place each bucket's
+// points in (key, generation index) order straight into the coordinate planes.  Sets of
+// at most kRankMaxN points skip the buckets: each point's rank is counted over all keys and
+// its planes are written there.
 // The 3+1 diamond is sampled by rejection: candidates are flagged, counted per
 // block, scanned, and the first n accepted are scattered in candidate order.
 #include "common.h"
@@ -15,7 +15,13 @@ namespace cs {
 namespace {
 
 constexpr int kBlock = 256;
-constexpr int kSortChunk = 2048;  // elements sorted per LDS pass (1024 threads)
+constexpr int kBucketMean = 64;     // points per bucket on average; at most four times as many
+                                    // expected anywhere (the densities below)
+constexpr int kBucketCap = 2048;    // points of a bucket placed through LDS
+constexpr int kBucketPad = 16;      // counters 64 bytes apart: adds to one line queue up (30001
+                                    // points of the 3+1 diamond: 45 us with counters side by side)
+constexpr int kPlaceThreads = 512;
+constexpr int kPlaceSplit = 4;      // lanes that share a point's comparisons
 
 // Candidate budget of the rejection samplers of the diamonds of height 1: the
 // acceptance probability is the diamond's volume in the unit box, pi/24 (3+1) or
@@ -30,23 +36,23 @@ int64_t mink_candidates(int region, int64_t n) {
   return align_up((size_t)m, kBlock);
 }
 
-int64_t pow2_at_least(int64_t n) {
-  int64_t p = 2;
-  while (p < n) p <<= 1;
-  return p;
-}
+int64_t buckets_of(int64_t n) { return ceil_div(n, kBucketMean); }
 
 struct SprinkleWs {
   double* raw;
   uint64_t* keys;
-  uint32_t* gens;
+  uint32_t* arrive;      // arrival number of each point in its bucket
+  uint32_t* slots;       // points by bucket
+  uint32_t* bkt_of;      // bucket of each point
+  uint32_t* bkt_count;   // points per bucket, kBucketPad apart, zeroed before the draws
+  uint64_t* bkt_start;   // their exclusive scan, plus [buckets] = n
   uint32_t* blk_count;   // rejection samplers only
   uint64_t* blk_offset;  // rejection samplers only (exclusive scan), plus [nblk] = total
 };
 
 size_t layout(int region, int64_t n, void* base, SprinkleWs* w) {
   const int planes = coord_planes(region);
-  const int64_t P = pow2_at_least(n);
+  const int64_t B = buckets_of(n);
   size_t off = 0;
   auto take = [&](size_t bytes) {
     size_t o = off;
@@ -54,8 +60,12 @@ size_t layout(int region, int64_t n, void* base, SprinkleWs* w) {
     return o;
   };
   size_t o_raw = take(sizeof(double) * planes * n);
-  size_t o_keys = take(sizeof(uint64_t) * P);
-  size_t o_gens = take(sizeof(uint32_t) * P);
+  size_t o_keys = take(sizeof(uint64_t) * n);
+  size_t o_arrive = take(sizeof(uint32_t) * n);
+  size_t o_slots = take(sizeof(uint32_t) * n);
+  size_t o_bof = take(sizeof(uint32_t) * n);
+  size_t o_bcnt = take(sizeof(uint32_t) * B * kBucketPad);
+  size_t o_bstart = take(sizeof(uint64_t) * (B + 1));
   size_t o_cnt = 0, o_off = 0;
   if (is_rejection(region)) {
     int64_t nblk = mink_candidates(region, n) / kBlock;
@@ -66,31 +76,54 @@ size_t layout(int region, int64_t n, void* base, SprinkleWs* w) {
     char* b = (char*)base;
     w->raw = (double*)(b + o_raw);
     w->keys = (uint64_t*)(b + o_keys);
-    w->gens = (uint32_t*)(b + o_gens);
+    w->arrive = (uint32_t*)(b + o_arrive);
+    w->slots = (uint32_t*)(b + o_slots);
+    w->bkt_of = (uint32_t*)(b + o_bof);
+    w->bkt_count = (uint32_t*)(b + o_bcnt);
+    w->bkt_start = (uint64_t*)(b + o_bstart);
     w->blk_count = is_rejection(region) ? (uint32_t*)(b + o_cnt) : nullptr;
     w->blk_offset = is_rejection(region) ? (uint64_t*)(b + o_off) : nullptr;
   }
   return off;
 }
 
+// Where the samplers put a point's time key and, for sets that are placed by buckets (B >
+// 0), its bucket: a monotone map of the key onto [0, B), under which no bucket holds more
+// than four times the mean.  (Densities of the key: 2 at the middle of the u + v triangle,
+// 3 and 4 at the waists of the 2+1 and 3+1 diamonds, 1 in tan(eta) on the 1+1 slab, up to
+// 3 at the ends of the 3+1 slab.)
+struct KeyOut {
+  uint64_t* keys;
+  uint32_t *bkt_of, *arrive, *bkt_count;
+  uint64_t B;
+};
+__device__ inline void put_key(const KeyOut& o, int64_t g, uint64_t key, uint64_t bucket) {
+  o.keys[g] = key;
+  if (o.B == 0) return;
+  const uint32_t b = (uint32_t)(bucket < o.B ? bucket : o.B - 1);
+  o.bkt_of[g] = b;
+  o.arrive[g] = atomicAdd(&o.bkt_count[(uint64_t)b * kBucketPad], 1u);
+}
+// Integer keys of `bits` bits; real keys on [-X, X].
+__device__ inline uint64_t bucket_of_bits(uint64_t key, int bits, uint64_t B) {
+  return __umul64hi(key << (64 - bits), B);
+}
+__device__ inline uint64_t bucket_of_real(double x, double X, uint64_t B) {
+  const double b = (x + X) * ((double)B / (2.0 * X));
+  return b > 0.0 ? (uint64_t)b : 0ull;
+}
+
 // ---------------------------------------------------------------------------
 // 1+1 diamond: u = U(2g), v = U(2g+1); key = exact integer (u + v) * 2^53.
 // ---------------------------------------------------------------------------
-__global__ void k_sprinkle_mink2(uint64_t skey, int64_t n, int64_t P, double* __restrict__ raw,
-                                 uint64_t* __restrict__ keys, uint32_t* __restrict__ gens) {
+__global__ void k_sprinkle_mink2(uint64_t skey, int64_t n, double* __restrict__ raw, KeyOut out) {
   int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (g >= P) return;
-  if (g < n) {
-    uint64_t ku = sm_output(skey, 2 * (uint64_t)g) >> 11;
-    uint64_t kv = sm_output(skey, 2 * (uint64_t)g + 1) >> 11;
-    raw[g] = (double)ku * 0x1.0p-53;
-    raw[n + g] = (double)kv * 0x1.0p-53;
-    keys[g] = ku + kv;
-    gens[g] = (uint32_t)g;
-  } else {
-    keys[g] = ~0ull;
-    gens[g] = 0xFFFFFFFFu;
-  }
+  if (g >= n) return;
+  uint64_t ku = sm_output(skey, 2 * (uint64_t)g) >> 11;
+  uint64_t kv = sm_output(skey, 2 * (uint64_t)g + 1) >> 11;
+  raw[g] = (double)ku * 0x1.0p-53;
+  raw[n + g] = (double)kv * 0x1.0p-53;
+  put_key(out, g, ku + kv, bucket_of_bits(ku + kv, 54, out.B));
 }
 
 // ---------------------------------------------------------------------------
@@ -146,59 +179,75 @@ __global__ void k_mink_count(uint64_t skey, uint32_t* __restrict__ blk_count) {
   if (threadIdx.x == 0) blk_count[blockIdx.x] = tot;
 }
 
-// Exclusive scan of nblk block counts by one workgroup of 1024 threads.
-__global__ void k_scan_counts(const uint32_t* __restrict__ cnt, int64_t nblk,
-                              uint64_t* __restrict__ off) {
-  __shared__ uint64_t s[1024];
+// Exclusive scan of nblk counts, `stride` apart, by one workgroup of 1024 threads, eight counts per thread
+// and step: lane exchanges within the waves, their sums through LDS.
+constexpr int kScanPer = 8;
+__global__ __launch_bounds__(1024) void k_scan_counts(const uint32_t* __restrict__ cnt, int stride,
+                                                      int64_t nblk, uint64_t* __restrict__ off) {
+  __shared__ uint64_t wave_sum[2][16];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   uint64_t carry = 0;
-  for (int64_t base = 0; base < nblk; base += 1024) {
-    int64_t i = base + threadIdx.x;
-    uint64_t v = i < nblk ? cnt[i] : 0;
-    s[threadIdx.x] = v;
-    __syncthreads();
-    for (int d = 1; d < 1024; d <<= 1) {  // Hillis-Steele inclusive scan
-      uint64_t a = threadIdx.x >= (unsigned)d ? s[threadIdx.x - d] : 0;
-      __syncthreads();
-      s[threadIdx.x] += a;
-      __syncthreads();
+  int buf = 0;
+  for (int64_t base = 0; base < nblk; base += 1024 * kScanPer, buf ^= 1) {
+    const int64_t i0 = base + (int64_t)threadIdx.x * kScanPer;
+    uint32_t v[kScanPer];
+    uint64_t sum = 0;
+#pragma unroll
+    for (int q = 0; q < kScanPer; ++q) {
+      v[q] = i0 + q < nblk ? cnt[(i0 + q) * stride] : 0u;
+      sum += v[q];
     }
-    if (i < nblk) off[i] = carry + s[threadIdx.x] - v;
-    carry += s[1023];
+    uint64_t x = sum;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const uint64_t y = __shfl_up((unsigned long long)x, d);
+      if (lane >= d) x += y;
+    }
+    if (lane == 63) wave_sum[buf][wave] = x;
     __syncthreads();
+    uint64_t at = carry + x - sum, total = 0;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) {
+      const uint64_t s = wave_sum[buf][w];
+      at += w < wave ? s : 0ull;
+      total += s;
+    }
+#pragma unroll
+    for (int q = 0; q < kScanPer; ++q) {
+      if (i0 + q < nblk) off[i0 + q] = at;
+      at += v[q];
+    }
+    carry += total;
   }
   if (threadIdx.x == 0) off[nblk] = carry;
 }
 
 template <int D>
-__device__ inline void put(const Cand& r, uint64_t rank, int64_t n, double* raw, uint64_t* keys,
-                            uint32_t* gens) {
+__device__ inline void put(const Cand& r, uint64_t rank, int64_t n, double* raw, const KeyOut& out) {
   raw[rank] = r.t;
   raw[n + rank] = r.x;
   raw[2 * n + rank] = r.y;
   if (D == 4) raw[3 * n + rank] = r.z;
-  keys[rank] = r.kt;
-  gens[rank] = (uint32_t)rank;
+  put_key(out, (int64_t)rank, r.kt, bucket_of_bits(r.kt, 53, out.B));
 }
 
 template <int D>
 __global__ void k_mink_scatter(uint64_t skey, int64_t n, const uint64_t* __restrict__ blk_off,
-                                double* __restrict__ raw, uint64_t* __restrict__ keys,
-                                uint32_t* __restrict__ gens) {
+                                double* __restrict__ raw, KeyOut out) {
   __shared__ uint32_t s_wave[kBlock / 64];
   uint64_t c = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
   Cand r = mink_candidate<D>(skey, c);
   uint32_t tot;
   uint32_t local = block_rank(r.ok, &tot, s_wave);
   uint64_t rank = blk_off[blockIdx.x] + local;
-  if (r.ok && rank < (uint64_t)n) put<D>(r, rank, n, raw, keys, gens);
+  if (r.ok && rank < (uint64_t)n) put<D>(r, rank, n, raw, out);
 }
 
 // Continues candidates after the budget if (improbably) fewer than n were accepted.
 // One workgroup; bounded number of rounds.
 template <int D>
 __global__ void k_mink_tail(uint64_t skey, int64_t n, int64_t M, const uint64_t* __restrict__ total,
-                             double* __restrict__ raw, uint64_t* __restrict__ keys,
-                             uint32_t* __restrict__ gens) {
+                             double* __restrict__ raw, KeyOut out) {
   __shared__ uint32_t s_wave[kBlock / 64];
   uint64_t have = *total;
   const int64_t kMaxRounds = 1ll << 22;
@@ -208,17 +257,8 @@ __global__ void k_mink_tail(uint64_t skey, int64_t n, int64_t M, const uint64_t*
     uint32_t tot;
     uint32_t local = block_rank(r.ok, &tot, s_wave);
     uint64_t rank = have + local;
-    if (r.ok && rank < (uint64_t)n) put<D>(r, rank, n, raw, keys, gens);
+    if (r.ok && rank < (uint64_t)n) put<D>(r, rank, n, raw, out);
     have += tot;
-  }
-}
-
-__global__ void k_pad_keys(int64_t n, int64_t P, uint64_t* __restrict__ keys,
-                           uint32_t* __restrict__ gens) {
-  int64_t g = n + (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (g < P) {
-    keys[g] = ~0ull;
-    gens[g] = 0xFFFFFFFFu;
   }
 }
 
@@ -227,16 +267,10 @@ __global__ void k_pad_keys(int64_t n, int64_t P, uint64_t* __restrict__ keys,
 // uniform, x = (2u - 1) tan(eta0) (one rounding); eta = atan(x); theta = 2 pi w.
 // Sorted by x, which orders the points by eta.
 // ---------------------------------------------------------------------------
-__global__ void k_sprinkle_ds2(uint64_t skey, double X, int64_t n, int64_t P,
-                               double* __restrict__ raw, uint64_t* __restrict__ keys,
-                               uint32_t* __restrict__ gens) {
+__global__ void k_sprinkle_ds2(uint64_t skey, double X, int64_t n, double* __restrict__ raw,
+                               KeyOut out) {
   int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (g >= P) return;
-  if (g >= n) {
-    keys[g] = ~0ull;
-    gens[g] = 0xFFFFFFFFu;
-    return;
-  }
+  if (g >= n) return;
   const double two_pi = 2.0 * 3.141592653589793;  // twice the double nearest pi (exact)
   double u = unit53(sm_output(skey, 2 * (uint64_t)g));
   double w = unit53(sm_output(skey, 2 * (uint64_t)g + 1));
@@ -244,24 +278,17 @@ __global__ void k_sprinkle_ds2(uint64_t skey, double X, int64_t n, int64_t P,
   raw[g] = x;
   raw[n + g] = atan(x);
   raw[2 * n + g] = __dmul_rn(two_pi, w);
-  keys[g] = order_bits(x);
-  gens[g] = (uint32_t)g;
+  put_key(out, g, order_bits(x), bucket_of_real(x, X, out.B));
 }
 
 // ---------------------------------------------------------------------------
 // 3+1 de Sitter slab: x = tan(eta) from the inverse CDF of (1 + x^2) dx,
 // x = 2 sinh(asinh(3y/2)/3); direction on S^3 by cube rejection, normalised.
 // ---------------------------------------------------------------------------
-__global__ void k_sprinkle_ds4(uint64_t skey_t, uint64_t skey_s, double X, int64_t n, int64_t P,
-                               double* __restrict__ raw, uint64_t* __restrict__ keys,
-                               uint32_t* __restrict__ gens) {
+__global__ void k_sprinkle_ds4(uint64_t skey_t, uint64_t skey_s, double X, int64_t n,
+                               double* __restrict__ raw, KeyOut out) {
   int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (g >= P) return;
-  if (g >= n) {
-    keys[g] = ~0ull;
-    gens[g] = 0xFFFFFFFFu;
-    return;
-  }
+  if (g >= n) return;
   double Y = __dadd_rn(X, __ddiv_rn(__dmul_rn(__dmul_rn(X, X), X), 3.0));
   double u = unit53(sm_output(skey_t, (uint64_t)g));
   double y = __dmul_rn(__dsub_rn(__dmul_rn(2.0, u), 1.0), Y);
@@ -291,91 +318,59 @@ __global__ void k_sprinkle_ds4(uint64_t skey_t, uint64_t skey_s, double X, int64
   raw[4 * n + g] = __ddiv_rn(a1, r);
   raw[5 * n + g] = __ddiv_rn(a2, r);
   raw[6 * n + g] = __ddiv_rn(a3, r);
-  keys[g] = order_bits(x);
-  gens[g] = (uint32_t)g;
+  put_key(out, g, order_bits(x), bucket_of_real(x, X, out.B));
 }
 
 // ---------------------------------------------------------------------------
-// Bitonic sort of (key, gen) pairs, P a power of two.
+// Time order by buckets.  The points of a bucket are brought together (k_bucket_scatter), and
+// a workgroup per bucket counts each one's rank among them and writes its planes to the
+// bucket's start plus the rank.  Four launches that pass over the points once each, bound
+// by launches and latency, where a bitonic network took 10 to 30 launches: the whole call for
+// a 3+1 diamond of 30001 points 35 us against 83, of 131072 points 49 against 133.  A bucket
+// of more than kBucketCap points (none arises from these densities) is ranked from memory.
 // ---------------------------------------------------------------------------
-__device__ inline void cmp_swap_lds(uint64_t* sk, uint32_t* sg, int i, int l, bool asc) {
-  uint64_t ka = sk[i], kb = sk[l];
-  uint32_t ga = sg[i], gb = sg[l];
-  bool gt = key_less(kb, gb, ka, ga);  // a > b
-  if (gt == asc) {
-    sk[i] = kb; sk[l] = ka;
-    sg[i] = gb; sg[l] = ga;
-  }
+__global__ void k_bucket_scatter(int64_t n, const uint32_t* __restrict__ bkt_of,
+                                 const uint32_t* __restrict__ arrive,
+                                 const uint64_t* __restrict__ start, uint32_t* __restrict__ slots) {
+  const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (g < n) slots[start[bkt_of[g]] + arrive[g]] = (uint32_t)g;
 }
 
-// Orders a bitonic compare-exchange step after the previous one.  A step of distance
-// j <= 64 pairs thread t (of a wave's 64) with elements inside the 128-element block
-// t / 64 (in steps of 64 threads), so each block belongs to one wave: such a step needs
-// only the wave's own earlier LDS writes.  Steps of larger distance, and the first step
-// after another step of larger distance or after loading, synchronise the workgroup.
-__device__ inline void bitonic_step_sync(bool workgroup) {
-  if (workgroup) {
-    __syncthreads();
-  } else {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  }
-}
-
-// kfirst == 0: full sort of each chunk (k = 2 .. CH).  Otherwise: the j < CH steps of
-// merge stage k = kfirst.  One thread per pair; CH/2 threads per block.
-__global__ void k_bitonic_lds(uint64_t* __restrict__ keys, uint32_t* __restrict__ gens, int CH,
-                              int64_t kfirst) {
-  __shared__ uint64_t sk[kSortChunk];
-  __shared__ uint32_t sg[kSortChunk];
-  const int64_t base = (int64_t)blockIdx.x * CH;
-  const int t = threadIdx.x;
-  sk[t] = keys[base + t];
-  sg[t] = gens[base + t];
-  sk[t + CH / 2] = keys[base + t + CH / 2];
-  sg[t + CH / 2] = gens[base + t + CH / 2];
-  int64_t k0 = kfirst ? kfirst : 2;
-  int64_t k1 = kfirst ? kfirst : CH;
-  bool wide = true;  // the previous step (or the load) crossed 128-element blocks
-  for (int64_t k = k0; k <= k1; k <<= 1) {
-    int jstart = (int)((k >> 1) < (CH >> 1) ? (k >> 1) : (CH >> 1));
-    for (int j = jstart; j > 0; j >>= 1) {
-      bitonic_step_sync(wide || j >= 128);
-      wide = j >= 128;
-      int i = 2 * t - (t & (j - 1));
-      bool asc = ((base + i) & k) == 0;
-      cmp_swap_lds(sk, sg, i, i + j, asc);
+__global__ __launch_bounds__(kPlaceThreads) void k_bucket_place(
+    const uint64_t* __restrict__ keys, const uint32_t* __restrict__ slots,
+    const uint64_t* __restrict__ start, const double* __restrict__ raw, int planes, int64_t n,
+    double* __restrict__ coords) {
+  __shared__ uint64_t sk[kBucketCap];
+  __shared__ uint32_t sg[kBucketCap];
+  const int64_t lo = (int64_t)start[blockIdx.x], m = (int64_t)start[blockIdx.x + 1] - lo;
+  const bool lds = m <= kBucketCap;
+  if (lds) {
+    for (int i = threadIdx.x; i < m; i += kPlaceThreads) {
+      const uint32_t g = slots[lo + i];
+      sg[i] = g;
+      sk[i] = keys[g];
     }
+    __syncthreads();
   }
-  __syncthreads();
-  keys[base + t] = sk[t];
-  gens[base + t] = sg[t];
-  keys[base + t + CH / 2] = sk[t + CH / 2];
-  gens[base + t + CH / 2] = sg[t + CH / 2];
-}
-
-__global__ void k_bitonic_global(uint64_t* __restrict__ keys, uint32_t* __restrict__ gens,
-                                 int64_t P, int64_t k, int64_t j) {
-  int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= P / 2) return;
-  int64_t i = 2 * t - (t & (j - 1));
-  int64_t l = i + j;
-  bool asc = (i & k) == 0;
-  uint64_t ka = keys[i], kb = keys[l];
-  uint32_t ga = gens[i], gb = gens[l];
-  if (key_less(kb, gb, ka, ga) == asc) {
-    keys[i] = kb; keys[l] = ka;
-    gens[i] = gb; gens[l] = ga;
+  const int s = threadIdx.x % kPlaceSplit;
+  for (int64_t i = threadIdx.x / kPlaceSplit; i < m; i += kPlaceThreads / kPlaceSplit) {
+    const uint32_t g = lds ? sg[i] : slots[lo + i];
+    const uint64_t k = lds ? sk[i] : keys[g];
+    uint32_t rank = 0;
+    if (lds) {
+#pragma unroll 8
+      for (int j = s; j < (int)m; j += kPlaceSplit) rank += key_less(sk[j], sg[j], k, g) ? 1u : 0u;
+    } else {
+      for (int64_t j = s; j < m; j += kPlaceSplit) {
+        const uint32_t h = slots[lo + j];
+        rank += key_less(keys[h], h, k, g) ? 1u : 0u;
+      }
+    }
+#pragma unroll
+    for (int off = kPlaceSplit / 2; off > 0; off >>= 1) rank += __shfl_xor(rank, off);
+    for (int p = s; p < planes; p += kPlaceSplit)
+      coords[(int64_t)p * n + lo + rank] = raw[(int64_t)p * n + g];
   }
-}
-
-__global__ void k_gather(const double* __restrict__ raw, const uint32_t* __restrict__ gens,
-                         int planes, int64_t n, double* __restrict__ coords) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  uint32_t g = gens[i];
-  for (int p = 0; p < planes; ++p) coords[(int64_t)p * n + i] = raw[(int64_t)p * n + g];
 }
 
 // ---------------------------------------------------------------------------
@@ -459,24 +454,6 @@ __global__ __launch_bounds__(kRankThreads) void k_rank_place_mink2(uint64_t skey
   }
   const uint32_t lt = rank_lane_sum(before);
   if (live && s < 2) coords[(int64_t)s * n + lt] = (double)(s == 0 ? ku : kv) * 0x1.0p-53;
-}
-
-cs_status bitonic_sort(uint64_t* keys, uint32_t* gens, int64_t P, hipStream_t st) {
-  const int CH = (int)(P < kSortChunk ? P : kSortChunk);
-  const unsigned nchunks = (unsigned)(P / CH);
-  hipLaunchKernelGGL(k_bitonic_lds, dim3(nchunks), dim3(CH / 2), 0, st, keys, gens, CH,
-                     (int64_t)0);
-  CS_LAUNCH_CHECK();
-  for (int64_t k = 2 * (int64_t)CH; k <= P; k <<= 1) {
-    for (int64_t j = k >> 1; j >= CH; j >>= 1) {
-      unsigned blocks = (unsigned)ceil_div(P / 2, 256);
-      hipLaunchKernelGGL(k_bitonic_global, dim3(blocks), dim3(256), 0, st, keys, gens, P, k, j);
-      CS_LAUNCH_CHECK();
-    }
-    hipLaunchKernelGGL(k_bitonic_lds, dim3(nchunks), dim3(CH / 2), 0, st, keys, gens, CH, k);
-    CS_LAUNCH_CHECK();
-  }
-  return CS_OK;
 }
 
 // ---------------------------------------------------------------------------
@@ -652,18 +629,23 @@ cs_status launch_sprinkle(int region, double eta0, uint64_t seed, int64_t n, dou
                           void* ws, hipStream_t st) {
   SprinkleWs w;
   layout(region, n, ws, &w);
-  const int64_t P = pow2_at_least(n);
   const int planes = coord_planes(region);
-  const unsigned gridP = (unsigned)ceil_div(P, kBlock);
+  const unsigned grid = (unsigned)ceil_div(n, kBlock);
   if (region == CS_MINK2_DIAMOND && n <= kRankMaxN) {
     hipLaunchKernelGGL(k_rank_place_mink2, dim3((unsigned)ceil_div(n, kRankPer)), dim3(kRankThreads),
                        0, st, sm_stream_key(seed, kStreamMink2), n, coords);
     CS_LAUNCH_CHECK();
     return CS_OK;
   }
+  const int64_t B = n <= kRankMaxN ? 0 : buckets_of(n);
+  const KeyOut out{w.keys, w.bkt_of, w.arrive, w.bkt_count, (uint64_t)B};
+  if (B > 0) {
+    cs_status s = launch_fill_u64((uint64_t*)w.bkt_count, B * kBucketPad / 2, 0, st);
+    if (s != CS_OK) return s;
+  }
   if (region == CS_MINK2_DIAMOND) {
-    hipLaunchKernelGGL(k_sprinkle_mink2, dim3(gridP), dim3(kBlock), 0, st,
-                       sm_stream_key(seed, kStreamMink2), n, P, w.raw, w.keys, w.gens);
+    hipLaunchKernelGGL(k_sprinkle_mink2, dim3(grid), dim3(kBlock), 0, st,
+                       sm_stream_key(seed, kStreamMink2), n, w.raw, out);
     CS_LAUNCH_CHECK();
   } else if (is_rejection(region)) {
     const bool d4 = region == CS_MINK4_DIAMOND;
@@ -675,31 +657,26 @@ cs_status launch_sprinkle(int region, double eta0, uint64_t seed, int64_t n, dou
     else hipLaunchKernelGGL(k_mink_count<3>, dim3((unsigned)nblk), dim3(kBlock), 0, st, skey,
                             w.blk_count);
     CS_LAUNCH_CHECK();
-    hipLaunchKernelGGL(k_scan_counts, dim3(1), dim3(1024), 0, st, w.blk_count, nblk, w.blk_offset);
+    hipLaunchKernelGGL(k_scan_counts, dim3(1), dim3(1024), 0, st, w.blk_count, 1, nblk, w.blk_offset);
     CS_LAUNCH_CHECK();
     if (d4) hipLaunchKernelGGL(k_mink_scatter<4>, dim3((unsigned)nblk), dim3(kBlock), 0, st, skey,
-                               n, w.blk_offset, w.raw, w.keys, w.gens);
+                               n, w.blk_offset, w.raw, out);
     else hipLaunchKernelGGL(k_mink_scatter<3>, dim3((unsigned)nblk), dim3(kBlock), 0, st, skey,
-                            n, w.blk_offset, w.raw, w.keys, w.gens);
+                            n, w.blk_offset, w.raw, out);
     CS_LAUNCH_CHECK();
     if (d4) hipLaunchKernelGGL(k_mink_tail<4>, dim3(1), dim3(kBlock), 0, st, skey, n, M,
-                               w.blk_offset + nblk, w.raw, w.keys, w.gens);
+                               w.blk_offset + nblk, w.raw, out);
     else hipLaunchKernelGGL(k_mink_tail<3>, dim3(1), dim3(kBlock), 0, st, skey, n, M,
-                            w.blk_offset + nblk, w.raw, w.keys, w.gens);
+                            w.blk_offset + nblk, w.raw, out);
     CS_LAUNCH_CHECK();
-    if (P > n) {
-      hipLaunchKernelGGL(k_pad_keys, dim3((unsigned)ceil_div(P - n, kBlock)), dim3(kBlock), 0, st,
-                         n, P, w.keys, w.gens);
-      CS_LAUNCH_CHECK();
-    }
   } else if (region == CS_DS2_SLAB) {
-    hipLaunchKernelGGL(k_sprinkle_ds2, dim3(gridP), dim3(kBlock), 0, st,
-                       sm_stream_key(seed, kStreamDs2), tan(eta0), n, P, w.raw, w.keys, w.gens);
+    hipLaunchKernelGGL(k_sprinkle_ds2, dim3(grid), dim3(kBlock), 0, st,
+                       sm_stream_key(seed, kStreamDs2), tan(eta0), n, w.raw, out);
     CS_LAUNCH_CHECK();
   } else {
-    hipLaunchKernelGGL(k_sprinkle_ds4, dim3(gridP), dim3(kBlock), 0, st,
+    hipLaunchKernelGGL(k_sprinkle_ds4, dim3(grid), dim3(kBlock), 0, st,
                        sm_stream_key(seed, kStreamDsTime), sm_stream_key(seed, kStreamDsSphere),
-                       tan(eta0), n, P, w.raw, w.keys, w.gens);
+                       tan(eta0), n, w.raw, out);
     CS_LAUNCH_CHECK();
   }
   if (n <= kRankMaxN) {
@@ -708,10 +685,14 @@ cs_status launch_sprinkle(int region, double eta0, uint64_t seed, int64_t n, dou
     CS_LAUNCH_CHECK();
     return CS_OK;
   }
-  cs_status s = bitonic_sort(w.keys, w.gens, P, st);
-  if (s != CS_OK) return s;
-  hipLaunchKernelGGL(k_gather, dim3((unsigned)ceil_div(n, kBlock)), dim3(kBlock), 0, st, w.raw,
-                     w.gens, planes, n, coords);
+  hipLaunchKernelGGL(k_scan_counts, dim3(1), dim3(1024), 0, st, w.bkt_count, kBucketPad, B,
+                     w.bkt_start);
+  CS_LAUNCH_CHECK();
+  hipLaunchKernelGGL(k_bucket_scatter, dim3(grid), dim3(kBlock), 0, st, n, w.bkt_of, w.arrive,
+                     w.bkt_start, w.slots);
+  CS_LAUNCH_CHECK();
+  hipLaunchKernelGGL(k_bucket_place, dim3((unsigned)B), dim3(kPlaceThreads), 0, st, w.keys, w.slots,
+                     w.bkt_start, w.raw, planes, n, coords);
   CS_LAUNCH_CHECK();
   return CS_OK;
 }
