@@ -92,15 +92,27 @@ def _check(rc: int, what: str):
         raise CausalError(f"{what}: {msg} (status {rc})")
 
 
+# A small pass is a handful of calls of ten microseconds, as much host time as device time, so
+# the helpers below ask torch for as little as possible: the device's visibility once, the
+# current device once per call, the current stream as a raw handle, pointers as integers.
+_devices: dict = {}
+
+
 def _dev():
-    if not torch.cuda.is_available():
+    if not _devices and not torch.cuda.is_available():
         raise CausalError("no ROCm GPU visible to torch")
-    return torch.device("cuda", torch.cuda.current_device())
+    index = torch.cuda.current_device()
+    dev = _devices.get(index)
+    if dev is None:
+        dev = _devices[index] = torch.device("cuda", index)
+    return dev
 
 
 def _stream(stream):
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return ctypes.c_void_p(s.cuda_stream)
+    """The stream's hipStream_t, an integer (0: the default stream)."""
+    if stream is not None:
+        return stream.cuda_stream
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _ptr(t: torch.Tensor):
@@ -108,10 +120,8 @@ def _ptr(t: torch.Tensor):
         raise CausalError("expected a device tensor")
     if not t.is_contiguous():
         raise CausalError("expected a contiguous tensor")
-    if t.device.index != torch.cuda.current_device():
-        raise CausalError(f"tensor on {t.device}, but the current device is "
-                          f"cuda:{torch.cuda.current_device()}")
-    return ctypes.c_void_p(t.data_ptr())
+    _on_device(t)
+    return t.data_ptr()
 
 
 def _need(t, name: str, dtypes, numel: int | None = None, min_numel: int | None = None,
@@ -131,13 +141,20 @@ def _need(t, name: str, dtypes, numel: int | None = None, min_numel: int | None 
         raise CausalError(f"{name}: {t.numel()} elements, expected at least {min_numel}")
     if not t.is_contiguous():
         raise CausalError(f"{name}: expected a contiguous tensor")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _on_device(*tensors):
     """Every tensor lives on the current ROCm device (checked after the shapes)."""
+    current = -1
     for t in tensors:
-        _ptr(t)
+        if not t.is_cuda:
+            raise CausalError("expected a device tensor")
+        if current < 0:
+            current = torch.cuda.current_device()
+        if t.get_device() != current:
+            raise CausalError(f"tensor on {t.device}, but the current device is "
+                              f"cuda:{current}")
 
 
 def _nbytes(t: torch.Tensor) -> int:
