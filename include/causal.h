@@ -252,7 +252,8 @@ cs_status cs_degrees(const uint64_t *bits, int64_t n, int64_t ld_words, int64_t 
  *   hist  device, n-1 uint64.   out  device, one double.
  * The local combination is an exact int64; the smeared sum is accumulated in
  * double-double (weights included), then rounded once to fp64.  Bins past the point
- * where (1 - eps)^m < e^-700 are not visited: all their terms together are below 2^-820.
+ * where (1 - eps)^m < 2^-(190 + 4 log2 n) are not visited: all their terms together are
+ * below 2^-120, less than the double-double sum resolves.
  */
 cs_status cs_action(const uint64_t *hist, int64_t n, int dim, double eps, double *out,
                     void *stream);

@@ -18,7 +18,7 @@
 // fma), then rounded once.  The local combination is an exact 128-bit integer.
 //
 // One workgroup of 1024 threads per action; bins are dealt in chunks of 8, and the
-// walk stops where the weights have fallen below 1e-304.
+// walk stops where all further terms together are below 2^-120.
 #include "common.h"
 
 namespace cs {
@@ -188,14 +188,17 @@ __device__ __attribute__((always_inline)) inline void action_block(
   for (int k = 0; k < 4; ++k)  // constant indices after unrolling (p[3] unused below 3+1)
     sm.p[k] = k <= K ? dd_mul(dd_powi(sm.e, k), dd_powi(sm.q, K - k)) : dd{0.0, 0.0};
 
-  // The weights fall as (1-e)^m: past the bin where (1-e)^(m-K) < e^-700 (about
-  // 2^-1010) a term is at most 2^-1010 * 2^93 (bracket, m < 2^31) * 2^61 (count), and all
-  // of them together stay below 2^-820, so the walk stops there (near m = 6600 for
-  // e = 0.1) instead of covering all n - 1 bins.
+  // The weights fall as (1-e)^m.  All terms past a bin where (1-e)^(m-K) <= 2^-(190 + 4 log2 n)
+  // together stay below 2^-120: n of them, a bracket of at most 20 n^3 and counts below 2^64
+  // each.  Beside N >= 2, which the sum is subtracted from, that is below the double-double
+  // resolution (2^-104), so the walk stops there: near m = 1615 for e = 0.1 and n = 16384,
+  // where a cut at the smallest normal numbers (2^-1010) came at 6640 and an action of 16384
+  // points took three times as long.
   const double log_q = log1p(-eps);  // -inf for eps = 1: only the bins up to K
   int64_t walk = nb;                  // bins up to the cut-off (uniform)
   if (log_q < 0.0) {
-    const double cut = (double)K + 700.0 / -log_q + 1.0;
+    const double cut =
+        (double)K + 0.69314718055994531 * (190.0 + 4.0 * log2((double)n)) / -log_q + 1.0;
     if (cut < (double)walk) walk = (int64_t)cut;
   }
   // One pass: thread t takes the bins [t C, t C + C) of the walk, with C chosen so that
