@@ -134,29 +134,58 @@ __device__ inline bool later_precedes(const Pt<CS_MINK3_DIAMOND>& a,
 // ANDed there: a ballot of the AND would first turn it into a per-lane value and back
 // (two VALU instructions more per pair test).  fcmp predicate 4 is ordered less-than,
 // false for NaN like the C operator.
-template <int R>
+// APART: every a of the wave is strictly earlier than b (see block_apart), so the slabs
+// drop their compare of the times.
+template <bool APART, int R>
 __device__ inline uint64_t precedes_mask(const Pt<R>& a, const Pt<R>& b) {
   return __builtin_amdgcn_ballot_w64(later_precedes(a, b));
 }
-template <>
+template <bool APART>
 __device__ inline uint64_t precedes_mask(const Pt<CS_MINK2_DIAMOND>& a,
                                          const Pt<CS_MINK2_DIAMOND>& b) {
   return __builtin_amdgcn_fcmp(a.u, b.u, 4) & __builtin_amdgcn_fcmp(a.v, b.v, 4);
 }
-template <>
+template <bool APART>
 __device__ inline uint64_t precedes_mask(const Pt<CS_DS4_SLAB>& a, const Pt<CS_DS4_SLAB>& b) {
   double cd = __dadd_rn(__dmul_rn(a.c, b.c), __dmul_rn(a.s, b.s));
   double dot = __dadd_rn(__dmul_rn(a.n0, b.n0), __dmul_rn(a.n1, b.n1));
   dot = __dadd_rn(dot, __dmul_rn(a.n2, b.n2));
   dot = __dadd_rn(dot, __dmul_rn(a.n3, b.n3));
+  if constexpr (APART) return __builtin_amdgcn_fcmp(cd, dot, 4);
   return __builtin_amdgcn_fcmp(a.x, b.x, 4) & __builtin_amdgcn_fcmp(cd, dot, 4);
 }
-template <>
+template <bool APART>
 __device__ inline uint64_t precedes_mask(const Pt<CS_DS2_SLAB>& a, const Pt<CS_DS2_SLAB>& b) {
   const double pi = 3.141592653589793;
   double dth = fabs(__dsub_rn(a.th, b.th));
   dth = __dsub_rn(pi, fabs(__dsub_rn(pi, dth)));
+  if constexpr (APART) return __builtin_amdgcn_fcmp(dth, __dsub_rn(b.eta, a.eta), 4);
   return __builtin_amdgcn_fcmp(a.eta, b.eta, 4) & __builtin_amdgcn_fcmp(dth, __dsub_rn(b.eta, a.eta), 4);
+}
+
+// The slabs' time of a point.
+__device__ inline double time_of(const Pt<CS_DS4_SLAB>& p) { return p.x; }
+__device__ inline double time_of(const Pt<CS_DS2_SLAB>& p) { return p.eta; }
+template <int R>
+constexpr bool kSlab = R == CS_DS4_SLAB || R == CS_DS2_SLAB;
+
+// Whether all rows of the wave are strictly earlier than all columns (one per lane): true of
+// time-ordered blocks above the diagonal but for ties, and then one compare of the 13 (3+1)
+// or 7 (1+1) operations of a pair test is known (fp64 issue bounds these blocks; measured:
+// 3+1 builder and degrees at 30001 points 258 -> 247 us, the 1+1 pass at 4001 57.2 -> 56.5).
+// False when a time is NaN.
+template <int R, int RB>
+__device__ inline bool block_apart(const Pt<R> (&rows)[RB], const Pt<R>& col) {
+  double first = time_of(col);
+  bool ordered = first == first;
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    const double o = __shfl_xor(first, off);
+    first = o < first ? o : first;
+  }
+#pragma unroll
+  for (int r = 0; r < RB; ++r) ordered = ordered & (time_of(rows[r]) < first);
+  return __builtin_amdgcn_ballot_w64(!ordered) == 0;
 }
 
 // 2 w + (this lane's bit of the wave mask m): one add with m as the carry-in.
@@ -203,16 +232,10 @@ __device__ inline uint64_t wave_transpose64(uint64_t x) {
 template <int R>
 constexpr bool kScalarColumns = R == CS_MINK4_DIAMOND || R == CS_MINK3_DIAMOND;
 
-template <int R, bool FULL, int RB>
+template <int R, bool FULL, int RB, bool APART>
 __device__ __attribute__((always_inline)) inline void row_words(
     const double* __restrict__ coords, int64_t n, int64_t j0, const Pt<R> (&pi)[RB], Pt<R>* cols,
     uint64_t (&out)[RB]) {
-  if constexpr (!kScalarColumns<R>) {
-    const int lane = threadIdx.x & 63;
-    cols[lane] = load_pt(coords, n, j0 + lane < n ? j0 + lane : n - 1, (Pt<R>*)nullptr);
-    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): the wave's LDS writes have landed
-    __builtin_amdgcn_wave_barrier();
-  }
   uint32_t half[RB][2];
 #pragma unroll
   for (int h = 1; h >= 0; --h) {
@@ -226,12 +249,11 @@ __device__ __attribute__((always_inline)) inline void row_words(
       const Pt<R> q = kScalarColumns<R> ? load_pt(coords, n, j, (Pt<R>*)nullptr) : cols[32 * h + c];
 #pragma unroll
       for (int r = 0; r < RB; ++r)
-        w[r] = shift_in(w[r], precedes_mask(pi[r], q));
+        w[r] = shift_in(w[r], precedes_mask<APART>(pi[r], q));
     }
 #pragma unroll
     for (int r = 0; r < RB; ++r) half[r][h] = w[r];
   }
-  if constexpr (!kScalarColumns<R>) __builtin_amdgcn_wave_barrier();
 #pragma unroll
   for (int r = 0; r < RB; ++r) out[r] = ((uint64_t)half[r][1] << 32) | half[r][0];
 }
@@ -256,8 +278,19 @@ __device__ __attribute__((always_inline)) inline void build_block(
     pi[r] = load_pt(coords, n, i < n ? i : n - 1, (Pt<R>*)nullptr);
   }
   uint64_t rows[RB];
-  if (bj * 64 + 64 <= n) row_words<R, true, RB>(coords, n, bj * 64, pi, cols, rows);
-  else row_words<R, false, RB>(coords, n, bj * 64, pi, cols, rows);
+  const int64_t j0 = bj * 64;
+  bool apart = false;
+  if constexpr (!kScalarColumns<R>) {
+    const Pt<R> col = load_pt(coords, n, j0 + lane < n ? j0 + lane : n - 1, (Pt<R>*)nullptr);
+    cols[lane] = col;
+    if constexpr (kSlab<R>) apart = block_apart<R, RB>(pi, col);
+    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): the wave's LDS writes have landed
+    __builtin_amdgcn_wave_barrier();
+  }
+  if (j0 + 64 > n) row_words<R, false, RB, false>(coords, n, j0, pi, cols, rows);
+  else if (kSlab<R> && apart) row_words<R, true, RB, kSlab<R>>(coords, n, j0, pi, cols, rows);
+  else row_words<R, true, RB, false>(coords, n, j0, pi, cols, rows);
+  if constexpr (!kScalarColumns<R>) __builtin_amdgcn_wave_barrier();
   const int64_t j = bj * 64 + lane;
   const bool jv = j < n;
   const int64_t ncols = n - bj * 64;  // valid columns of the block (>= 1)
