@@ -1,7 +1,8 @@
 """Ensemble leg of bench.py: 256 independent 1+1 diamonds, N uniform in [512, 8192].
 
 One HIP-graph launch of the batch pipeline (sprinkle, matrix, counts, actions for
-every instance), with each of the three counters, against the same 256 instances as
+every instance), with each of the three counters (each counts by ranks where the tuner
+finds that faster than the counter's tiles), against the same 256 instances as
 separate per-instance calls of the single-instance entry points (int8 counter, and
 again with the fp4 counter).  All are timed with HIP events on one stream.
 """

@@ -16,8 +16,9 @@
 // build, rank tables, count (one persistent launch per configuration in use), action.
 //
 // Counting configuration per instance: by ranks (ranks.hip), the default, or the
-// counter's tiles for the instance's size bucket.  The candidates are, for the MFMA counters, 128x128 tiles with one or two
-// workgroups per CU and 256x256 tiles (one per CU); for the bitset counter, the dense
+// counter's tiles for the instance's size bucket.  The candidates are, for the MFMA
+// counters, 128x128 tiles with one or two workgroups per CU and 256x256 tiles (one per
+// CU); for the bitset counter, the dense
 // product on every tile or the related-pair tiles with two thresholds, two workgroups
 // per CU, and the related-pair tiles with one.  cs_autotune times every candidate on
 // the device per (counter, bucket) and stores the fastest in a JSON cache, one entry per

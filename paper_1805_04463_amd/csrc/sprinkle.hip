@@ -375,13 +375,12 @@ __global__ __launch_bounds__(kPlaceThreads) void k_bucket_place(
 
 // ---------------------------------------------------------------------------
 // Small sets: the time order by ranks.  Element g's place is the number of elements
-// before it in (key, index) order, the order the sort network produces; the place is
-// counted over every key and the coordinates are written straight there, which replaces
-// the sort and the gather by one launch.  Sixteen lanes share an element, each comparing
-// against every sixteenth key of a chunk staged in LDS (consecutive lanes read
-// consecutive words, so a wave's reads hit distinct banks); the partial counts are summed
-// by lane exchanges.  Each comparison is the order itself, key first and index on equal
-// keys, so equal keys need no separate pass.
+// before it in (key, index) order, the order of the buckets above 8192 points; the place is
+// counted over every key and the coordinates are written straight there, in one launch.
+// Sixteen lanes share an element, each comparing against every sixteenth key of a chunk
+// staged in LDS (consecutive lanes read consecutive words, so a wave's reads hit distinct
+// banks); the partial counts are summed by lane exchanges.  Each comparison is the order
+// itself, key first and index on equal keys, so equal keys need no separate pass.
 // ---------------------------------------------------------------------------
 constexpr int kRankThreads = 256;
 constexpr int kRankSplit = 16;                       // lanes per element
