@@ -167,7 +167,9 @@ cs_status cs_interval_histogram(const uint64_t *bits, int64_t n, int64_t ld_word
 cs_status cs_interval_histogram_noalloc(const uint64_t *bits, int64_t n, int64_t ld_words,
                                         int counter, uint64_t *hist, void *stream);
 
-/* Device workspace needed by cs_dalembertian, in bytes (0 for a bad n or counter). */
+/* Device workspace for cs_dalembertian, in bytes (0 for a bad n or counter): 256, and up to
+ * 32768 points (15000 for CS_COUNT_MFMA) 8 n more, which halve the length of its sums.  256
+ * bytes are enough for any n. */
 size_t cs_dalembertian_workspace_bytes(int64_t n, int counter);
 
 /*
@@ -185,7 +187,7 @@ size_t cs_dalembertian_workspace_bytes(int64_t n, int counter);
  *            tiles as cs_interval_histogram; the bitset counter gives CS_ERR_UNSUPPORTED).
  *   phi      device, n doubles (time-ordered like the points).
  *   out      device, n doubles, overwritten.
- *   workspace device, at least cs_dalembertian_workspace_bytes(n, counter) bytes.
+ *   workspace device, cs_dalembertian_workspace_bytes(n, counter) bytes, at least 256.
  * The sums over L_m(j) are accumulated in fp64 by atomic adds in an order that varies
  * between runs, so each out[j] is exact up to the rounding of a sum of its summands.
  * Same limits as cs_interval_histogram for the MFMA counters.

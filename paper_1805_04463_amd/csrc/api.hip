@@ -128,9 +128,9 @@ cs_status cs_dalembertian(const uint64_t* bits, int64_t n, int64_t ld_words_, in
   if (!(ell > 0.0) || !isfinite(ell)) return CS_ERR_INVALID_ARG;
   if (counter == CS_COUNT_MFMA_FP4 && n >= (int64_t)1 << 24) return CS_ERR_OVERFLOW;
   if (ld_words_ > kMaxMfmaLd) return CS_ERR_OVERFLOW;
-  if (workspace_bytes < field_ws_bytes(n, counter)) return CS_ERR_WORKSPACE;
+  if (workspace_bytes < kFieldWsMin) return CS_ERR_WORKSPACE;
   return launch_dalembertian(bits, n, ld_words_, counter, dim, ell, phi, out, workspace,
-                             as_stream(stream));
+                             workspace_bytes, as_stream(stream));
 }
 
 size_t cs_longest_chain_workspace_bytes(int64_t n, int64_t count) {

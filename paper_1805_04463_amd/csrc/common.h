@@ -130,10 +130,11 @@ cs_status launch_sprinkle(int region, double eta0, uint64_t seed, int64_t n, dou
 cs_status launch_causal_matrix(int region, const double* coords, int64_t n, uint64_t* bits,
                                int64_t ld, hipStream_t st);
 size_t histogram_ws_bytes(int64_t n, int counter);
+constexpr size_t kFieldWsMin = 256;  // what the d'Alembertian cannot do without
 size_t field_ws_bytes(int64_t n, int counter);
 long double prefactor_c3();  // (pi / (3 sqrt 2))^(2/3) / Gamma(5/3), the 2+1 constant
 cs_status launch_dalembertian(const uint64_t* bits, int64_t n, int64_t ld, int counter, int dim,
-                              double ell, const double* phi, double* out, void* ws, hipStream_t st);
+                              double ell, const double* phi, double* out, void* ws, size_t ws_bytes, hipStream_t st);
 cs_status launch_histogram(const uint64_t* bits, int64_t n, int64_t ld, int counter,
                            uint64_t* hist, void* ws, hipStream_t st);
 cs_status launch_action(const uint64_t* hist, int64_t n, int dim, double eps, double* out,

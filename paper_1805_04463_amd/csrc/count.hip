@@ -218,10 +218,15 @@ __device__ inline int64_t next_tile(unsigned int* counter, int* slot) {
   return *slot;
 }
 
-// Arguments of the d'Alembertian epilogue: out[j] accumulates sum_m c_m sum_{L_m(j)} phi(i).
+// Arguments of the d'Alembertian epilogue: out[j] accumulates sum_m c_m sum_{L_m(j)} phi(i);
+// 128-row tiles add the rows of every other tile to odd[j].  (Sums of half as many terms:
+// the mean error of the 3+1 operator at 5000 to 10007 points is 2.22e-16 of its mean, 2.44e-16
+// with all in out[j], 2.32e-16 with 256-row tiles, whose sums arrive in another order.  77 us
+// either way at 10007.)
 struct FieldArgs {
   const double* phi;
   double* out;
+  double* odd;                // out itself where the workspace has no room
   double c0, c1, c2, c3;      // c_m for pairs with m interior elements (0 past the last layer)
 };
 
@@ -841,12 +846,13 @@ __device__ __attribute__((always_inline)) inline bool mfma_tile(const TileArgs& 
       if (WM == 2 && wr == 1 && hsel == 0) cols[wc * (WM * 32) + nb * 32 + l32] = part[nb];
     }
     if constexpr (WM == 2) __syncthreads();
+    double* const to = WM == 2 && (I0 & BM) ? ta.f.odd : ta.f.out;
 #pragma unroll
     for (int nb = 0; nb < WM; ++nb) {
       const int c = wc * (WM * 32) + nb * 32 + l32;
       const double sum = WM == 2 && wr == 0 ? part[nb] + cols[c] : part[nb];
       const int64_t j = J0 + c;
-      if ((WM == 4 || wr == 0) && hsel == 0 && sum != 0.0 && j < n) atomicAdd(ta.f.out + j, sum);
+      if ((WM == 4 || wr == 0) && hsel == 0 && sum != 0.0 && j < n) atomicAdd(to + j, sum);
     }
   }
   return true;
@@ -1474,11 +1480,14 @@ cs_status launch_mfma(const uint64_t* bits, int64_t n, int64_t ld, uint64_t* his
   return CS_OK;
 }
 
-// out[j] = scale (out[j] - phi[j]): the bracket's -phi(j) and the prefactor K / ell^2.
-__global__ void k_field_finish(const double* __restrict__ phi, double* __restrict__ out, int64_t n,
-                               double scale) {
+// out[j] = scale (out[j] + odd[j] - phi[j]): the bracket's -phi(j) and the prefactor
+// K / ell^2.  odd: null if out holds the whole sum.
+__global__ void k_field_finish(const double* __restrict__ phi, const double* __restrict__ odd,
+                               double* __restrict__ out, int64_t n, double scale) {
   int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (j < n) out[j] = __dmul_rn(scale, __dsub_rn(out[j], phi[j]));
+  if (j >= n) return;
+  const double sum = odd ? __dadd_rn(out[j], odd[j]) : out[j];
+  out[j] = __dmul_rn(scale, __dsub_rn(sum, phi[j]));
 }
 
 cs_status launch_histogram(const uint64_t* bits, int64_t n, int64_t ld, int counter, uint64_t* hist,
@@ -1510,16 +1519,29 @@ cs_status launch_histogram(const uint64_t* bits, int64_t n, int64_t ld, int coun
   }
 }
 
-size_t field_ws_bytes(int64_t, int) { return 256; }
+// Whether the d'Alembertian takes 128-row tiles.
+static bool small_field(int64_t n, int counter) {
+  return n <= (counter == CS_COUNT_MFMA ? kSmallFieldInt8 : kSmallFieldFp4);
+}
+
+// The queue counters, and for 128-row tiles the second sums.
+size_t field_ws_bytes(int64_t n, int counter) {
+  return kFieldWsMin + (small_field(n, counter) ? 8 * (size_t)n : 0);
+}
 
 cs_status launch_dalembertian(const uint64_t* bits, int64_t n, int64_t ld, int counter, int dim,
-                              double ell, const double* phi, double* out, void* ws, hipStream_t st) {
+                              double ell, const double* phi, double* out, void* ws, size_t ws_bytes,
+                              hipStream_t st) {
   unsigned int* ctr = (unsigned int*)ws;
-  // out = +0.0, 8 queue counters
-  cs_status s = launch_zero2((uint64_t*)out, n, (uint64_t*)ws, 4, st);
+  const bool small = small_field(n, counter);
+  double* const odd = small && ws_bytes >= field_ws_bytes(n, counter)
+                          ? (double*)((char*)ws + kFieldWsMin) : nullptr;
+  // out = +0.0, 8 queue counters (the rest of their 256 bytes too before odd = +0.0)
+  cs_status s = launch_zero2((uint64_t*)out, n, (uint64_t*)ws,
+                             odd ? (int64_t)(kFieldWsMin / 8) + n : 4, st);
   if (s != CS_OK) return s;
   // Eqs. b2d_local, b3d_local, b4d_local: K / ell^2 [-phi(j) + sum_m c_m sum_{L_m(j)} phi(i)].
-  FieldArgs f{phi, out, 0.0, 0.0, 0.0, 0.0};
+  FieldArgs f{phi, out, odd ? odd : out, 0.0, 0.0, 0.0, 0.0};
   double K;
   if (dim == 2) {
     K = 2.0;
@@ -1532,13 +1554,13 @@ cs_status launch_dalembertian(const uint64_t* bits, int64_t n, int64_t ld, int c
     f.c0 = 1.0; f.c1 = -9.0; f.c2 = 16.0; f.c3 = -8.0;
   }
   if (counter == CS_COUNT_MFMA)
-    s = n <= kSmallFieldInt8 ? launch_mfma<2, false, 1, 1, true>(bits, n, ld, nullptr, ctr, st, f)
-                             : launch_mfma<4, false, 1, 1, true>(bits, n, ld, nullptr, ctr, st, f);
+    s = small ? launch_mfma<2, false, 1, 1, true>(bits, n, ld, nullptr, ctr, st, f)
+              : launch_mfma<4, false, 1, 1, true>(bits, n, ld, nullptr, ctr, st, f);
   else
-    s = n <= kSmallFieldFp4 ? launch_mfma<2, true, 1, 1, true>(bits, n, ld, nullptr, ctr, st, f)
-                            : launch_mfma<4, true, 1, 1, true>(bits, n, ld, nullptr, ctr, st, f);
+    s = small ? launch_mfma<2, true, 1, 1, true>(bits, n, ld, nullptr, ctr, st, f)
+              : launch_mfma<4, true, 1, 1, true>(bits, n, ld, nullptr, ctr, st, f);
   if (s != CS_OK) return s;
-  hipLaunchKernelGGL(k_field_finish, dim3((unsigned)ceil_div(n, 256)), dim3(256), 0, st, phi, out, n,
+  hipLaunchKernelGGL(k_field_finish, dim3((unsigned)ceil_div(n, 256)), dim3(256), 0, st, phi, odd, out, n,
                      K / (ell * ell));
   CS_LAUNCH_CHECK();
   return CS_OK;

@@ -53,3 +53,22 @@ def test_dalembertian_large_total_order(cs, n):  # noqa: F811
     want = np.full(n, -2.0)
     want[:3] = [-2.0, 2.0, -6.0]
     assert np.array_equal(got, want)
+
+
+@pytest.mark.parametrize("counter", [1, 2], ids=["mfma", "mfma_fp4"])
+@pytest.mark.parametrize("n", [2, 128, 129, 4100, 15000, 15001, 32768, 32769])
+def test_dalembertian_workspaces(cs, n, counter):  # noqa: F811
+    """The smallest workspace (one accumulator per element) and the queried one (a second,
+    with whatever it held before) give the same bits for whole phi and coefficients, whose
+    sums are exact in any order; one byte less than the smallest is refused."""
+    b = cs.cs_causal_matrix(W.MINK4_DIAMOND, cs.cs_sprinkle(W.MINK4_DIAMOND, n, n))
+    g = torch.Generator(device="cuda").manual_seed(n)
+    phi = torch.randint(-8, 9, (n,), device="cuda", generator=g).double()
+    small = torch.full((256,), 255, dtype=torch.uint8, device="cuda")
+    full = torch.full((cs.lib().cs_dalembertian_workspace_bytes(n, counter),), 255,
+                      dtype=torch.uint8, device="cuda")
+    one = cs.cs_dalembertian(b, n, 4, 1.0, phi, counter=counter, workspace=small)
+    two = cs.cs_dalembertian(b, n, 4, 1.0, phi, counter=counter, workspace=full)
+    assert torch.equal(one, two)
+    with pytest.raises(RuntimeError):
+        cs.cs_dalembertian(b, n, 4, 1.0, phi, counter=counter, workspace=small[:255])
