@@ -837,9 +837,11 @@ __device__ __attribute__((always_inline)) inline bool mfma_tile(const TileArgs& 
         }
       }
     }
-    // 128-row tiles: the two wave rows meet in LDS (the ring is free), so that a column
-    // takes one addition per 128 rows with either tile size.
-    double* const cols = (double*)ring;
+    // 128-row tiles: the two wave rows meet in LDS, so that a column takes one addition per
+    // 128 rows with either tile size.  The sums have words of their own, after the
+    // coefficients: a wave has waited for its own requests past the last stage, but until
+    // the next barrier another wave's may still write zeros to the ring.
+    double* const cols = phis + BM + 8;
 #pragma unroll
     for (int nb = 0; nb < WM; ++nb) {
       part[nb] += __shfl_xor(part[nb], 32);
@@ -1236,7 +1238,8 @@ struct MfmaLds {
   uint32_t ring[MRing<BM>::value * 2 * BM * kMStageU32] __attribute__((aligned(16)));
   uint32_t rel[BM == 128 ? 1 : BM * BM / 32];  // relation bits of the tile's pairs (i < j);
                                               // 128-row tiles keep theirs in registers
-  double phis[EPI == 1 ? BM + 8 : 1];  // phi of the tile's rows, then c_0 .. c_3, 0 (d'Alembertian)
+  // d'Alembertian: phi of the tile's rows; c_0 .. c_3, 0; the lower wave row's column sums
+  double phis[EPI == 1 ? BM + 8 + (BM == 128 ? BM : 0) : 1];
   uint32_t hist[HB + 64];      // bins, then one spare word per lane (never flushed)
   uint32_t maxbin;
   int slot;
