@@ -206,13 +206,13 @@ __device__ __forceinline__ int64_t first_witness(const uint64_t* __restrict__ ro
   return q < 0 ? -1 : q * kWave + 63 - __builtin_clzll(hit);
 }
 
-// Round t for the 64 elements of one listed word.  R: the members (read only); R_next: the
-// members without this round's minimal elements.
+// Round t for the 64 elements of each of the `active` listed words, a workgroup per word.  R:
+// the members (read only); R_next: the members without this round's minimal elements.
 template <int THREADS>
 __global__ __launch_bounds__(THREADS, 8) void k_chain_round(
     const uint64_t* __restrict__ bits, int64_t n, int64_t ld, int64_t W,
-    const uint64_t* __restrict__ list, const uint64_t* __restrict__ R, uint64_t* __restrict__ R_next,
-    int32_t* __restrict__ wit, int32_t* __restrict__ height, const int32_t* __restrict__ low,
+    const uint64_t* __restrict__ list, int64_t active, const uint64_t* __restrict__ R,
+    uint64_t* __restrict__ R_next, int32_t* __restrict__ wit, int32_t* __restrict__ height, const int32_t* __restrict__ low,
     int32_t* __restrict__ low_next, int32_t t) {
   constexpr int kWaves = THREADS / kWave;
   __shared__ int32_t todo[kWave], top_of[kWave];  // element of the word; word to resume at
@@ -221,8 +221,10 @@ __global__ __launch_bounds__(THREADS, 8) void k_chain_round(
   __shared__ int ntodo;
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const uint64_t entry = list[blockIdx.x];
-  if (entry == kNoWord) return;  // the whole workgroup
+  const int64_t group = group_index();
+  if (group >= active) return;  // the whole workgroup
+  const uint64_t entry = list[group];
+  if (entry == kNoWord) return;
   const int s = (int)(entry >> 32);
   const int64_t w = (int64_t)((uint32_t)entry >> 1);
   const uint64_t* r = R + (int64_t)s * W;
@@ -634,13 +636,13 @@ cs_status launch_longest_chain(const uint64_t* bits, int64_t n, int64_t ld, cons
     batch = end - t;
     for (; t < end; ++t) {
       const int c = (int)(t & 1);
-      const dim3 grid((unsigned)now.active);
+      const dim3 grid = grid_rows((int64_t)now.active);
       if (now.active <= kWideWords)
-        hipLaunchKernelGGL(k_chain_round<1024>, grid, dim3(1024), 0, st, bits, n, ld, W, L.list, L.X[c],
-                           L.X[c ^ 1], L.wit, h, L.low[c ^ 1], L.low[c], (int32_t)t);
+        hipLaunchKernelGGL(k_chain_round<1024>, grid, dim3(1024), 0, st, bits, n, ld, W, L.list,
+                           (int64_t)now.active, L.X[c], L.X[c ^ 1], L.wit, h, L.low[c ^ 1], L.low[c], (int32_t)t);
       else
-        hipLaunchKernelGGL(k_chain_round<256>, grid, dim3(256), 0, st, bits, n, ld, W, L.list, L.X[c],
-                           L.X[c ^ 1], L.wit, h, L.low[c ^ 1], L.low[c], (int32_t)t);
+        hipLaunchKernelGGL(k_chain_round<256>, grid, dim3(256), 0, st, bits, n, ld, W, L.list,
+                           (int64_t)now.active, L.X[c], L.X[c ^ 1], L.wit, h, L.low[c ^ 1], L.low[c], (int32_t)t);
       CS_LAUNCH_CHECK();
     }
   }

@@ -59,6 +59,15 @@ inline int64_t ld_words(int64_t n) { return ((n + 511) / 512) * 8; }
 __host__ __device__ inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
+// Grid of `groups` workgroups in rows of at most 2^21: a launch holds less than 2^32 work-items
+// along x, a row here at most 2^31.  The kernel's workgroup is group_index(), which in the last
+// of several rows can be `groups` or more.
+inline dim3 grid_rows(int64_t groups) {
+  constexpr int64_t kRow = (int64_t)1 << 21;
+  return groups <= kRow ? dim3((unsigned)groups) : dim3((unsigned)kRow, (unsigned)ceil_div(groups, kRow));
+}
+__device__ inline int64_t group_index() { return (int64_t)blockIdx.y * gridDim.x + blockIdx.x; }
+
 // Coordinate planes per region (2, 4, 7).
 inline int coord_planes(int region) {
   switch (region) {

@@ -1,0 +1,68 @@
+"""Launch shapes of the library's host code at sizes that no test can run: the built objects
+are linked with a recording HIP runtime (tests/native/recording_hip.cpp) that refuses a launch
+as the real one does, 2^32 work-items or more along x among the reasons, and runs nothing."""
+import ctypes
+import os
+import subprocess
+
+import pytest
+
+from paper_1805_04463_amd import build as hip_build
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+
+@pytest.fixture(scope="module")
+def rec(tmp_path_factory):
+    objects = [os.path.join(hip_build.BUILD, os.path.splitext(s)[0] + ".o") for s in hip_build.SOURCES]
+    if not all(os.path.exists(o) for o in objects):
+        hip_build.build()
+    path = str(tmp_path_factory.mktemp("rec") / "librecorded.so")
+    subprocess.run(["g++", "-O1", "-std=c++17", "-fPIC", "-shared", "-Wl,-Bsymbolic",
+                    os.path.join(HERE, "native", "recording_hip.cpp"), *objects, "-o", path], check=True)
+    L = ctypes.CDLL(path)
+    i64, p, sz = ctypes.c_int64, ctypes.c_void_p, ctypes.c_size_t
+    L.rec_kernel.restype = ctypes.c_char_p
+    L.rec_reply.argtypes = [p, sz]
+    L.cs_longest_chain.argtypes = [p, i64, i64, p, p, i64, p, p, p, sz, p]
+    return L
+
+
+def launches(L, part):
+    """(grid x, grid y, block x) of the recorded launches of kernels named *part*."""
+    out = []
+    for i in range(L.rec_count()):
+        if part in L.rec_kernel(i).decode():
+            d = (ctypes.c_uint32 * 6)()
+            L.rec_dims(i, d)
+            assert (d[2], d[4], d[5]) == (1, 1, 1)
+            out.append((d[0], d[1], d[3]))
+    return out
+
+
+ANY = 256          # a device pointer; nothing is read
+ROOM = 1 << 60     # workspace bytes
+
+
+@pytest.mark.parametrize("n,count,active", [
+    (131072, 1, 2048), (131072, 2, 4096), (131072, 3, 2049), (131072, 8192, 2**24 - 1), (131072, 8192, 2**24),
+    (32768, 32768, 2**24), (20000, 65535, 313 * 65535)])
+def test_chain_rounds_over_many_words(rec, n, count, active):
+    """A launch per round over `active` words: at least a workgroup for each, less than one
+    grid row too many."""
+    rec.rec_reset()
+    survey = (ctypes.c_uint64 * 4)(64 * active, n, active, 0)
+    ended = (ctypes.c_uint64 * 8)(64 * active, n, active, 0, 0, 0, 0, 0)
+    if (n + 63) // 64 * count > 4096:  # else the first batch covers every word, unseen
+        rec.rec_reply(survey, 32)
+    rec.rec_reply(ended, 64)
+    ends = (ctypes.c_int64 * (2 * count))(*([-1] * count + [n] * count))
+    at = ctypes.addressof(ends)
+    rc = rec.cs_longest_chain(ANY, n, n, at, at + 8 * count, count, ANY, ANY, ANY, ROOM, None)
+    assert rc == 0
+    rounds = launches(rec, "k_chain_round")
+    assert len(rounds) == 8
+    for x, y, threads in rounds:
+        assert x * threads < 2**32 and y <= 65535
+        assert 0 <= x * y - active < x
+        assert y == 1 or active * threads >= 2**31  # one row wherever it does
