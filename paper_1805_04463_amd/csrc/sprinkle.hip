@@ -338,11 +338,13 @@ __global__ void k_bucket_scatter(int64_t n, const uint32_t* __restrict__ bkt_of,
 
 __global__ __launch_bounds__(kPlaceThreads) void k_bucket_place(
     const uint64_t* __restrict__ keys, const uint32_t* __restrict__ slots,
-    const uint64_t* __restrict__ start, const double* __restrict__ raw, int planes, int64_t n,
-    double* __restrict__ coords) {
+    const uint64_t* __restrict__ start, int64_t B, const double* __restrict__ raw, int planes,
+    int64_t n, double* __restrict__ coords) {
   __shared__ uint64_t sk[kBucketCap];
   __shared__ uint32_t sg[kBucketCap];
-  const int64_t lo = (int64_t)start[blockIdx.x], m = (int64_t)start[blockIdx.x + 1] - lo;
+  const int64_t b = group_index();
+  if (b >= B) return;  // the whole workgroup
+  const int64_t lo = (int64_t)start[b], m = (int64_t)start[b + 1] - lo;
   const bool lds = m <= kBucketCap;
   if (lds) {
     for (int i = threadIdx.x; i < m; i += kPlaceThreads) {
@@ -690,8 +692,8 @@ cs_status launch_sprinkle(int region, double eta0, uint64_t seed, int64_t n, dou
   hipLaunchKernelGGL(k_bucket_scatter, dim3(grid), dim3(kBlock), 0, st, n, w.bkt_of, w.arrive,
                      w.bkt_start, w.slots);
   CS_LAUNCH_CHECK();
-  hipLaunchKernelGGL(k_bucket_place, dim3((unsigned)B), dim3(kPlaceThreads), 0, st, w.keys, w.slots,
-                     w.bkt_start, w.raw, planes, n, coords);
+  hipLaunchKernelGGL(k_bucket_place, grid_rows(B), dim3(kPlaceThreads), 0, st, w.keys, w.slots,
+                     w.bkt_start, B, w.raw, planes, n, coords);
   CS_LAUNCH_CHECK();
   return CS_OK;
 }

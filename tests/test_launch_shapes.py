@@ -24,6 +24,7 @@ def rec(tmp_path_factory):
     i64, p, sz = ctypes.c_int64, ctypes.c_void_p, ctypes.c_size_t
     L.rec_kernel.restype = ctypes.c_char_p
     L.rec_reply.argtypes = [p, sz]
+    L.cs_sprinkle.argtypes = [ctypes.c_int, ctypes.c_double, ctypes.c_uint64, i64, p, p, sz, p]
     L.cs_longest_chain.argtypes = [p, i64, i64, p, p, i64, p, p, p, sz, p]
     return L
 
@@ -66,3 +67,20 @@ def test_chain_rounds_over_many_words(rec, n, count, active):
         assert x * threads < 2**32 and y <= 65535
         assert 0 <= x * y - active < x
         assert y == 1 or active * threads >= 2**31  # one row wherever it does
+
+
+@pytest.mark.parametrize("n", [8193, 131072, 2**27, 2**27 + 1, 2**29 - 64, 2**29, 2**29 + 1, 2**31 - 1])
+@pytest.mark.parametrize("region", range(5))
+def test_bucket_placement_of_many_points(rec, region, n):
+    """A workgroup for each 64 points.  (The candidates of the 3+1 and 2+1 diamonds, about eight and
+    four per point, are a work-item each: their own launch is refused above these sizes, as it
+    always was.)"""
+    if n > {1: 2**29 + 1, 4: 2**30}.get(region, n):
+        return
+    rec.rec_reset()
+    assert rec.cs_sprinkle(region, 1.2, 7, n, ANY, ANY, ROOM, None) == 0
+    (x, y, threads), = launches(rec, "k_bucket_place")
+    buckets = (n + 63) // 64
+    assert x * threads < 2**32 and y <= 65535
+    assert 0 <= x * y - buckets < x
+    assert y == 1 or buckets * threads >= 2**30
