@@ -168,8 +168,9 @@ cs_status cs_interval_histogram_noalloc(const uint64_t *bits, int64_t n, int64_t
                                         int counter, uint64_t *hist, void *stream);
 
 /* Device workspace for cs_dalembertian, in bytes (0 for a bad n or counter): 256, and up to
- * 32768 points (15000 for CS_COUNT_MFMA) 8 n more, which halve the length of its sums.  256
- * bytes are enough for any n. */
+ * 32768 points (15000 for CS_COUNT_MFMA) 8 n more, for the second sums of its 128-row tiles.
+ * 256 bytes are enough for any n: with less than the above, more than 4096 points take 256-row
+ * tiles, which are slower and need none. */
 size_t cs_dalembertian_workspace_bytes(int64_t n, int counter);
 
 /*

@@ -65,6 +65,7 @@ constexpr int kBinsSingle = 12288;      // LDS histogram bins, single instance (
 constexpr int kBinsSmall = 11776;  // 2 x 80 KiB of LDS per CU
 constexpr int64_t kSmallHistFp4 = 24000, kSmallHistInt8 = kBinsSmall + 1;
 constexpr int64_t kSmallFieldFp4 = 32768, kSmallFieldInt8 = 15000;
+constexpr int64_t kOneSumField = 4096;  // 128-row tiles with one sum per element
 constexpr int64_t kPerTile = 65 * 66 / 2;
 constexpr int kBinsBatch = 8192;        // LDS histogram bins, ensembles (n <= 8192)
 
@@ -219,10 +220,12 @@ __device__ inline int64_t next_tile(unsigned int* counter, int* slot) {
 }
 
 // Arguments of the d'Alembertian epilogue: out[j] accumulates sum_m c_m sum_{L_m(j)} phi(i);
-// 128-row tiles add the rows of every other tile to odd[j].  (Sums of half as many terms:
-// the mean error of the 3+1 operator at 5000 to 10007 points is 2.22e-16 of its mean, 2.44e-16
-// with all in out[j], 2.32e-16 with 256-row tiles, whose sums arrive in another order.  77 us
-// either way at 10007.)
+// 128-row tiles add the rows of every other tile to odd[j], sums of half as many terms.  Mean
+// error, of the operator's mean, against extended precision: 3+1 at 10007 points 2.3e-16, with
+// all in out[j] 2.45 to 2.7e-16, with 256-row tiles 2.5 to 2.6e-16; at 32000 points 3.0e-16
+// (fp4) against the 256-row tiles' 3.6e-16.  At 10007 points 77 us with or without.  So 128-row
+// tiles go without the second sums up to 4096 points only, where that costs little (2.1e-16
+// against 2.0e-16).
 struct FieldArgs {
   const double* phi;
   double* out;
@@ -1522,7 +1525,7 @@ cs_status launch_histogram(const uint64_t* bits, int64_t n, int64_t ld, int coun
   }
 }
 
-// Whether the d'Alembertian takes 128-row tiles.
+// Whether the d'Alembertian takes 128-row tiles, given room for its second sums.
 static bool small_field(int64_t n, int counter) {
   return n <= (counter == CS_COUNT_MFMA ? kSmallFieldInt8 : kSmallFieldFp4);
 }
@@ -1536,9 +1539,10 @@ cs_status launch_dalembertian(const uint64_t* bits, int64_t n, int64_t ld, int c
                               double ell, const double* phi, double* out, void* ws, size_t ws_bytes,
                               hipStream_t st) {
   unsigned int* ctr = (unsigned int*)ws;
-  const bool small = small_field(n, counter);
-  double* const odd = small && ws_bytes >= field_ws_bytes(n, counter)
-                          ? (double*)((char*)ws + kFieldWsMin) : nullptr;
+  // Without that room, 128-row tiles up to kOneSumField points only.
+  const bool room = ws_bytes >= field_ws_bytes(n, counter);
+  const bool small = small_field(n, counter) && (room || n <= kOneSumField);
+  double* const odd = small && room ? (double*)((char*)ws + kFieldWsMin) : nullptr;
   // out = +0.0, 8 queue counters (the rest of their 256 bytes too before odd = +0.0)
   cs_status s = launch_zero2((uint64_t*)out, n, (uint64_t*)ws,
                              odd ? (int64_t)(kFieldWsMin / 8) + n : 4, st);

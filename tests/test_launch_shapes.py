@@ -25,6 +25,9 @@ def rec(tmp_path_factory):
     L.rec_kernel.restype = ctypes.c_char_p
     L.rec_reply.argtypes = [p, sz]
     L.cs_sprinkle.argtypes = [ctypes.c_int, ctypes.c_double, ctypes.c_uint64, i64, p, p, sz, p]
+    L.cs_dalembertian.argtypes = [p, i64, i64, ctypes.c_int, ctypes.c_double, ctypes.c_int, p, p, p, sz, p]
+    L.cs_dalembertian_workspace_bytes.argtypes = [i64, ctypes.c_int]
+    L.cs_dalembertian_workspace_bytes.restype = sz
     L.cs_longest_chain.argtypes = [p, i64, i64, p, p, i64, p, p, p, sz, p]
     return L
 
@@ -84,3 +87,24 @@ def test_bucket_placement_of_many_points(rec, region, n):
     assert x * threads < 2**32 and y <= 65535
     assert 0 <= x * y - buckets < x
     assert y == 1 or buckets * threads >= 2**30
+
+
+@pytest.mark.parametrize("counter,last", [(1, 15000), (2, 32768)], ids=["mfma", "mfma_fp4"])
+@pytest.mark.parametrize("n", [700, 4096, 4097, 10007, 15000, 15001, 32768, 32769])
+def test_dalembertian_tiles_follow_the_workspace(rec, n, counter, last):
+    """128-row tiles need room for their second sums above 4096 points: with the 256 bytes that
+    are always enough, larger sets keep the 256-row tiles, whose rounding error is smaller than
+    that of 128-row tiles with one sum per element."""
+    full = rec.cs_dalembertian_workspace_bytes(n, counter)
+    assert full == 256 + (8 * n if n <= last else 0)
+    for room in (256, full - 1, full):
+        if room < 256:
+            continue
+        rec.rec_reset()
+        assert rec.cs_dalembertian(ANY, n, 1 << 10, 4, 1.0, counter, ANY, ANY, ANY, room, None) == 0
+        small = n <= 4096 or (n <= last and room == full)
+        tiles = -(-n // (128 if small else 256))
+        tiles = tiles * (tiles + 1) // 2
+        assert len(launches(rec, "k_count_mfmaILi2E" if small else "k_count_mfmaILi4E")) == 1
+        (x, y, threads), = launches(rec, "k_count_mfma")
+        assert (x, y, threads) == (tiles if small else min(tiles, 256), 1, 256)
