@@ -55,6 +55,25 @@ __device__ inline uint64_t order_bits(double x) {
   return (b >> 63) ? ~b : (b | 0x8000000000000000ull);
 }
 
+// Bucket in [0, B) (or past it, for the caller to clamp) of point g of n in a slab whose time x
+// = tan(eta) lies in [-X, X]: monotone in (order_bits(x), g).  In slabs below 2^-900 the quotient
+// B / 2X can overflow, and few different times may be representable: there the times are
+// counted in steps of the smallest double, two to spare at each end for the rounding of the
+// samplers and one from -0 to 0, and points of equal time are spread by their index, so that
+// no bucket holds them all.
+__host__ __device__ inline uint64_t bucket_of_time(double x, double X, uint64_t g, uint64_t n,
+                                                   uint64_t B) {
+  double b;
+  if (X >= 0x1p-900) {
+    b = (x + X) * ((double)B / (2.0 * X));
+  } else {
+    const double at = ldexp(x, 1074) + ldexp(X, 1074) + (__builtin_signbit(x) ? 2.0 : 3.0);
+    const double steps = 2.0 * ldexp(X, 1074) + 6.0;
+    b = (at + (double)g / (double)n) * ((double)B / steps);
+  }
+  return b > 0.0 ? (uint64_t)b : 0ull;
+}
+
 inline int64_t ld_words(int64_t n) { return ((n + 511) / 512) * 8; }
 __host__ __device__ inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }

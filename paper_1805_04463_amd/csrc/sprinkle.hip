@@ -15,9 +15,10 @@ namespace cs {
 namespace {
 
 constexpr int kBlock = 256;
-constexpr int kBucketMean = 64;     // points per bucket on average; at most four times as many
-                                    // expected anywhere (the densities below)
-constexpr int kBucketCap = 2048;    // points of a bucket placed through LDS
+constexpr int kBucketMean = 64;     // points per bucket on average; at most five times as many
+                                    // expected anywhere (the densities below; the thinnest slabs)
+constexpr int kBucketCap = 2048;    // points of a bucket placed through LDS: six times the most
+                                    // expected, 96 standard deviations above
 constexpr int kBucketPad = 16;      // counters 64 bytes apart: adds to one line queue up (30001
                                     // points of the 3+1 diamond: 45 us with counters side by side)
 constexpr int kPlaceThreads = 512;
@@ -89,9 +90,9 @@ size_t layout(int region, int64_t n, void* base, SprinkleWs* w) {
 
 // Where the samplers put a point's time key and, for sets that are placed by buckets (B >
 // 0), its bucket: a monotone map of the key onto [0, B), under which no bucket holds more
-// than four times the mean.  (Densities of the key: 2 at the middle of the u + v triangle,
+// than five times the mean.  (Densities of the key: 2 at the middle of the u + v triangle,
 // 3 and 4 at the waists of the 2+1 and 3+1 diamonds, 1 in tan(eta) on the 1+1 slab, up to
-// 3 at the ends of the 3+1 slab.)
+// 3 at the ends of the 3+1 slab, up to 5 in slabs a few steps of the smallest double wide.)
 struct KeyOut {
   uint64_t* keys;
   uint32_t *bkt_of, *arrive, *bkt_count;
@@ -104,13 +105,9 @@ __device__ inline void put_key(const KeyOut& o, int64_t g, uint64_t key, uint64_
   o.bkt_of[g] = b;
   o.arrive[g] = atomicAdd(&o.bkt_count[(uint64_t)b * kBucketPad], 1u);
 }
-// Integer keys of `bits` bits; real keys on [-X, X].
+// Integer keys of `bits` bits; the slabs' real keys take bucket_of_time.
 __device__ inline uint64_t bucket_of_bits(uint64_t key, int bits, uint64_t B) {
   return __umul64hi(key << (64 - bits), B);
-}
-__device__ inline uint64_t bucket_of_real(double x, double X, uint64_t B) {
-  const double b = (x + X) * ((double)B / (2.0 * X));
-  return b > 0.0 ? (uint64_t)b : 0ull;
 }
 
 // ---------------------------------------------------------------------------
@@ -278,7 +275,7 @@ __global__ void k_sprinkle_ds2(uint64_t skey, double X, int64_t n, double* __res
   raw[g] = x;
   raw[n + g] = atan(x);
   raw[2 * n + g] = __dmul_rn(two_pi, w);
-  put_key(out, g, order_bits(x), bucket_of_real(x, X, out.B));
+  put_key(out, g, order_bits(x), bucket_of_time(x, X, (uint64_t)g, (uint64_t)n, out.B));
 }
 
 // ---------------------------------------------------------------------------
@@ -318,7 +315,7 @@ __global__ void k_sprinkle_ds4(uint64_t skey_t, uint64_t skey_s, double X, int64
   raw[4 * n + g] = __ddiv_rn(a1, r);
   raw[5 * n + g] = __ddiv_rn(a2, r);
   raw[6 * n + g] = __ddiv_rn(a3, r);
-  put_key(out, g, order_bits(x), bucket_of_real(x, X, out.B));
+  put_key(out, g, order_bits(x), bucket_of_time(x, X, (uint64_t)g, (uint64_t)n, out.B));
 }
 
 // ---------------------------------------------------------------------------
