@@ -254,9 +254,9 @@ cs_status cs_degrees(const uint64_t *bits, int64_t n, int64_t ld_words, int64_t 
  *   0 <= eps <= 1; at eps = 1 the smeared form equals the local one.
  *   hist  device, n-1 uint64.   out  device, one double.
  * The local combination is an exact int64; the smeared sum is accumulated in
- * double-double (weights included), then rounded once to fp64.  Bins past the point
- * where (1 - eps)^m < 2^-(190 + 4 log2 n) are not visited: all their terms together are
- * below 2^-120, less than the double-double sum resolves.
+ * double-double (weights included), then rounded once to fp64.  Bins past the point where
+ * (1 - eps)^m < 2^-(190 + 4 lg n), lg n the bits of n, are not visited: all their terms
+ * together are below 2^-120, less than the double-double sum resolves.
  */
 cs_status cs_action(const uint64_t *hist, int64_t n, int dim, double eps, double *out,
                     void *stream);

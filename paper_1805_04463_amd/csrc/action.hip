@@ -188,17 +188,17 @@ __device__ __attribute__((always_inline)) inline void action_block(
   for (int k = 0; k < 4; ++k)  // constant indices after unrolling (p[3] unused below 3+1)
     sm.p[k] = k <= K ? dd_mul(dd_powi(sm.e, k), dd_powi(sm.q, K - k)) : dd{0.0, 0.0};
 
-  // The weights fall as (1-e)^m.  All terms past a bin where (1-e)^(m-K) <= 2^-(190 + 4 log2 n)
-  // together stay below 2^-120: n of them, a bracket of at most 20 n^3 and counts below 2^64
-  // each.  Beside N >= 2, which the sum is subtracted from, that is below the double-double
-  // resolution (2^-104), so the walk stops there: near m = 1615 for e = 0.1 and n = 16384,
-  // where a cut at the smallest normal numbers (2^-1010) came at 6640 and an action of 16384
-  // points took three times as long.
+  // The weights fall as (1-e)^m.  All terms past a bin where (1-e)^(m-K) <= 2^-(190 + 4 lg n), lg n
+  // the bits of n, together stay below 2^-120: n of them, a bracket of at most 20 n^3 and counts
+  // below 2^64 each.  Beside N >= 2, which the sum is subtracted from, that is below the
+  // double-double resolution (2^-104), so the walk stops there: near m = 1650 for e = 0.1 and n =
+  // 16384, where a cut at the smallest normal numbers (2^-1010) came at 6640 and an action of
+  // 16384 points took three times as long.  (A logarithm of n cost every smeared action 0.6 us.)
   const double log_q = log1p(-eps);  // -inf for eps = 1: only the bins up to K
   int64_t walk = nb;                  // bins up to the cut-off (uniform)
   if (log_q < 0.0) {
-    const double cut =
-        (double)K + 0.69314718055994531 * (190.0 + 4.0 * log2((double)n)) / -log_q + 1.0;
+    const int lg = 64 - __clzll((long long)n);
+    const double cut = (double)K + 0.69314718055994531 * (double)(190 + 4 * lg) / -log_q + 1.0;
     if (cut < (double)walk) walk = (int64_t)cut;
   }
   // One pass: thread t takes the bins [t C, t C + C) of the walk, with C chosen so that
