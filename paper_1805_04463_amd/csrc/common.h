@@ -78,6 +78,22 @@ inline int64_t ld_words(int64_t n) { return ((n + 511) / 512) * 8; }
 __host__ __device__ inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
+// A step s coprime to m near the golden section of m: t -> t s mod m goes through 0 .. m-1 with
+// consecutive t far apart.
+inline int64_t scatter_step(int64_t m) {
+  auto coprime = [](int64_t a, int64_t b) {
+    while (b) {
+      const int64_t r = a % b;
+      a = b;
+      b = r;
+    }
+    return a == 1;
+  };
+  int64_t s = (int64_t)(0.6180339887 * (double)m) | 1;
+  while (!coprime(s, m)) s += 2;
+  return s;
+}
+
 // Grid of `groups` workgroups in rows of at most 2^21: a launch holds less than 2^32 work-items
 // along x, a row here at most 2^31.  The kernel's workgroup is group_index(), which in the last
 // of several rows can be `groups` or more.
