@@ -46,10 +46,21 @@ namespace {
 
 constexpr int kChainBlock = 256;  // four wavefronts
 constexpr int kChainWaves = kChainBlock / kWave;
-constexpr int kPairThreads = 1024;   // of k_chain_pair
-constexpr int kPairWaves = kPairThreads / kWave;
 constexpr int kScanDepth = 4;        // 64-word loads in flight per wave in a long scan step
-constexpr unsigned long long kWideWords = 2048;  // 16 wavefronts per word up to here, then four
+// Threads for each word of a round over `active` words of pairs of W words.  Few words take many
+// wavefronts each, as long as the workgroups are resident together (512 of 1024 threads), or
+// four times as many where rows are long and their scans outweigh the test; many short rows
+// take two wavefronts, as one does the test.  Calls, us, with 1024 / 512 / 256 / 128 threads: the
+// whole 3+1 order of 131072 elements (2048 words) 896 / 991 / 1379 / 2289, eight of 16384 (2048
+// words) 429 / 390 / 413 / 513, one of 4096 (64 words) 203 / 217 / 238 / 294, 100 of 500 (800
+// words) 164 / 149 / 157 / 172, seven of 60000 (6566 words) 1218 / 1000 / 890 / 1085; 40000
+// random pairs of a 1+1 diamond of 500 (8 words a pair) 3545 / 2367 / 1585 / 1353, of 65 (2)
+// 993 / 691 / 516 / 473.
+int round_threads(int64_t W, unsigned long long active) {
+  if (active <= 512 || (active <= 2048 && W >= 512)) return 1024;
+  if (active <= 2048) return 512;
+  return active > 16384 && W <= 64 ? 128 : 256;
+}
 // Costs that decide between the two forms after each batch, in us: a round's launch, plus
 // so much per word that it visits; a round of k_chain_pair, plus so much per member of
 // the largest pair for the scans of its one workgroup.  (Fitted to both forms alone on 1+1,
@@ -59,7 +70,9 @@ constexpr unsigned long long kWideWords = 2048;  // 16 wavefronts per word up to
 constexpr double kRoundUs = 5.0, kWordUs = 6e-4, kPairRoundUs = 3.5, kPairMemberUs = 0.03;
 constexpr uint64_t kNoWord = ~0ull;  // unused entry of the word list
 // Up to this many words in all, round 0 is launched over every one before the first look at
-// the members (entries past the list's end return at once): a host round trip costs more.
+// the members (entries past the list's end return at once): the host round trip costs 20 us, e.g.
+// 896 -> 921 for the whole 3+1 order of 131072 elements without.  A limit of 16384 words made
+// seven random pairs of 131072, few of whose words have members, take 120 us instead of 57.
 constexpr int64_t kBlindWords = 4096;
 constexpr int64_t kPairMaxN = 32768;  // k_chain_pair: 16-bit indices, 140 KiB of LDS
 
@@ -158,6 +171,78 @@ __global__ __launch_bounds__(kSurveyThreads) void k_chain_survey(
     if (lane == 0) at = atomicAdd(&active, (uint32_t)__popcll(m));
     at = __shfl(at, 0) + (uint32_t)__popcll(m & ((1ull << lane) - 1));
     if (some) list[first + at] = (uint64_t)s << 32 | (uint64_t)w << 1 | (w == (int64_t)lowest ? 1u : 0u);
+  }
+}
+
+// The same for more than kSurveyPairs pairs: a wavefront per pair, pairs dealt to the wavefronts
+// of at most kSurveyGroups workgroups, so that few workgroups add to the survey's one line.
+// (40000 pairs of 65 elements: 20 us, where a workgroup per pair took 777.)
+constexpr int kSurveyPairs = 256, kSurveyGroups = 256;
+constexpr int kSurveyWaves = kSurveyThreads / kWave;
+__global__ __launch_bounds__(kSurveyThreads) void k_chain_survey_many(
+    const uint64_t* __restrict__ R, uint64_t* __restrict__ other, int64_t W, int64_t count,
+    int32_t* __restrict__ low, uint64_t* __restrict__ list, Survey* __restrict__ out) {
+  __shared__ unsigned long long wave_left[kSurveyWaves], wave_most[kSurveyWaves],
+      wave_active[kSurveyWaves];  // the last: then where the wavefront's entries go
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int64_t step = (int64_t)gridDim.x * kSurveyWaves;
+  unsigned long long left = 0, most = 0, active = 0;
+  for (int64_t s = (int64_t)blockIdx.x * kSurveyWaves + wave; s < count; s += step) {
+    uint32_t members = 0;
+    int64_t lowest = W;
+    for (int64_t w0 = 0; w0 < W; w0 += kWave) {
+      const int64_t w = w0 + lane;
+      const uint64_t x = w < W ? R[s * W + w] : 0ull;
+      if (w < W && x == 0) other[s * W + w] = 0;
+      const uint64_t m = __ballot(x != 0);
+      members += (uint32_t)__popcll(x);
+      active += (unsigned long long)__popcll(m);
+      if (m && lowest == W) lowest = w0 + __builtin_ctzll(m);
+    }
+    for (int off = kWave / 2; off > 0; off >>= 1) members += __shfl_xor(members, off);
+    if (lane == 0) low[s] = (int32_t)lowest;
+    left += members;
+    most = max(most, (unsigned long long)members);
+  }
+  if (lane == 0) {
+    wave_left[wave] = left;
+    wave_most[wave] = most;
+    wave_active[wave] = active;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    unsigned long long words = 0;
+    for (int i = 0; i < kSurveyWaves; ++i) words += wave_active[i];
+    if (words) {
+      unsigned long long at = atomicAdd(&out->active, words);
+      left = most = 0;
+      for (int i = 0; i < kSurveyWaves; ++i) {
+        left += wave_left[i];
+        most = max(most, wave_most[i]);
+        const unsigned long long own = wave_active[i];
+        wave_active[i] = at;
+        at += own;
+      }
+      atomicAdd(&out->left, left);
+      atomicMax(&out->most, most);
+    }
+  }
+  __syncthreads();
+  if (active == 0) return;
+  unsigned long long at = wave_active[wave];
+  for (int64_t s = (int64_t)blockIdx.x * kSurveyWaves + wave; s < count; s += step) {
+    bool first = true;
+    for (int64_t w0 = 0; w0 < W; w0 += kWave) {
+      const int64_t w = w0 + lane;
+      const bool some = w < W && R[s * W + w] != 0;
+      const uint64_t m = __ballot(some);
+      if (m == 0) continue;
+      const int below = __popcll(m & ((1ull << lane) - 1));
+      if (some) list[at + below] = (uint64_t)s << 32 | (uint64_t)w << 1 | (first && below == 0 ? 1u : 0u);
+      at += (unsigned long long)__popcll(m);
+      first = false;
+    }
   }
 }
 
@@ -316,11 +401,16 @@ __global__ __launch_bounds__(THREADS, 8) void k_chain_round(
 // group of 8 lanes and 64 words per step, so a wavefront serves 8 members at once.
 constexpr int kPairGroup = 8;    // lanes per scan
 constexpr int kPairUnroll = 4;   // words per wavefront and check step; loads per scan step
+constexpr int64_t kNarrowWords = 16;  // more pairs than CUs take 256 threads for up to so many
+                                      // words, which four wavefronts check in a step (5000
+                                      // pairs of 65 elements 8 us, with 1024 threads 10)
 
+template <int kPairThreads>
 __global__ __launch_bounds__(kPairThreads) void k_chain_pair(
     const uint64_t* __restrict__ bits, int64_t n, int64_t ld, int64_t W64,
     const uint64_t* __restrict__ X0, const int32_t* __restrict__ wit0,
     const int32_t* __restrict__ low0, int32_t* __restrict__ height, int t) {
+  constexpr int kPairWaves = kPairThreads / kWave;
   extern __shared__ uint64_t chain_lds[];
   const int W = (int)W64;
   uint64_t* X = chain_lds;      // bitmap c at X + c W
@@ -602,8 +692,14 @@ cs_status launch_longest_chain(const uint64_t* bits, int64_t n, int64_t ld, cons
   Survey& now = seen[1];
   for (int64_t t = 0, batch = 8, b = 0;; ++b) {
     // the members before round t; low[] is read by round t from the other parity
-    hipLaunchKernelGGL(k_chain_survey, dim3((unsigned)count), dim3(kSurveyThreads), 0, st, L.X[t & 1],
-                       L.X[(t + 1) & 1], W, L.low[(t + 1) & 1], L.list, L.survey + b);
+    if (count <= kSurveyPairs)
+      hipLaunchKernelGGL(k_chain_survey, dim3((unsigned)count), dim3(kSurveyThreads), 0, st,
+                         L.X[t & 1], L.X[(t + 1) & 1], W, L.low[(t + 1) & 1], L.list, L.survey + b);
+    else
+      hipLaunchKernelGGL(k_chain_survey_many,
+                         dim3((unsigned)std::min<int64_t>(kSurveyGroups, ceil_div(count, kSurveyWaves))),
+                         dim3(kSurveyThreads), 0, st, L.X[t & 1], L.X[(t + 1) & 1], W, count,
+                         L.low[(t + 1) & 1], L.list, L.survey + b);
     CS_LAUNCH_CHECK();
     if (t == 0 && words <= kBlindWords) {
       now.active = (unsigned long long)words;
@@ -624,8 +720,13 @@ cs_status launch_longest_chain(const uint64_t* bits, int64_t n, int64_t ld, cons
       if (n <= kPairMaxN && rounds * (kRoundUs + kWordUs * (double)now.active) >
                                 rounds * kPairRoundUs + kPairMemberUs * (double)now.most) {
         const size_t lds = (size_t)W * (3 * sizeof(uint64_t) + 2 * kWave * sizeof(uint16_t));
-        hipLaunchKernelGGL(k_chain_pair, dim3((unsigned)count), dim3(kPairThreads), lds, st, bits, n,
-                           ld, W, L.X[t & 1], L.wit, L.low[(t + 1) & 1], h, (int)t);
+        const bool narrow = W <= kNarrowWords && count > kSurveyPairs;
+        auto pairs = [&](auto kernel, int threads) {
+          hipLaunchKernelGGL(kernel, dim3((unsigned)count), dim3(threads), lds, st, bits, n, ld, W,
+                             L.X[t & 1], L.wit, L.low[(t + 1) & 1], h, (int)t);
+        };
+        if (narrow) pairs(k_chain_pair<256>, 256);
+        else pairs(k_chain_pair<1024>, 1024);
         CS_LAUNCH_CHECK();
         CS_HIP_CHECK(hipStreamSynchronize(st));
         break;
@@ -634,15 +735,18 @@ cs_status launch_longest_chain(const uint64_t* bits, int64_t n, int64_t ld, cons
     }
     const int64_t end = std::min<int64_t>(t + batch, n + 1);
     batch = end - t;
+    const int threads = round_threads(W, now.active);
     for (; t < end; ++t) {
       const int c = (int)(t & 1);
-      const dim3 grid = grid_rows((int64_t)now.active);
-      if (now.active <= kWideWords)
-        hipLaunchKernelGGL(k_chain_round<1024>, grid, dim3(1024), 0, st, bits, n, ld, W, L.list,
-                           (int64_t)now.active, L.X[c], L.X[c ^ 1], L.wit, h, L.low[c ^ 1], L.low[c], (int32_t)t);
-      else
-        hipLaunchKernelGGL(k_chain_round<256>, grid, dim3(256), 0, st, bits, n, ld, W, L.list,
-                           (int64_t)now.active, L.X[c], L.X[c ^ 1], L.wit, h, L.low[c ^ 1], L.low[c], (int32_t)t);
+      auto round = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid_rows((int64_t)now.active), dim3(threads), 0, st, bits, n, ld, W,
+                           L.list, (int64_t)now.active, L.X[c], L.X[c ^ 1], L.wit, h, L.low[c ^ 1],
+                           L.low[c], (int32_t)t);
+      };
+      if (threads == 1024) round(k_chain_round<1024>);
+      else if (threads == 512) round(k_chain_round<512>);
+      else if (threads == 256) round(k_chain_round<256>);
+      else round(k_chain_round<128>);
       CS_LAUNCH_CHECK();
     }
   }

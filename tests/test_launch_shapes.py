@@ -108,3 +108,21 @@ def test_dalembertian_tiles_follow_the_workspace(rec, n, counter, last):
         assert len(launches(rec, "k_count_mfmaILi2E" if small else "k_count_mfmaILi4E")) == 1
         (x, y, threads), = launches(rec, "k_count_mfma")
         assert (x, y, threads) == (tiles if small else min(tiles, 256), 1, 256)
+
+
+@pytest.mark.parametrize("count", [1, 256, 257, 40000, 65535])
+def test_chain_survey_workgroups(rec, count):
+    """Each workgroup of a survey adds to the same line: at most 256 of them."""
+    rec.rec_reset()
+    n, words = 65, 2 * count
+    survey = (ctypes.c_uint64 * 4)(words, 2, words, 0)
+    ended = (ctypes.c_uint64 * 8)(words, 2, words, 0, 0, 0, 0, 0)
+    if words > 4096:
+        rec.rec_reply(survey, 32)
+    rec.rec_reply(ended, 64)
+    ends = (ctypes.c_int64 * (2 * count))(*([-1] * count + [n] * count))
+    at = ctypes.addressof(ends)
+    assert rec.cs_longest_chain(ANY, n, 8, at, at + 8 * count, count, ANY, ANY, ANY, ROOM, None) == 0
+    surveys = launches(rec, "k_chain_survey")
+    assert len(surveys) == 2
+    assert all(x <= 256 and y == 1 and threads == 1024 for x, y, threads in surveys)
