@@ -39,6 +39,7 @@ using namespace cs;
 namespace {
 
 constexpr int kMaxSlots = 8;  // distinct tile configurations in one plan
+constexpr int kSmallUnits = 12;  // counting units of 512 points: an item holds a small instance
 
 // Size buckets of the tuner: [lo, hi] and the centre of the sizes timed for each.
 constexpr int kBuckets = 4;
@@ -65,7 +66,8 @@ const BatchTile kBitsetCandidates[] = {{0, 2, -1}, {0, 2, 1152}, {0, 2, 2304}, {
 
 // Counting by ranks is one more configuration (mode 1), the same for every counter: O(N^2)
 // operations per instance where the tiles take O(N^3), the same exact counts.
-const BatchTile kRankTile = {1, 2, 0};
+// Small instances in launches of their own (kSmallN) have eight workgroups per CU.
+const BatchTile kRankTile = {1, 2, 0}, kSmallRankTile = {1, 32 / kSmallWaves, 0};
 
 struct TuneTable {
   bool have[3][kBuckets] = {};
@@ -178,21 +180,23 @@ struct cs_batch_plan_t {
   int n_eps = 0;
   std::vector<BatchInst> inst;
   int64_t coords_len = 0, bits_len = 0, hist_len = 0;
-  int64_t n_build = 0;
   int nslots = 0;
   BatchTile slot_cfg[kMaxSlots] = {};
   int64_t n_items[kMaxSlots] = {};
   BatchQueues queues[kMaxSlots] = {};
   size_t ws_bytes = 0, off_coords = 0, off_bits = 0, off_uv = 0, off_rank = 0;
-  int64_t n_tab = 0;                // work items of the rank tables
-  int rank_units = kRankWaves;      // counting units per item
+  int rank_units = kRankWaves;      // counting units per item (small instances: kSmallUnits)
   void* dev = nullptr;              // device tables
   BatchInst* d_inst = nullptr;
   RankInst* d_rank = nullptr;
-  uint32_t* d_tab = nullptr;
   double* d_eps = nullptr;
-  uint32_t* d_build = nullptr;
   uint32_t* d_items[kMaxSlots] = {};
+  // Per class, small instances first: its instances (ids null: all of the plan), and the work
+  // items of the builder and of the rank tables.
+  struct Class {
+    int64_t count = 0, n_build = 0, n_tab = 0;
+    uint32_t *ids = nullptr, *build = nullptr, *tab = nullptr;
+  } cls[2];
   int device = 0;
 };
 
@@ -219,7 +223,11 @@ cs_status build_plan(int64_t count, const int64_t* n, int counter, int n_eps, co
   std::vector<Item> items[kMaxSlots];
   const int cslot = counter_slot(counter);
   std::vector<RankInst> rank(count);  // n = 0: counted by tiles
-  std::vector<uint32_t> tab;
+  const int64_t nsmall = std::count_if(n, n + count, [](int64_t m) { return m <= kSmallN; });
+  const bool tiny = *std::max_element(n, n + count) <= kTinyN;
+  const bool split = tiny || nsmall >= kSmallMany;  // small instances by themselves
+  auto class_of = [&](int64_t m) { return split && m <= kSmallN ? 0 : 1; };
+  std::vector<uint32_t> ids[2], build[2], tab[2];
   int64_t roff = 0, units = 0;
   int64_t coff = 0, boff = 0, hoff = 0;
   for (int64_t k = 0; k < count; ++k) {
@@ -234,7 +242,10 @@ cs_status build_plan(int64_t count, const int64_t* n, int counter, int n_eps, co
     hoff += d.n - 1;
     const int64_t nb = ceil_div(d.n, 64);
     const int b = bucket_of(d.n);
-    const BatchTile cfg = force ? *force : tune.choice(cslot, b);
+    const int cl = class_of(d.n);
+    ids[cl].push_back((uint32_t)k);
+    BatchTile cfg = force ? *force : tune.choice(cslot, b);
+    if (cl == 0 && same_tile(cfg, kRankTile)) cfg = kSmallRankTile;
     int slot = -1;
     for (int q = 0; q < p->nslots; ++q)
       if (same_tile(p->slot_cfg[q], cfg)) slot = q;
@@ -250,8 +261,9 @@ cs_status build_plan(int64_t count, const int64_t* n, int counter, int n_eps, co
       r.n = (int32_t)d.n;
       r.nb = (int32_t)nb;
       roff = (int64_t)align_up((size_t)r.end(), 256);
-      units += r.units();
-      for (int64_t g = 0; g * kTabBlocks < nb; ++g) tab.push_back((uint32_t)(k << 16 | g));
+      if (cl == 1) units += r.units();
+      for (int64_t g = 0; g * (cl ? kTabBlocks : kSmallWaves) < nb; ++g)
+        tab[cl].push_back((uint32_t)(k << 16 | g));
       continue;
     }
     const int64_t BM = cfg.mode == 4 ? 256 : 128;
@@ -267,15 +279,13 @@ cs_status build_plan(int64_t count, const int64_t* n, int counter, int n_eps, co
   // back from several XCDs multiplied the builder's HBM writes).  Workgroup b takes entry
   // b div 8 of list b mod 8 (the XCD that the dispatcher gives it): a group of 512 columns
   // of an instance.  Lists are padded with kNoBuildItem to one length.
-  std::vector<uint32_t> build;
-  {
-    std::vector<int64_t> order(count);
-    for (int64_t k = 0; k < count; ++k) order[k] = k;
+  for (int cl = 0; cl < 2; ++cl) {
+    std::vector<uint32_t> order = ids[cl];
     std::stable_sort(order.begin(), order.end(),
-                     [&](int64_t a, int64_t b) { return p->inst[a].n > p->inst[b].n; });
+                     [&](uint32_t a, uint32_t b) { return p->inst[a].n > p->inst[b].n; });
     std::vector<uint32_t> lists[kBatchQueues];
     int64_t load[kBatchQueues] = {};
-    for (int64_t k : order) {
+    for (uint32_t k : order) {
       const BatchInst& d = p->inst[k];
       const int best = (int)(std::min_element(load, load + kBatchQueues) - load);
       load[best] += d.n * d.ld;
@@ -283,25 +293,36 @@ cs_status build_plan(int64_t count, const int64_t* n, int counter, int n_eps, co
     }
     size_t len = 0;
     for (auto& l : lists) len = std::max(len, l.size());
-    build.assign(len * kBatchQueues, kNoBuildItem);
+    build[cl].assign(len * kBatchQueues, kNoBuildItem);
     for (int x = 0; x < kBatchQueues; ++x)
-      std::copy(lists[x].begin(), lists[x].end(), build.begin() + x * len);
+      std::copy(lists[x].begin(), lists[x].end(), build[cl].begin() + x * len);
+    p->cls[cl].count = (int64_t)ids[cl].size();
+    p->cls[cl].n_build = (int64_t)build[cl].size();
+    p->cls[cl].n_tab = (int64_t)tab[cl].size();
   }
-  p->n_build = (int64_t)build.size();
-  p->n_tab = (int64_t)tab.size();
   for (int s = 0; s < p->nslots; ++s) {
-    if (p->slot_cfg[s].mode == kRankTile.mode) {
+    if (same_tile(p->slot_cfg[s], kSmallRankTile)) {  // an item per instance, largest first
+      std::vector<uint32_t> order;
+      for (uint32_t k : ids[0])
+        if (rank[k].n) order.push_back(k);
+      std::stable_sort(order.begin(), order.end(),
+                       [&](uint32_t a, uint32_t b) { return rank[a].n > rank[b].n; });
+      for (uint32_t k : order) items[s].push_back({k << 16, 0});
+      p->n_items[s] = (int64_t)items[s].size();
+      continue;
+    }
+    if (same_tile(p->slot_cfg[s], kRankTile)) {
       // Units in items of one instance, largest instances first.  An item's histogram is
       // flushed when the workgroup moves to another instance, so items are long, down to
       // about four per resident workgroup (two per CU), and at least a unit per wavefront.
       const int64_t per = units / (4 * 2 * (int64_t)device_cu_count()) / kRankWaves * kRankWaves;
       p->rank_units = (int)std::min<int64_t>(std::max<int64_t>(per, kRankWaves), 8 * kRankWaves);
-      std::vector<int64_t> order;
-      for (int64_t k = 0; k < count; ++k)
+      std::vector<uint32_t> order;
+      for (uint32_t k : ids[1])
         if (rank[k].n) order.push_back(k);
       std::stable_sort(order.begin(), order.end(),
-                       [&](int64_t a, int64_t b) { return rank[a].n > rank[b].n; });
-      for (int64_t k : order)
+                       [&](uint32_t a, uint32_t b) { return rank[a].n > rank[b].n; });
+      for (uint32_t k : order)
         for (int64_t c = 0; c * p->rank_units < rank[k].units(); ++c)
           items[s].push_back({(uint32_t)(k << 16 | c), 0});
       p->n_items[s] = (int64_t)items[s].size();
@@ -362,9 +383,13 @@ cs_status build_plan(int64_t count, const int64_t* n, int counter, int n_eps, co
   size_t doff = 0;
   size_t o_inst = take(&doff, sizeof(BatchInst) * count);
   size_t o_rank = take(&doff, sizeof(RankInst) * count);
-  size_t o_tab = take(&doff, sizeof(uint32_t) * tab.size());
   size_t o_eps = take(&doff, sizeof(double) * (n_eps > 0 ? n_eps : 1));
-  size_t o_build = take(&doff, sizeof(uint32_t) * build.size());
+  size_t o_ids[2], o_build[2], o_tab[2];
+  for (int cl = 0; cl < 2; ++cl) {
+    o_ids[cl] = take(&doff, sizeof(uint32_t) * ids[cl].size());
+    o_build[cl] = take(&doff, sizeof(uint32_t) * build[cl].size());
+    o_tab[cl] = take(&doff, sizeof(uint32_t) * tab[cl].size());
+  }
   size_t o_items[kMaxSlots];
   for (int s = 0; s < p->nslots; ++s) o_items[s] = take(&doff, sizeof(uint32_t) * items[s].size());
   CS_HIP_CHECK(hipGetDevice(&p->device));
@@ -372,15 +397,21 @@ cs_status build_plan(int64_t count, const int64_t* n, int counter, int n_eps, co
   char* b = (char*)p->dev;
   p->d_inst = (BatchInst*)(b + o_inst);
   p->d_rank = (RankInst*)(b + o_rank);
-  p->d_tab = (uint32_t*)(b + o_tab);
   p->d_eps = (double*)(b + o_eps);
-  p->d_build = (uint32_t*)(b + o_build);
   std::vector<char> host(doff, 0);
   memcpy(host.data() + o_inst, p->inst.data(), sizeof(BatchInst) * count);
   memcpy(host.data() + o_rank, rank.data(), sizeof(RankInst) * count);
-  if (!tab.empty()) memcpy(host.data() + o_tab, tab.data(), sizeof(uint32_t) * tab.size());
   if (n_eps > 0) memcpy(host.data() + o_eps, eps, sizeof(double) * n_eps);
-  memcpy(host.data() + o_build, build.data(), sizeof(uint32_t) * build.size());
+  for (int cl = 0; cl < 2; ++cl) {
+    auto put = [&](const std::vector<uint32_t>& v, size_t at) {
+      std::copy(v.begin(), v.end(), (uint32_t*)(host.data() + at));
+      return (uint32_t*)(b + at);
+    };
+    uint32_t* all = put(ids[cl], o_ids[cl]);
+    p->cls[cl].ids = p->cls[cl].count == count ? nullptr : all;
+    p->cls[cl].build = put(build[cl], o_build[cl]);
+    p->cls[cl].tab = put(tab[cl], o_tab[cl]);
+  }
   for (int s = 0; s < p->nslots; ++s) {
     p->d_items[s] = (uint32_t*)(b + o_items[s]);
     uint32_t* dst = (uint32_t*)(host.data() + o_items[s]);
@@ -397,9 +428,12 @@ cs_status run_counts(cs_batch_plan_t* p, char* ws, uint64_t* hist, hipStream_t s
   for (int s = 0; s < p->nslots; ++s) {
     if (!p->n_items[s]) continue;
     if (p->slot_cfg[s].mode == kRankTile.mode) {
-      cs_status r = launch_rank_tables(p->d_rank, p->d_tab, p->n_tab, rank_base, st);
+      const bool small = same_tile(p->slot_cfg[s], kSmallRankTile);
+      const cs_batch_plan_t::Class& c = p->cls[small ? 0 : 1];
+      cs_status r = launch_rank_tables(small, p->d_rank, c.tab, c.n_tab, rank_base, st);
       if (r != CS_OK) return r;
-      r = launch_count_ranks(p->d_rank, p->d_items[s], p->n_items[s], p->rank_units, rank_base, hist,
+      r = launch_count_ranks(small, p->d_rank, p->d_items[s], p->n_items[s],
+                             small ? kSmallUnits : p->rank_units, rank_base, hist,
                              ctr + s * kBatchQueues, st);
       if (r != CS_OK) return r;
       continue;
@@ -472,12 +506,21 @@ cs_status cs_batch_run(cs_batch_plan_handle plan, const uint64_t* seeds, uint64_
   uint32_t* uv = (uint32_t*)(ws + plan->off_uv);
   cs_status s;
   // the sprinkle kernel also clears the histograms and the work counters
-  if ((s = launch_sprinkle_batch(seeds, plan->d_inst, plan->d_rank, plan->count, coords,
-                                 uv, ws + plan->off_rank, hist, (uint64_t*)ctr,
-                                 kMaxSlots * kBatchQueues / 2, st)) != CS_OK)
-    return s;
-  if ((s = launch_build_batch(uv, plan->d_inst, plan->d_build, plan->n_build, bits, st)) != CS_OK)
-    return s;
+  bool cleared = false;
+  for (int cl = 0; cl < 2; ++cl) {
+    const cs_batch_plan_t::Class& c = plan->cls[cl];
+    if (!c.count) continue;
+    if ((s = launch_sprinkle_batch(cl == 0, seeds, plan->d_inst, plan->d_rank, c.ids, c.count, coords,
+                                   uv, ws + plan->off_rank, hist, (uint64_t*)ctr,
+                                   cleared ? 0 : kMaxSlots * kBatchQueues / 2, st)) != CS_OK)
+      return s;
+    cleared = true;
+  }
+  for (int cl = 0; cl < 2; ++cl) {
+    const cs_batch_plan_t::Class& c = plan->cls[cl];
+    if ((s = launch_build_batch(cl == 0, uv, plan->d_inst, c.build, c.n_build, bits, st)) != CS_OK)
+      return s;
+  }
   if ((s = run_counts(plan, ws, hist, st)) != CS_OK) return s;
   return launch_action_batch(hist, plan->d_inst, plan->count, 2, plan->d_eps, plan->n_eps, actions,
                              st);

@@ -405,14 +405,18 @@ __global__ __launch_bounds__(256) void k_build(const double* __restrict__ coords
 // XCD, padded with kNoBuildItem: workgroup b takes entry b div kBatchQueues of list
 // b mod kBatchQueues, the XCD that the dispatcher gives it, whose L2 completes the lines.
 constexpr int kBuildBlocks = 8;
-constexpr int kBuildTables = 2 * kBuildBlocks;  // (block, axis); one wavefront each
-constexpr int kBuildThreads = 64 * kBuildTables;
-constexpr int kBuildWords = (int)(kBatchMaxN / 32);
+constexpr int kBuildTables = 2 * kBuildBlocks;  // (block, axis)
+// Wavefronts, for instances of up to CAP points: one per table, or four, with eight workgroups per
+// CU (30000 diamonds of 64 points 45 us, 298 with sixteen).
+template <int CAP>
+constexpr int kBuildWaves = CAP == kBatchMaxN ? kBuildTables : 4;
 
-__global__ __launch_bounds__(kBuildThreads, 8) void k_build_batch(
+template <int CAP>
+__global__ __launch_bounds__(64 * kBuildWaves<CAP>, 8) void k_build_batch(
     const uint32_t* __restrict__ uvs, const BatchInst* __restrict__ inst,
     const uint32_t* __restrict__ items, int64_t nitems, uint64_t* __restrict__ bits) {
-  __shared__ uint2 sets[kBuildTables][kBuildWords] __attribute__((aligned(16)));  // bits, count below
+  constexpr int kWaves = kBuildWaves<CAP>, kWords = CAP / 32;
+  __shared__ uint2 sets[kBuildTables][kWords] __attribute__((aligned(16)));  // bits, count below
   __shared__ uint64_t above[kBuildTables][66];  // [c]: columns with at least c of the block below
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -431,20 +435,20 @@ __global__ __launch_bounds__(kBuildThreads, 8) void k_build_batch(
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   };
-  {  // wavefront 2 b + axis: the tables of column block b0 + b
-    const int j = 64 * (b0 + (wave >> 1)) + lane;
-    const bool valid = j < n;
+  const int blocks = nb - b0 < kBuildBlocks ? nb - b0 : kBuildBlocks;
+  for (int a = wave; a < 2 * blocks; a += kWaves) {  // table 2 b + axis: column block b0 + b
+    const int j = 64 * (b0 + (a >> 1)) + lane;
+    const bool valid = j < n, mine = 4 * lane < kWords;  // a lane's four words of the set
     const uint32_t t = valid ? uv[j] : 0u;
-    const uint32_t place = (wave & 1) ? t & 0xFFFFu : t >> 16;
-    uint4* s4 = (uint4*)(sets[wave] + 4 * lane);
-    s4[0] = make_uint4(0, 0, 0, 0);
-    s4[1] = make_uint4(0, 0, 0, 0);
-    above[wave][lane] = 0;
-    if (lane < 2) above[wave][64 + lane] = 0;
+    const uint32_t place = (a & 1) ? t & 0xFFFFu : t >> 16;
+    uint4* s4 = (uint4*)(sets[a] + (mine ? 4 * lane : 0));
+    if (mine) s4[0] = s4[1] = make_uint4(0, 0, 0, 0);
+    above[a][lane] = 0;
+    if (lane < 2) above[a][64 + lane] = 0;
     wave_sync();
-    if (valid) atomicOr(&sets[wave][place >> 5].x, 1u << (place & 31));
+    if (valid) atomicOr(&sets[a][place >> 5].x, 1u << (place & 31));
     wave_sync();
-    const uint4 p0 = s4[0], p1 = s4[1];
+    const uint4 none = make_uint4(0, 0, 0, 0), p0 = mine ? s4[0] : none, p1 = mine ? s4[1] : none;
     const uint32_t c0 = __popc(p0.x), c1 = c0 + __popc(p0.z), c2 = c1 + __popc(p1.x);
     const uint32_t sum = c2 + __popc(p1.z);
     uint32_t x = sum;
@@ -454,18 +458,20 @@ __global__ __launch_bounds__(kBuildThreads, 8) void k_build_batch(
       if (lane >= k) x += y;
     }
     x -= sum;
-    s4[0] = make_uint4(p0.x, x, p0.z, x + c0);
-    s4[1] = make_uint4(p1.x, x + c1, p1.z, x + c2);
+    if (mine) {
+      s4[0] = make_uint4(p0.x, x, p0.z, x + c0);
+      s4[1] = make_uint4(p1.x, x + c1, p1.z, x + c2);
+    }
     wave_sync();
-    if (valid) above[wave][query(wave, place)] = 1ull << lane;
+    if (valid) above[a][query(a, place)] = 1ull << lane;
     wave_sync();
-    uint64_t m = above[wave][lane];
+    uint64_t m = above[a][lane];
 #pragma unroll
     for (int k = 1; k < 64; k <<= 1) {  // suffix OR over the lanes
       const uint32_t lo = __shfl_down((uint32_t)m, k), hi = __shfl_down((uint32_t)(m >> 32), k);
       if (lane + k < 64) m |= (uint64_t)hi << 32 | lo;
     }
-    above[wave][lane] = m;
+    above[a][lane] = m;
   }
   __syncthreads();
   // Four lanes per row, two words each: a store instruction writes 16 whole 64-byte
@@ -474,7 +480,7 @@ __global__ __launch_bounds__(kBuildThreads, 8) void k_build_batch(
   const int quarter = lane & 3, own = 2 * quarter;  // this lane's blocks: b0 + own, + 1
   const bool edge = 64 * (b0 + kBuildBlocks) > n;   // columns past n in this group
   uint64_t* __restrict__ S = bits + d.bits_off + b0 + own;
-  for (int rb = wave; rb < nb; rb += kBuildTables) {
+  for (int rb = wave; rb < nb; rb += kWaves) {
     uint32_t t[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
@@ -489,11 +495,11 @@ __global__ __launch_bounds__(kBuildThreads, 8) void k_build_batch(
 #pragma unroll
       for (int e = 0; e < 2; ++e) {
         const int a = 2 * (own + e);
-        w[e] = ~(above[a][query(a, pu)] ^ above[a + 1][query(a + 1, pv)]);
+        w[e] = own + e < blocks ? ~(above[a][query(a, pu)] ^ above[a + 1][query(a + 1, pv)]) : 0ull;
         if (rb - b0 == own + e) w[e] &= ~(1ull << (i & 63));  // not related to itself
         if (edge) {
           const int left = n - 64 * (b0 + own + e);
-          w[e] &= left >= 64 ? ~0ull : (left <= 0 ? 0ull : (1ull << left) - 1ull);
+          if (left > 0 && left < 64) w[e] &= (1ull << left) - 1ull;
         }
       }
       if (i < n)
@@ -541,12 +547,16 @@ cs_status launch_causal_matrix(int region, const double* coords, int64_t n, uint
   }
 }
 
-cs_status launch_build_batch(const uint32_t* uv, const BatchInst* inst, const uint32_t* items,
-                             int64_t nitems, uint64_t* bits, hipStream_t st) {
+cs_status launch_build_batch(bool small, const uint32_t* uv, const BatchInst* inst,
+                             const uint32_t* items, int64_t nitems, uint64_t* bits, hipStream_t st) {
   if (nitems <= 0) return CS_OK;
   if (nitems % kBatchQueues != 0) return CS_ERR_INVALID_ARG;
-  hipLaunchKernelGGL(k_build_batch, dim3((unsigned)nitems), dim3(kBuildThreads), 0, st, uv, inst,
-                     items, nitems, bits);
+  auto go = [&](auto kernel, int waves) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)nitems), dim3(64 * waves), 0, st, uv, inst, items, nitems,
+                       bits);
+  };
+  if (small) go(k_build_batch<(int)kSmallN>, kBuildWaves<(int)kSmallN>);
+  else go(k_build_batch<(int)kBatchMaxN>, kBuildWaves<(int)kBatchMaxN>);
   CS_LAUNCH_CHECK();
   return CS_OK;
 }

@@ -162,6 +162,14 @@ struct RankInst {
 // Largest instance of an ensemble (its whole histogram fits the LDS bins, its sort
 // fits one workgroup's LDS).
 constexpr int64_t kBatchMaxN = 8192;
+// Instances of up to kSmallN points can take forms of the ensemble kernels with less LDS and
+// fewer wavefronts per instance, in launches of their own: a workgroup sized for 8192 points
+// keeps half a CU or a whole one to itself for microseconds whatever its instance holds.  They
+// do where there are kSmallMany of them, or where the whole ensemble has at most kTinyN points
+// an instance.  Whole runs, us, in the large / the small forms: 60000 of 30 points 3650 / 960,
+// 2000 of 512 212 / 138, 600 of 512 87 / 76, 300 of 512 57 / 65, one of 512 34 / 55 (its units on
+// four wavefronts), one of 200 28.4 / 26.9, one of 64 23.1 / 19.0.
+constexpr int64_t kSmallN = 512, kSmallMany = 512, kTinyN = 192;
 // Padding entry of the ensemble builder's per-XCD item lists.
 constexpr uint32_t kNoBuildItem = 0xFFFFFFFFu;
 
@@ -199,20 +207,25 @@ constexpr size_t kScratchBytes = 16384;
 cs_status scratch_for_current_device(void** out);
 
 // Ensemble pieces (1+1 diamonds).
-cs_status launch_sprinkle_batch(const uint64_t* seeds, const BatchInst* inst, const RankInst* rank,
-                                int64_t count, double* coords, uint32_t* uv, char* rank_base,
-                                uint64_t* hist, uint64_t* zero, int nzero, hipStream_t st);
-// Rank tables (items: instance << 16 | group of kTabBlocks column blocks), then the counts from them (items:
-// instance << 16 | chunk of `per_item` units; counter: one work counter, zero at launch).
-cs_status launch_rank_tables(const RankInst* rank, const uint32_t* items, int64_t nitems,
+// small: the forms for instances of at most kSmallN points.  ids: the instances of the launch
+// (null: 0 .. count - 1).
+cs_status launch_sprinkle_batch(bool small, const uint64_t* seeds, const BatchInst* inst,
+                                const RankInst* rank, const uint32_t* ids, int64_t count,
+                                double* coords, uint32_t* uv, char* rank_base, uint64_t* hist,
+                                uint64_t* zero, int nzero, hipStream_t st);
+// Rank tables (items: instance << 16 | group of kTabBlocks column blocks), then the counts from
+// them (items: instance << 16 | chunk of `per_item` units; counter: one work counter, zero at
+// launch).
+cs_status launch_rank_tables(bool small, const RankInst* rank, const uint32_t* items, int64_t nitems,
                              char* rank_base, hipStream_t st);
-cs_status launch_count_ranks(const RankInst* rank, const uint32_t* items, int64_t nitems,
+cs_status launch_count_ranks(bool small, const RankInst* rank, const uint32_t* items, int64_t nitems,
                              int per_item, const char* rank_base, uint64_t* hist,
                              unsigned int* counter, hipStream_t st);
 constexpr int kRankWaves = 16;  // wavefronts per workgroup of the rank counter
 constexpr int kTabBlocks = 16;  // column blocks per workgroup of the rank tables
-cs_status launch_build_batch(const uint32_t* uv, const BatchInst* inst, const uint32_t* items,
-                             int64_t nitems, uint64_t* bits, hipStream_t st);
+constexpr int kSmallWaves = 4;  // both for small instances
+cs_status launch_build_batch(bool small, const uint32_t* uv, const BatchInst* inst,
+                             const uint32_t* items, int64_t nitems, uint64_t* bits, hipStream_t st);
 // Launch configuration of an ensemble counter: mode 0 is the bitset counter (128 tiles;
 // tiles with more than pair_max related-pair tasks take the dense product, pair_max < 0:
 // every tile), modes 2 / 4 the MFMA counter with 128 / 256 tiles on the int8 or (fp4 =

@@ -27,50 +27,54 @@ namespace cs {
 namespace {
 
 // ---------------------------------------------------------------------------
-// Tables: a workgroup per (instance, group of kTabBlocks column blocks), one wavefront per
-// column block J.  F(64 J, x) is a rank query on the set of v places of the points with u
-// place below 64 J: a bit per v place, with the running count beside every 32 of them.
+// Tables: a workgroup per (instance of up to CAP points, group of TB column blocks), one
+// wavefront per column block J.  F(64 J, x) is a rank query on the set of v places of the points
+// with u place below 64 J: a bit per v place, with the running count beside every 32 of them.
 // The group's first set comes from sigma (one ballot per 64 places), the others add the
 // preceding blocks' points.  A query is one 8-byte LDS gather and a popcount, about nine
 // operations per table entry; scattering F through LDS from a scan of sigma by every
 // wavefront took 146 us for 256 diamonds of 512 to 8192 points, this takes 70 us (97 MB
-// written).
+// written).  30000 diamonds of 64 points take 36 us with CAP = 512, TB = 4, and 184 with 8192, 16.
 // ---------------------------------------------------------------------------
-constexpr int kTabThreads = 64 * kTabBlocks;
-constexpr int kTabWords = (int)(kBatchMaxN / 32);
-
-__global__ __launch_bounds__(kTabThreads) void k_rank_tables(const RankInst* __restrict__ rank,
-                                                             const uint32_t* __restrict__ items,
-                                                             char* __restrict__ base) {
-  __shared__ uint16_t pis[kBatchMaxN] __attribute__((aligned(16)));
-  __shared__ uint32_t first[kTabWords] __attribute__((aligned(16)));
-  __shared__ uint32_t own[kTabBlocks][kTabWords] __attribute__((aligned(16)));
-  __shared__ uint2 sets[kTabBlocks][kTabWords] __attribute__((aligned(16)));  // bits, count below
+template <int CAP, int TB>
+__global__ __launch_bounds__(64 * TB) void k_rank_tables(const RankInst* __restrict__ rank,
+                                                         const uint32_t* __restrict__ items,
+                                                         char* __restrict__ base) {
+  constexpr int kThreads = 64 * TB, kWords = CAP / 32;
+  __shared__ uint16_t pis[CAP] __attribute__((aligned(16)));
+  __shared__ uint32_t first[kWords] __attribute__((aligned(16)));
+  __shared__ uint32_t own[TB][kWords] __attribute__((aligned(16)));
+  __shared__ uint2 sets[TB][kWords] __attribute__((aligned(16)));  // bits, count below
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const uint32_t item = __builtin_amdgcn_readfirstlane(items[blockIdx.x]);
   const RankInst d = rank[item >> 16];
-  const int J0 = (int)(item & 0xFFFFu) * kTabBlocks, J = J0 + wave;
+  const int J0 = (int)(item & 0xFFFFu) * TB, J = J0 + wave;
   const int n = d.n, lim = 64 * J;
   const uint16_t* __restrict__ sigma = (const uint16_t*)(base + d.sigma_off());
   const uint16_t* __restrict__ pi = (const uint16_t*)(base + d.pi_off());
-  for (int r = 8 * threadIdx.x; r < 64 * d.nb; r += 8 * kTabThreads)
+  for (int r = 8 * threadIdx.x; r < 64 * d.nb; r += 8 * kThreads)
     *(uint4*)(pis + r) = *(const uint4*)(pi + r);
-  for (int w = wave; w < d.nb; w += kTabBlocks) {  // sigma is 0xFFFF past n
+  for (int w = wave; w < d.nb; w += TB) {  // sigma is 0xFFFF past n
     const uint64_t m = __ballot((int)sigma[64 * w + lane] < 64 * J0);
     if (lane == 0) *(uint2*)(first + 2 * w) = make_uint2((uint32_t)m, (uint32_t)(m >> 32));
   }
-  for (int w = 2 * d.nb + threadIdx.x; w < kTabWords; w += kTabThreads) first[w] = 0;
-  *(uint4*)(own[wave] + 4 * lane) = make_uint4(0, 0, 0, 0);
+  for (int w = 2 * d.nb + threadIdx.x; w < kWords; w += kThreads) first[w] = 0;
+  const bool mine = 4 * lane < kWords;  // a lane's four words of a set
+  const int at = mine ? 4 * lane : 0;
+  if (mine) *(uint4*)(own[wave] + at) = make_uint4(0, 0, 0, 0);
   const int i = lim + lane;  // the block's own points
   const uint32_t p = i < n ? pi[i] : 0u;
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   if (i < n) atomicOr(&own[wave][p >> 5], 1u << (p & 31));
   __syncthreads();
   if (J >= d.nb) return;  // no barrier below
   {
-    uint4 v = *(const uint4*)(first + 4 * lane);
-    for (int w = 0; w < wave; ++w) {
-      const uint4 o = *(const uint4*)(own[w] + 4 * lane);
+    uint4 v = mine ? *(const uint4*)(first + at) : make_uint4(0, 0, 0, 0);
+    for (int w = 0; w < wave && mine; ++w) {
+      const uint4 o = *(const uint4*)(own[w] + at);
       v.x |= o.x;
       v.y |= o.y;
       v.z |= o.z;
@@ -85,8 +89,10 @@ __global__ __launch_bounds__(kTabThreads) void k_rank_tables(const RankInst* __r
       if (lane >= k) x += y;
     }
     x -= sum;
-    *(uint4*)(sets[wave] + 4 * lane) = make_uint4(v.x, x, v.y, x + c0);
-    *(uint4*)(sets[wave] + 4 * lane + 2) = make_uint4(v.z, x + c1, v.w, x + c2);
+    if (mine) {
+      *(uint4*)(sets[wave] + at) = make_uint4(v.x, x, v.y, x + c0);
+      *(uint4*)(sets[wave] + at + 2) = make_uint4(v.z, x + c1, v.w, x + c2);
+    }
   }
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
@@ -123,16 +129,16 @@ __global__ __launch_bounds__(kTabThreads) void k_rank_tables(const RankInst* __r
 }
 
 // ---------------------------------------------------------------------------
-// Counts.  Persistent workgroups of kRankWaves wavefronts, one LDS histogram each; an item
+// Counts.  Persistent workgroups of WAVES wavefronts, one LDS histogram each; an item
 // is `per_item` units of one instance, dealt to the wavefronts in turn.  A row costs five
 // VALU and three scalar operations for 64 pairs and one LDS add on the related lanes (about
 // half): 256 diamonds of 512 to 8192 points (3.1e9 pairs) take 0.66 ms, 7.3 cycles per
 // row and CU, where the fp4 matrix-core tiles took 3.15 ms.  Issue is the bound: the VALU
 // is busy 68 % of the time, the scalar unit 62 %, the LDS 59 % (without the adds a copy
-// of the kernel took 0.60 ms; 16 rows per fetch 0.68 ms).
+// of the kernel took 0.60 ms; 16 rows per fetch 0.68 ms).  Thousands of small instances are
+// bound by the one work counter, 12 ns an item (30000 of 128 points 374 us; with 16 wavefronts
+// and all 8191 bins 504).
 // ---------------------------------------------------------------------------
-constexpr int kRankThreads = 64 * kRankWaves;
-constexpr int kRankBins = (int)kBatchMaxN - 1;
 constexpr int kRankRows = 8;   // rows per scalar fetch
 
 // One row against the 64 columns of the lanes.  x: pi_i << 16 with low bits of no weight
@@ -215,13 +221,15 @@ __device__ inline void rank_unit(const RankInst& d, const char* __restrict__ bas
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the adds have reached LDS
 }
 
-__global__ __launch_bounds__(kRankThreads, 8) void k_count_ranks(
+template <int CAP, int WAVES>
+__global__ __launch_bounds__(64 * WAVES, 8) void k_count_ranks(
     const RankInst* __restrict__ rank, const uint32_t* __restrict__ items, int64_t nitems,
     int per_item, const char* __restrict__ base, unsigned long long* __restrict__ ghist,
     unsigned int* __restrict__ counter) {
-  __shared__ uint32_t hist[kRankBins];
+  constexpr int kThreads = 64 * WAVES, kBins = CAP - 1;
+  __shared__ uint32_t hist[kBins];
   __shared__ int slot;
-  for (int b = threadIdx.x; b < kRankBins; b += kRankThreads) hist[b] = 0;
+  for (int b = threadIdx.x; b < kBins; b += kThreads) hist[b] = 0;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const bool direct = nitems <= (int64_t)gridDim.x;  // an item per workgroup: no counter
   int cur = -1;
@@ -243,7 +251,7 @@ __global__ __launch_bounds__(kRankThreads, 8) void k_count_ranks(
     const int k = (int)(it >> 16);
     if (k != cur) {
       if (cur >= 0) {
-        for (int b = threadIdx.x; b < d.n - 1; b += kRankThreads)
+        for (int b = threadIdx.x; b < d.n - 1; b += kThreads)
           if (const uint32_t v = hist[b]) {
             atomicAdd(ghist + d.hist_off + b, (unsigned long long)v);
             hist[b] = 0;
@@ -257,7 +265,7 @@ __global__ __launch_bounds__(kRankThreads, 8) void k_count_ranks(
     const int64_t total = (int64_t)(d.nb / kRankSegBlocks + 1) *
                           (kRankSegBlocks / 2 * (d.nb / kRankSegBlocks) + d.nb % kRankSegBlocks);
     const int64_t u1 = u0 + per_item < total ? u0 + per_item : total;
-    for (int64_t u = u0 + wave; u < u1; u += kRankWaves) {
+    for (int64_t u = u0 + wave; u < u1; u += WAVES) {
       // Unit u: the column blocks 4q .. 4q + 3 have q + 1 segments each, 2q (q + 1) units
       // before them.
       int Q = (int)((sqrtf(2.0f * (float)u + 1.0f) - 1.0f) * 0.5f);
@@ -271,28 +279,36 @@ __global__ __launch_bounds__(kRankThreads, 8) void k_count_ranks(
   }
   __syncthreads();
   if (cur >= 0)
-    for (int b = threadIdx.x; b < d.n - 1; b += kRankThreads)
+    for (int b = threadIdx.x; b < d.n - 1; b += kThreads)
       if (const uint32_t v = hist[b]) atomicAdd(ghist + d.hist_off + b, (unsigned long long)v);
 }
 
 }  // namespace
 
-cs_status launch_rank_tables(const RankInst* rank, const uint32_t* items, int64_t nitems,
+cs_status launch_rank_tables(bool small, const RankInst* rank, const uint32_t* items, int64_t nitems,
                              char* rank_base, hipStream_t st) {
   if (nitems <= 0) return CS_OK;
-  hipLaunchKernelGGL(k_rank_tables, dim3((unsigned)nitems), dim3(kTabThreads), 0, st, rank, items,
-                     rank_base);
+  auto go = [&](auto kernel, int blocks) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)nitems), dim3(64 * blocks), 0, st, rank, items, rank_base);
+  };
+  if (small) go(k_rank_tables<(int)kSmallN, kSmallWaves>, kSmallWaves);
+  else go(k_rank_tables<(int)kBatchMaxN, kTabBlocks>, kTabBlocks);
   CS_LAUNCH_CHECK();
   return CS_OK;
 }
 
-cs_status launch_count_ranks(const RankInst* rank, const uint32_t* items, int64_t nitems,
+cs_status launch_count_ranks(bool small, const RankInst* rank, const uint32_t* items, int64_t nitems,
                              int per_item, const char* rank_base, uint64_t* hist,
                              unsigned int* counter, hipStream_t st) {
   if (nitems <= 0) return CS_OK;
-  const unsigned grid = (unsigned)(nitems < 2 * device_cu_count() ? nitems : 2 * device_cu_count());
-  hipLaunchKernelGGL(k_count_ranks, dim3(grid), dim3(kRankThreads), 0, st, rank, items, nitems,
-                     per_item, rank_base, (unsigned long long*)hist, counter);
+  auto go = [&](auto kernel, int waves) {
+    const int64_t resident = 32 / waves * (int64_t)device_cu_count();
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(nitems < resident ? nitems : resident)),
+                       dim3(64 * waves), 0, st, rank, items, nitems, per_item, rank_base,
+                       (unsigned long long*)hist, counter);
+  };
+  if (small) go(k_count_ranks<(int)kSmallN, kSmallWaves>, kSmallWaves);
+  else go(k_count_ranks<(int)kBatchMaxN, kRankWaves>, kRankWaves);
   CS_LAUNCH_CHECK();
   return CS_OK;
 }

@@ -463,38 +463,42 @@ __global__ __launch_bounds__(kRankThreads) void k_rank_place_mink2(uint64_t skey
 // and its place is its bucket's start plus the points of the bucket that precede it.
 // The bucket's leading key bits being equal, the remaining ones and the index fit one
 // 64-bit word, so a comparison is exact.  Bound by its barriers and LDS latency (one
-// workgroup per CU, the largest instance ends last).
+// workgroup per CU, the largest instance ends last; sixteen of the form for small instances:
+// 30000 diamonds of 64 points 61 us, 926 in the large form).
 // ---------------------------------------------------------------------------
-constexpr int kBatchSortThreads = 1024;
-constexpr int kBatchSortWaves = kBatchSortThreads / 64;
-constexpr int kBatchPer = (int)(kBatchMaxN / kBatchSortThreads);  // points per thread
+template <int CAP>
+constexpr int kSortThreads = CAP == kBatchMaxN ? 1024 : 128;  // for up to CAP points
+template <int CAP>
+constexpr int kSortPer = CAP / kSortThreads<CAP>;             // points per thread
 
+template <int CAP>
 struct BucketLds {
-  uint64_t word[kBatchMaxN];       // rest of the key << lg | index, by bucket slot
-  uint32_t start[kBatchMaxN + 4];  // bucket counts, then starts; start[buckets] = n
-  uint32_t wsum[kBatchSortWaves];
+  uint64_t word[CAP];       // rest of the key << lg | index, by bucket slot
+  uint32_t start[CAP + 4];  // bucket counts, then starts; start[buckets] = n
+  uint32_t wsum[kSortThreads<CAP> / 64];
 };
 
-// place[e] = number of points before point threadIdx.x + 1024 e in (key, index) order; keys
+// place[e] = number of points before point threadIdx.x + threads e in (key, index) order; keys
 // below 2^KB, 2^lg >= n buckets.  tie(g, h): for equal keys, whether g comes first.
-template <int KB, typename Tie>
-__device__ inline void bucket_places(const uint64_t (&key)[kBatchPer], int n, int lg, BucketLds& L,
-                                     uint32_t (&place)[kBatchPer], Tie&& tie) {
+template <int KB, int CAP, typename Tie>
+__device__ inline void bucket_places(const uint64_t (&key)[kSortPer<CAP>], int n, int lg,
+                                     BucketLds<CAP>& L, uint32_t (&place)[kSortPer<CAP>], Tie&& tie) {
+  constexpr int kThreads = kSortThreads<CAP>, kPer = kSortPer<CAP>;
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int P = 1 << lg, sh = KB - lg;
   __syncthreads();  // the last use of the buffers is over
-  for (int b = t; b < P; b += kBatchSortThreads) L.start[b] = 0;
+  for (int b = t; b < P; b += kThreads) L.start[b] = 0;
   __syncthreads();
-  uint32_t at[kBatchPer];
+  uint32_t at[kPer];
 #pragma unroll
-  for (int e = 0; e < kBatchPer; ++e)
-    if (t + e * kBatchSortThreads < n) at[e] = atomicAdd(&L.start[key[e] >> sh], 1u);
+  for (int e = 0; e < kPer; ++e)
+    if (t + e * kThreads < n) at[e] = atomicAdd(&L.start[key[e] >> sh], 1u);
   __syncthreads();
   {  // exclusive scan of the counts: m consecutive buckets per thread
-    const int m = P > kBatchSortThreads ? P / kBatchSortThreads : 1;
-    uint32_t c[kBatchPer], sum = 0;
+    const int m = P > kThreads ? P / kThreads : 1;
+    uint32_t c[kPer], sum = 0;
 #pragma unroll
-    for (int q = 0; q < kBatchPer; ++q)
+    for (int q = 0; q < kPer; ++q)
       if (q < m && t * m + q < P) {
         c[q] = L.start[t * m + q];
         sum += c[q];
@@ -509,9 +513,9 @@ __device__ inline void bucket_places(const uint64_t (&key)[kBatchPer], int n, in
     __syncthreads();
     uint32_t off = x - sum;
 #pragma unroll
-    for (int w = 0; w < kBatchSortWaves; ++w) off += w < wave ? L.wsum[w] : 0u;
+    for (int w = 0; w < kThreads / 64; ++w) off += w < wave ? L.wsum[w] : 0u;
 #pragma unroll
-    for (int q = 0; q < kBatchPer; ++q)
+    for (int q = 0; q < kPer; ++q)
       if (q < m && t * m + q < P) {
         L.start[t * m + q] = off;
         off += c[q];
@@ -520,15 +524,15 @@ __device__ inline void bucket_places(const uint64_t (&key)[kBatchPer], int n, in
   }
   __syncthreads();
 #pragma unroll
-  for (int e = 0; e < kBatchPer; ++e) {
-    const uint32_t g = t + e * kBatchSortThreads;
+  for (int e = 0; e < kPer; ++e) {
+    const uint32_t g = t + e * kThreads;
     if ((int)g < n)
       L.word[L.start[key[e] >> sh] + at[e]] = (key[e] & ((1ull << sh) - 1)) << lg | g;
   }
   __syncthreads();
 #pragma unroll
-  for (int e = 0; e < kBatchPer; ++e) {
-    const uint32_t g = t + e * kBatchSortThreads;
+  for (int e = 0; e < kPer; ++e) {
+    const uint32_t g = t + e * kThreads;
     if ((int)g < n) {
       const uint64_t b = key[e] >> sh;
       const uint64_t w = (key[e] & ((1ull << sh) - 1)) << lg | g;
@@ -551,23 +555,27 @@ __device__ inline void bucket_places(const uint64_t (&key)[kBatchPer], int n, in
 // sigma[x] is the u place of the point at v place x, pi its inverse.  Equal coordinates
 // are unrelated, so ties take opposite orders in u and v: equal u by v descending, equal
 // v by u descending, equal points by index one way and the other.
-__global__ __launch_bounds__(kBatchSortThreads) void k_sprinkle_mink2_batch(
+template <int CAP>
+__global__ __launch_bounds__(kSortThreads<CAP>) void k_sprinkle_mink2_batch(
     const uint64_t* __restrict__ seeds, const BatchInst* __restrict__ inst,
-    const RankInst* __restrict__ rank, double* __restrict__ coords, uint32_t* __restrict__ uv,
-    char* __restrict__ rank_base, uint64_t* __restrict__ hist, uint64_t* __restrict__ zero, int nzero) {
-  __shared__ BucketLds L;
-  const BatchInst d = inst[blockIdx.x];
+    const RankInst* __restrict__ rank, const uint32_t* __restrict__ ids, double* __restrict__ coords,
+    uint32_t* __restrict__ uv, char* __restrict__ rank_base, uint64_t* __restrict__ hist,
+    uint64_t* __restrict__ zero, int nzero) {
+  constexpr int kThreads = kSortThreads<CAP>, kPer = kSortPer<CAP>;
+  __shared__ BucketLds<CAP> L;
+  const uint32_t inst_id = ids ? ids[blockIdx.x] : blockIdx.x;
+  const BatchInst d = inst[inst_id];
   const int n = (int)d.n, t = threadIdx.x;
-  for (int m = t; m < n - 1; m += kBatchSortThreads) hist[d.hist_off + m] = 0;
+  for (int m = t; m < n - 1; m += kThreads) hist[d.hist_off + m] = 0;
   if (blockIdx.x == 0)
-    for (int w = t; w < nzero; w += kBatchSortThreads) zero[w] = 0;
+    for (int w = t; w < nzero; w += kThreads) zero[w] = 0;
   int lg = 1;
   while ((1 << lg) < n) ++lg;
-  const uint64_t skey = sm_stream_key(seeds[blockIdx.x], kStreamMink2);
-  uint64_t ku[kBatchPer], kv[kBatchPer], key[kBatchPer];
+  const uint64_t skey = sm_stream_key(seeds[inst_id], kStreamMink2);
+  uint64_t ku[kPer], kv[kPer], key[kPer];
 #pragma unroll
-  for (int e = 0; e < kBatchPer; ++e) {
-    const int g = t + e * kBatchSortThreads;
+  for (int e = 0; e < kPer; ++e) {
+    const int g = t + e * kThreads;
     ku[e] = kv[e] = key[e] = 0;
     if (g < n) {
       ku[e] = sm_output(skey, 2 * (uint64_t)g) >> 11;
@@ -575,47 +583,47 @@ __global__ __launch_bounds__(kBatchSortThreads) void k_sprinkle_mink2_batch(
       key[e] = ku[e] + kv[e];
     }
   }
-  uint32_t place[kBatchPer];
-  bucket_places<54>(key, n, lg, L, place, [](uint32_t a, uint32_t b) { return a < b; });
+  uint32_t place[kPer];
+  bucket_places<54, CAP>(key, n, lg, L, place, [](uint32_t a, uint32_t b) { return a < b; });
   double* cu = coords + d.coord_off;
   double* cv = cu + n;
 #pragma unroll
-  for (int e = 0; e < kBatchPer; ++e)
-    if (t + e * kBatchSortThreads < n) {
+  for (int e = 0; e < kPer; ++e)
+    if (t + e * kThreads < n) {
       cu[place[e]] = (double)ku[e] * 0x1.0p-53;
       cv[place[e]] = (double)kv[e] * 0x1.0p-53;
     }
   auto draw = [&](uint32_t g, int axis) { return sm_output(skey, 2 * (uint64_t)g + axis) >> 11; };
-  uint32_t pu[kBatchPer], pv[kBatchPer];
-  bucket_places<53>(ku, n, lg, L, pu, [&](uint32_t a, uint32_t b) {
+  uint32_t pu[kPer], pv[kPer];
+  bucket_places<53, CAP>(ku, n, lg, L, pu, [&](uint32_t a, uint32_t b) {
     const uint64_t va = draw(a, 1), vb = draw(b, 1);
     return va > vb || (va == vb && a < b);
   });
-  bucket_places<53>(kv, n, lg, L, pv, [&](uint32_t a, uint32_t b) {
+  bucket_places<53, CAP>(kv, n, lg, L, pv, [&](uint32_t a, uint32_t b) {
     const uint64_t ua = draw(a, 0), ub = draw(b, 0);
     return ua > ub || (ua == ub && a > b);
   });
   uint32_t* place_uv = uv + d.coord_off / 2;
 #pragma unroll
-  for (int e = 0; e < kBatchPer; ++e)
-    if (t + e * kBatchSortThreads < n) place_uv[place[e]] = pu[e] << 16 | pv[e];
-  const RankInst r = rank[blockIdx.x];
+  for (int e = 0; e < kPer; ++e)
+    if (t + e * kThreads < n) place_uv[place[e]] = pu[e] << 16 | pv[e];
+  const RankInst r = rank[inst_id];
   if (r.n == 0) return;
   // Both permutations leave through LDS, in whole lines.
   uint16_t* perm = (uint16_t*)L.word;  // sigma, then pi
   __syncthreads();
 #pragma unroll
-  for (int e = 0; e < kBatchPer; ++e)
-    if (t + e * kBatchSortThreads < n) {
+  for (int e = 0; e < kPer; ++e)
+    if (t + e * kThreads < n) {
       perm[pv[e]] = (uint16_t)pu[e];
-      perm[kBatchMaxN + pu[e]] = (uint16_t)pv[e];
+      perm[CAP + pu[e]] = (uint16_t)pv[e];
     }
   __syncthreads();
   uint16_t* sigma = (uint16_t*)(rank_base + r.sigma_off());
   uint16_t* pi = (uint16_t*)(rank_base + r.pi_off());
-  for (int i = t; i < 64 * r.nb; i += kBatchSortThreads) {
+  for (int i = t; i < 64 * r.nb; i += kThreads) {
     sigma[i] = i < n ? perm[i] : (uint16_t)0xFFFFu;
-    pi[i] = i < n ? perm[kBatchMaxN + i] : (uint16_t)0u;
+    pi[i] = i < n ? perm[CAP + i] : (uint16_t)0u;
   }
 }
 
@@ -695,12 +703,17 @@ cs_status launch_sprinkle(int region, double eta0, uint64_t seed, int64_t n, dou
   return CS_OK;
 }
 
-cs_status launch_sprinkle_batch(const uint64_t* seeds, const BatchInst* inst, const RankInst* rank,
-                                int64_t count, double* coords, uint32_t* uv, char* rank_base,
-                                uint64_t* hist, uint64_t* zero, int nzero, hipStream_t st) {
+cs_status launch_sprinkle_batch(bool small, const uint64_t* seeds, const BatchInst* inst,
+                                const RankInst* rank, const uint32_t* ids, int64_t count,
+                                double* coords, uint32_t* uv, char* rank_base, uint64_t* hist,
+                                uint64_t* zero, int nzero, hipStream_t st) {
   if (count <= 0) return CS_OK;
-  hipLaunchKernelGGL(k_sprinkle_mink2_batch, dim3((unsigned)count), dim3(kBatchSortThreads), 0, st,
-                     seeds, inst, rank, coords, uv, rank_base, hist, zero, nzero);
+  auto go = [&](auto kernel, int threads) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)count), dim3(threads), 0, st, seeds, inst, rank, ids,
+                       coords, uv, rank_base, hist, zero, nzero);
+  };
+  if (small) go(k_sprinkle_mink2_batch<(int)kSmallN>, kSortThreads<(int)kSmallN>);
+  else go(k_sprinkle_mink2_batch<(int)kBatchMaxN>, kSortThreads<(int)kBatchMaxN>);
   CS_LAUNCH_CHECK();
   return CS_OK;
 }

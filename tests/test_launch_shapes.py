@@ -126,3 +126,27 @@ def test_chain_survey_workgroups(rec, count):
     surveys = launches(rec, "k_chain_survey")
     assert len(surveys) == 2
     assert all(x <= 256 and y == 1 and threads == 1024 for x, y, threads in surveys)
+
+
+@pytest.mark.parametrize("sizes,small,large", [
+    ([30] * 60000, 60000, 0), ([512] * 512, 512, 0), ([512] * 511, 0, 511), ([192, 2, 64], 3, 0),
+    ([193, 2, 64], 0, 3), ([8192] + [100] * 512, 512, 1), ([8192] + [100] * 511, 0, 512),
+    ([513] * 600, 0, 600)])
+def test_ensemble_forms(rec, sizes, small, large):
+    """Small diamonds leave the kernels that are sized for 8192 points, where they are many or
+    alone."""
+    rec.rec_reset()
+    i64, p, sz = ctypes.c_int64, ctypes.c_void_p, ctypes.c_size_t
+    rec.cs_batch_plan.argtypes = [i64, p, ctypes.c_int, ctypes.c_int, p, p, p]
+    rec.cs_batch_run.argtypes = [p, p, p, p, p, sz, p]
+    n, plan = (ctypes.c_int64 * len(sizes))(*sizes), p()
+    assert rec.cs_batch_plan(len(sizes), n, 2, 0, None, None, ctypes.byref(plan)) == 0
+    assert rec.cs_batch_run(plan, ANY, ANY, ANY, ANY, ROOM, None) == 0
+    for cap, count in ((512, small), (8192, large)):
+        for kernel in ("k_sprinkle_mink2_batch", "k_rank_tables", "k_build_batch", "k_count_ranks"):
+            seen = launches(rec, f"{kernel}ILi{cap}")
+            assert len(seen) == (1 if count else 0), (kernel, cap)
+            if count and kernel == "k_sprinkle_mink2_batch":
+                assert seen[0] == (count, 1, 128 if cap == 512 else 1024)
+    rec.cs_batch_free.argtypes = [p]
+    assert rec.cs_batch_free(plan) == 0
