@@ -416,6 +416,7 @@ __global__ __launch_bounds__(64 * kBuildWaves<CAP>, 8) void k_build_batch(
     const uint32_t* __restrict__ uvs, const BatchInst* __restrict__ inst,
     const uint32_t* __restrict__ items, int64_t nitems, uint64_t* __restrict__ bits) {
   constexpr int kWaves = kBuildWaves<CAP>, kWords = CAP / 32;
+  constexpr bool kAll = kWaves == kBuildTables;  // empty blocks have tables too
   __shared__ uint2 sets[kBuildTables][kWords] __attribute__((aligned(16)));  // bits, count below
   __shared__ uint64_t above[kBuildTables][66];  // [c]: columns with at least c of the block below
   const int lane = threadIdx.x & 63;
@@ -436,7 +437,8 @@ __global__ __launch_bounds__(64 * kBuildWaves<CAP>, 8) void k_build_batch(
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   };
   const int blocks = nb - b0 < kBuildBlocks ? nb - b0 : kBuildBlocks;
-  for (int a = wave; a < 2 * blocks; a += kWaves) {  // table 2 b + axis: column block b0 + b
+  for (int a = wave; a < (kAll ? kBuildTables : 2 * blocks); a += kWaves) {
+    // table 2 b + axis: column block b0 + b
     const int j = 64 * (b0 + (a >> 1)) + lane;
     const bool valid = j < n, mine = 4 * lane < kWords;  // a lane's four words of the set
     const uint32_t t = valid ? uv[j] : 0u;
@@ -495,11 +497,12 @@ __global__ __launch_bounds__(64 * kBuildWaves<CAP>, 8) void k_build_batch(
 #pragma unroll
       for (int e = 0; e < 2; ++e) {
         const int a = 2 * (own + e);
-        w[e] = own + e < blocks ? ~(above[a][query(a, pu)] ^ above[a + 1][query(a + 1, pv)]) : 0ull;
+        w[e] = kAll || own + e < blocks
+                   ? ~(above[a][query(a, pu)] ^ above[a + 1][query(a + 1, pv)]) : 0ull;
         if (rb - b0 == own + e) w[e] &= ~(1ull << (i & 63));  // not related to itself
         if (edge) {
           const int left = n - 64 * (b0 + own + e);
-          if (left > 0 && left < 64) w[e] &= (1ull << left) - 1ull;
+          w[e] &= left >= 64 ? ~0ull : (left <= 0 ? 0ull : (1ull << left) - 1ull);
         }
       }
       if (i < n)

@@ -292,8 +292,9 @@ __device__ __forceinline__ int64_t first_witness(const uint64_t* __restrict__ ro
 }
 
 // Round t for the 64 elements of each of the `active` listed words, a workgroup per word.  R:
-// the members (read only); R_next: the members without this round's minimal elements.
-template <int THREADS>
+// the members (read only); R_next: the members without this round's minimal elements.  ROWS:
+// the grid has several rows (testing the index in every round cost 0.3 us each).
+template <int THREADS, bool ROWS = false>
 __global__ __launch_bounds__(THREADS, 8) void k_chain_round(
     const uint64_t* __restrict__ bits, int64_t n, int64_t ld, int64_t W,
     const uint64_t* __restrict__ list, int64_t active, const uint64_t* __restrict__ R,
@@ -306,8 +307,8 @@ __global__ __launch_bounds__(THREADS, 8) void k_chain_round(
   __shared__ int ntodo;
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const int64_t group = group_index();
-  if (group >= active) return;  // the whole workgroup
+  const int64_t group = ROWS ? group_index() : (int64_t)blockIdx.x;
+  if (ROWS && group >= active) return;  // the whole workgroup, here and below
   const uint64_t entry = list[group];
   if (entry == kNoWord) return;
   const int s = (int)(entry >> 32);
@@ -743,10 +744,11 @@ cs_status launch_longest_chain(const uint64_t* bits, int64_t n, int64_t ld, cons
                            L.list, (int64_t)now.active, L.X[c], L.X[c ^ 1], L.wit, h, L.low[c ^ 1],
                            L.low[c], (int32_t)t);
       };
+      const bool rows = (int64_t)now.active > kGridRow;
       if (threads == 1024) round(k_chain_round<1024>);
       else if (threads == 512) round(k_chain_round<512>);
-      else if (threads == 256) round(k_chain_round<256>);
-      else round(k_chain_round<128>);
+      else if (threads == 256) rows ? round(k_chain_round<256, true>) : round(k_chain_round<256>);
+      else rows ? round(k_chain_round<128, true>) : round(k_chain_round<128>);
       CS_LAUNCH_CHECK();
     }
   }

@@ -97,11 +97,12 @@ inline int64_t scatter_step(int64_t m) {
 // Grid of `groups` workgroups in rows of at most 2^21: a launch holds less than 2^32 work-items
 // along x, a row here at most 2^31.  The kernel's workgroup is group_index(), which in the last
 // of several rows can be `groups` or more.
+constexpr int64_t kGridRow = (int64_t)1 << 21;
 inline dim3 grid_rows(int64_t groups) {
-  constexpr int64_t kRow = (int64_t)1 << 21;
-  return groups <= kRow ? dim3((unsigned)groups) : dim3((unsigned)kRow, (unsigned)ceil_div(groups, kRow));
+  return groups <= kGridRow ? dim3((unsigned)groups)
+                            : dim3((unsigned)kGridRow, (unsigned)ceil_div(groups, kGridRow));
 }
-__device__ inline int64_t group_index() { return (int64_t)blockIdx.y * gridDim.x + blockIdx.x; }
+__device__ inline int64_t group_index() { return (int64_t)blockIdx.y * kGridRow + blockIdx.x; }
 
 // Coordinate planes per region (2, 4, 7).
 inline int coord_planes(int region) {
