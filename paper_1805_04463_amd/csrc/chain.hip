@@ -175,8 +175,10 @@ __global__ __launch_bounds__(kSurveyThreads) void k_chain_survey(
 }
 
 // The same for more than kSurveyPairs pairs: a wavefront per pair, pairs dealt to the wavefronts
-// of at most kSurveyGroups workgroups, so that few workgroups add to the survey's one line.
-// (40000 pairs of 65 elements: 20 us, where a workgroup per pair took 777.)
+// of few workgroups, as each adds three times to the survey's one line (12 ns) while a
+// wavefront spends about 1.2 us on a pair of a few words: about sqrt(2 count) workgroups balance
+// the two.  (40000 pairs of 65 elements: 20 us, where a workgroup per pair took 777; 5000: 8.6
+// us, 12.1 with 256 workgroups.)
 constexpr int kSurveyPairs = 256, kSurveyGroups = 256;
 constexpr int kSurveyWaves = kSurveyThreads / kWave;
 __global__ __launch_bounds__(kSurveyThreads) void k_chain_survey_many(
@@ -698,7 +700,7 @@ cs_status launch_longest_chain(const uint64_t* bits, int64_t n, int64_t ld, cons
                          L.X[t & 1], L.X[(t + 1) & 1], W, L.low[(t + 1) & 1], L.list, L.survey + b);
     else
       hipLaunchKernelGGL(k_chain_survey_many,
-                         dim3((unsigned)std::min<int64_t>(kSurveyGroups, ceil_div(count, kSurveyWaves))),
+                         dim3((unsigned)std::min<int64_t>(kSurveyGroups, (int64_t)sqrt(2.0 * (double)count))),
                          dim3(kSurveyThreads), 0, st, L.X[t & 1], L.X[(t + 1) & 1], W, count,
                          L.low[(t + 1) & 1], L.list, L.survey + b);
     CS_LAUNCH_CHECK();
