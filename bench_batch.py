@@ -1,8 +1,8 @@
 """Ensemble leg of bench.py: 256 independent 1+1 diamonds, N uniform in [512, 8192].
 
 One HIP-graph launch of the batch pipeline (sprinkle, matrix, counts, actions for
-every instance), with each of the three counters (each counts by ranks where the tuner
-finds that faster than the counter's tiles), against the same 256 instances as
+every instance), counted by ranks as plans do whose tuner cache shows nothing faster, and
+on the tuned tiles of each of the three counters, against the same 256 instances as
 separate per-instance calls of the single-instance entry points (int8 counter, and
 again with the fp4 counter).  All are timed with HIP events on one stream.
 """
@@ -32,11 +32,25 @@ def run_batch(cs, torch, dev, stream, reps: int = 5):
     tune_s = time.perf_counter() - t0
     import json
     tuned = {}
-    for e in json.load(open(tune))["entries"]:
+    entries = json.load(open(tune))["entries"]
+    for e in entries:
         tuned.setdefault(e["counter"], []).append(
             {"n": [e["n_lo"], e["n_hi"]], "tile": e["tile"], "per_cu": e["per_cu"],
              **({"pair_max": e["pair_max"]} if e["counter"] == "bitset" else {}),
-             "probe_ms": e["ms"], "probe": [e["probe_instances"], e["probe_n"]]})
+             "tile_ms": e["ms"], "rank_ms": e["rank_ms"],
+             "plan_counts_by": "ranks" if e["rank_ms"] < e["ms"] else "tiles",
+             "probe": [e["probe_instances"], e["probe_n"]]})
+
+    def cache_of(name, ents):
+        path = os.path.join(tempfile.gettempdir(), name)
+        with open(path, "w") as f:
+            f.write('{\n  "format": "causal-batch-tune-2",\n  "entries": [\n'
+                    + ",\n".join("    " + json.dumps(e) for e in ents) + "\n  ]\n}\n")
+        return path
+
+    # entries without rank_ms keep their tiles
+    tiles = cache_of("cs_tune_tiles.json", [{k: v for k, v in e.items() if k != "rank_ms"}
+                                            for e in entries])
 
     def ev():
         return torch.cuda.Event(enable_timing=True)
@@ -47,18 +61,16 @@ def run_batch(cs, torch, dev, stream, reps: int = 5):
     # The fp4 counter also with 256x256 tiles (one workgroup per CU) for the instances of
     # 4096 points or more, the tuner's other candidate there, to show what its choice is
     # worth; a cache file of the tuner's format gives that configuration.
-    alt = os.path.join(tempfile.gettempdir(), "cs_tune_fp4_tiles256.json")
-    ent = [{"counter": "mfma_fp4", "n_lo": lo, "n_hi": hi, "mode": 4 if lo >= 4096 else 2,
-            "tile": 256 if lo >= 4096 else 128, "per_cu": 1 if lo >= 4096 else 2,
-            "pair_max": 0, "ms": 0.0}
-           for lo, hi in ((2, 1023), (1024, 2047), (2048, 4095), (4096, 8192))]
-    with open(alt, "w") as f:
-        f.write('{\n  "format": "causal-batch-tune-2",\n  "entries": [\n'
-                + ",\n".join("    " + json.dumps(e) for e in ent) + "\n  ]\n}\n")
-    # each counter with the tuned tiles
-    for name, counter, cache in (("mfma", cs.CS_COUNT_MFMA, tune),
-                                 ("mfma_fp4", cs.CS_COUNT_MFMA_FP4, tune),
-                                 ("bitset", cs.CS_COUNT_BITSET, tune),
+    alt = cache_of("cs_tune_fp4_tiles256.json", [
+        {"counter": "mfma_fp4", "n_lo": lo, "n_hi": hi, "mode": 4 if lo >= 4096 else 2,
+         "tile": 256 if lo >= 4096 else 128, "per_cu": 1 if lo >= 4096 else 2,
+         "pair_max": 0, "ms": 0.0}
+        for lo, hi in ((2, 1023), (1024, 2047), (2048, 4095), (4096, 8192))])
+    # the tuned plan, then the tiles of each counter
+    for name, counter, cache in (("tuned", cs.CS_COUNT_MFMA_FP4, tune),
+                                 ("mfma_tiles", cs.CS_COUNT_MFMA, tiles),
+                                 ("mfma_fp4_tiles", cs.CS_COUNT_MFMA_FP4, tiles),
+                                 ("bitset_tiles", cs.CS_COUNT_BITSET, tiles),
                                  ("mfma_fp4_tiles256_from4096", cs.CS_COUNT_MFMA_FP4, alt)):
         plan = cs.BatchPlan(sizes, counter=counter, eps=eps, tune_cache=cache)
         s = torch.from_numpy(seeds.view(np.int64)).to(dev)
@@ -127,15 +139,14 @@ def run_batch(cs, torch, dev, stream, reps: int = 5):
     seq_ms = timed_pass(cs.CS_COUNT_MFMA)
     out["per_instance_ms"] = seq_ms
     out["per_instance_ensembles_per_s"] = count / (seq_ms * 1e-3)
-    out["graph_vs_per_instance"] = seq_ms / out["graph_mfma_ms"]
+    out["graph_vs_per_instance"] = seq_ms / out["graph_tuned_ms"]
     one_pass(cs.CS_COUNT_MFMA_FP4)
     seq4_ms = timed_pass(cs.CS_COUNT_MFMA_FP4)
     out["per_instance_fp4_ms"] = seq4_ms
-    out["graph_fp4_vs_per_instance_fp4"] = seq4_ms / out["graph_mfma_fp4_ms"]
-    hm, offs = results["mfma"]
-    hb, _ = results["bitset"]
-    out["mfma_equals_bitset"] = bool(np.array_equal(hm, hb))
-    out["mfma_fp4_equals_bitset"] = bool(np.array_equal(results["mfma_fp4"][0], hb))
+    out["graph_vs_per_instance_fp4"] = seq4_ms / out["graph_tuned_ms"]
+    hm, offs = results["tuned"]
+    for name in ("mfma_tiles", "mfma_fp4_tiles", "bitset_tiles"):
+        out[f"{name}_equal_tuned"] = bool(np.array_equal(results[name][0], hm))
     out["per_instance_equals_graph"] = all(
         np.array_equal(last[k], hm[offs[k]:offs[k] + int(sizes[k]) - 1]) for k in last)
     return out

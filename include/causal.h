@@ -16,7 +16,7 @@
  *   cs_longest_chain       longest chains through Alexandroff sets (Sec. 2.5.2), and
  *   cs_degrees             the degree vectors of the matrix (Sec. 3.2)
  *   cs_batch_*             the four steps for an ensemble of independent 1+1 diamonds in
- *                          one persistent launch per step, capturable in a HIP graph
+ *                          a few launches for all of it, capturable in a HIP graph
  *
  * Conventions for every entry point:
  *   - Pointers named "device" are caller-owned device memory (hipMalloc, or a torch CUDA
@@ -303,9 +303,11 @@ cs_status cs_batch_free(cs_batch_plan_handle plan);
 /*
  * HIP graph of one cs_batch_run with these buffers, captured on an internal stream and
  * instantiated (so the graph replays the same launches: sprinkle, which also clears the
- * histograms and the work counters, build, rank tables, count, action).  graph_exec receives an opaque hipGraphExec_t owned by the caller:
- * launch it with cs_batch_graph_launch on any stream, release it with
- * cs_batch_graph_destroy.  The buffers must stay valid while the graph is in use.
+ * histograms and the work counters, build, rank tables, count, action; each but the last
+ * twice where many small diamonds accompany larger ones).  graph_exec receives an opaque
+ * hipGraphExec_t owned by the caller: launch it with cs_batch_graph_launch on any stream,
+ * release it with cs_batch_graph_destroy.  The buffers must stay valid while the graph is in
+ * use.
  */
 cs_status cs_batch_graph_create(cs_batch_plan_handle plan, const uint64_t *seeds, uint64_t *hist,
                                 double *actions, void *workspace, size_t workspace_bytes,

@@ -17,8 +17,8 @@
 // double-double (error-free transformations: Knuth's two-sum, Dekker's product via
 // fma), then rounded once.  The local combination is an exact 128-bit integer.
 //
-// One workgroup of 1024 threads per action; bins are dealt in chunks of 8, and the
-// walk stops where all further terms together are below 2^-120.
+// One workgroup of 1024 threads per action; about 512 of them take a chunk of bins each, and
+// the walk stops where all further terms together are below 2^-120.
 #include "common.h"
 
 namespace cs {

@@ -1,6 +1,6 @@
 // Ensembles of independent 1+1 diamonds: plan, run, HIP-graph capture and the tile
 // autotuner.  (The thesis averages its action measurements over ensembles of
-// causal sets; here the ensemble is one pipeline of four launches.)
+// causal sets; here the ensemble is one pipeline of five launches.)
 //
 // Plan: per-instance offsets into three concatenated buffers (coordinates, matrices,
 // histograms), the builder's work lists (groups of 512 columns, per XCD) and

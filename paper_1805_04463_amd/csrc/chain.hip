@@ -731,7 +731,7 @@ cs_status launch_longest_chain(const uint64_t* bits, int64_t n, int64_t ld, cons
         if (narrow) pairs(k_chain_pair<256>, 256);
         else pairs(k_chain_pair<1024>, 1024);
         CS_LAUNCH_CHECK();
-        CS_HIP_CHECK(hipStreamSynchronize(st));
+        CS_HIP_CHECK(hipStreamSynchronize(st));  // the call returns after its rounds in either form
         break;
       }
       batch = std::max<int64_t>(2, std::min<int64_t>(64, (int64_t)ceil(rounds)));

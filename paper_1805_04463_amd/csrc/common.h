@@ -44,7 +44,7 @@ enum : uint64_t {
 // 0.69^4096: never reached in practice, but every loop has a bound).
 constexpr int kSphereTries = 4096;
 
-// Bitonic sort element: (key, generation index), ordered lexicographically.
+// The time order: (key, generation index), lexicographically.
 __device__ inline bool key_less(uint64_t ka, uint32_t ga, uint64_t kb, uint32_t gb) {
   return ka < kb || (ka == kb && ga < gb);
 }
@@ -104,7 +104,7 @@ inline dim3 grid_rows(int64_t groups) {
 }
 __device__ inline int64_t group_index() { return (int64_t)blockIdx.y * kGridRow + blockIdx.x; }
 
-// Coordinate planes per region (2, 4, 7).
+// Coordinate planes per region.
 inline int coord_planes(int region) {
   switch (region) {
     case CS_MINK2_DIAMOND: return 2;

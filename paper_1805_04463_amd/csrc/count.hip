@@ -12,7 +12,9 @@
 // Both counters share:
 //   - a persistent grid that takes output tiles from an atomic counter, longest
 //     K-range first (tiles with the same distance J - I from the diagonal have
-//     equal cost);
+//     equal cost); small matrices on the MFMA counter launch a workgroup per tile
+//     instead, and the 128-row tiles of larger ones leave the queue in a scattered
+//     order where counts can lie past the LDS bins;
 //   - a whole-tile skip when no pair of the tile is related;
 //   - K staged through LDS 256 bits at a time; the triangular masks (k > i for A,
 //     k < j for B) only matter on stages that overlap the tile's own diagonal
@@ -20,11 +22,11 @@
 //   - an epilogue that tests the related bit S[j][i] of each output and bins the
 //     count into a per-workgroup LDS histogram (HB uint32 bins) or, beyond it,
 //     straight into the global uint64 histogram; LDS bins are flushed at exit.
-// The MFMA counter fills a 4-deep LDS ring with direct global->LDS DMA loads
-// (buffer_load_dwordx4 ... lds; rows past n read as zero through the buffer
-// descriptor's range), so three stages are in flight while one is multiplied and
-// each stage costs one barrier.  The bitset counter prefetches one stage through
-// registers.
+// The MFMA counter fills an LDS ring of three stages (256-row tiles) or two (128-row) with
+// direct global->LDS DMA loads (buffer_load_dwordx4 ... lds; rows past n read as zero through
+// the buffer descriptor's range), so the next stages are in flight while one is multiplied
+// and each stage costs one barrier.  The bitset counter prefetches two stages through
+// registers (one on dense tiles).
 // They differ in the inner product:
 //   MFMA   bits are expanded to int8 0/1 in registers and multiplied on
 //          v_mfma_i32_32x32x32_i8 with int32 accumulation (exact: counts < 2^31).
@@ -58,7 +60,7 @@ constexpr int kBinsSingle = 12288;      // LDS histogram bins, single instance (
 //                      16384: 281 / 305, 476 / 446;  28000: 1222 / 1204, 2140 / 1934
 //   d'Alembertian (3+1) 10007: 81 / 122, 126 / 147;  16384: 265 / 331, 443 / 434;
 //                      28000: 1175 / 1290, 2044 / 1891
-// Up to kBinsSmall + 1 points every count fits the bins.  Up to kPerTile tiles (8193
+// Up to kBinsSmall + 1 points every count fits the bins.  Up to kPerTile tiles (8320
 // points) each tile is a workgroup, longest first; more tiles are taken from one queue by
 // resident workgroups, which flush their bins once instead of per tile (the d'Alembertian
 // has none: a workgroup per tile always).

@@ -385,7 +385,12 @@ constexpr int kRankThreads = 256;
 constexpr int kRankSplit = 16;                       // lanes per element
 constexpr int kRankPer = kRankThreads / kRankSplit;  // elements per workgroup
 constexpr int kRankChunk = 2048;                     // keys staged per pass
-constexpr int64_t kRankMaxN = 8192;                  // n^2 comparisons: small sets only
+// n^2 comparisons: small sets only.  The line was drawn against a sorting network; buckets take,
+// by ranks / by buckets, us, the whole call: 1+1 diamond 2000 points 6.6 / 16.0, 4001 10.9 / 17.5,
+// 6000 18.0 / 17.2, 8192 23.4 / 17.5; 1+1 slab 9.9 / 14.3, 15.6 / 15.2, 21.8 / 14.4, 27.4 / 15.5; 3+1
+// diamond 17.6 / 28.4, 23.4 / 30.0, 29.3 / 31.9, 35.8 / 32.8; 3+1 slab 18.6 / 25.9, 24.4 / 25.9, 30.9 /
+// 26.0, 37.0 / 27.1.  So buckets are ahead from 4000 points on in slabs and 6000 to 8000 in diamonds.
+constexpr int64_t kRankMaxN = 8192;
 
 __device__ inline uint32_t rank_lane_sum(uint32_t v) {
 #pragma unroll
