@@ -396,8 +396,9 @@ __global__ __launch_bounds__(256) void k_build(const double* __restrict__ coords
 // place with running counts, as in the rank tables) and picks one of 65 precomputed
 // masks.  Four 8-byte LDS gathers and a dozen operations give 64 pairs of one row, against
 // 192 operations for testing the pairs, and rows below the diagonal need no transpose: 256
-// diamonds of 512 to 8192 points take 0.19 ms for 0.82 GB of matrices (4.3 TB/s; the LDS is
-// busy 35 % of the time, the VALU 16 %), against 0.41 ms with the pair tests.
+// diamonds of 512 to 8192 points take 0.19 ms for 0.82 GB of matrices (4.3 TB/s; the VALU
+// is busy 58 % of the time, bank conflicts take half of the LDS), against 0.41 ms with the pair
+// tests.
 //
 // A workgroup takes kBuildBlocks column blocks of an instance (512 columns: a lane's words
 // of a row are 64 contiguous bytes, padding words included) against all its rows.  The

@@ -134,8 +134,9 @@ __global__ __launch_bounds__(64 * TB) void k_rank_tables(const RankInst* __restr
 // VALU and three scalar operations for 64 pairs and one LDS add on the related lanes (about
 // half): 256 diamonds of 512 to 8192 points (3.1e9 pairs) take 0.66 ms, 7.3 cycles per
 // row and CU, where the fp4 matrix-core tiles took 3.15 ms.  Issue is the bound: the VALU
-// is busy 68 % of the time, the scalar unit 62 %, the LDS 59 % (without the adds a copy
-// of the kernel took 0.60 ms; 16 rows per fetch 0.68 ms).  Thousands of small instances are
+// is busy 79 % of the time (instructions times 4 cycles), the scalar unit 72 %, and bank
+// conflicts of the adds take 39 % of the LDS (without the adds a copy of the kernel took
+// 0.60 ms; 16 rows per fetch 0.68 ms).  Thousands of small instances are
 // bound by the one work counter, 12 ns an item (30000 of 128 points 374 us; with 16 wavefronts
 // and all 8191 bins 504).
 // ---------------------------------------------------------------------------
