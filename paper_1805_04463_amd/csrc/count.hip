@@ -525,9 +525,9 @@ __device__ inline void mfma_stage(Acc (&acc)[WM][WM], uint4 (&aw)[2][WM], uint4 
 // Single instances chain nothing, but end a 128-row tile without a related pair after its first
 // stage: a wave that holds one stores the tile's tag (not 0, another for each tile of the
 // workgroup) in *related before the barrier at the first stage's middle, and all waves read it
-// after that stage, so the skip costs no barrier and sprinkled orders no time.  (Antichains, us,
-// fp4 histogram: 9000 points 62 -> 44, 20000 435 -> 171; 256-row tiles, a quarter as many and
-// skipped before their first stage, take 44 and 84.)
+// after that stage, so the skip costs no barrier: 0.1 % of a sprinkled order's histogram, 0.5 % of
+// its d'Alembertian.  (Antichains, us, fp4 histogram: 9000 points 62 -> 44, 20000 435 -> 171;
+// 256-row tiles, a quarter as many and skipped before their first stage, take 44 and 84.)
 struct TileChain {
   int rofs = 0;
   bool ready = false;
@@ -768,11 +768,12 @@ __device__ __attribute__((always_inline)) inline bool mfma_tile(const TileArgs& 
   };
   int s = 0;
   for (; s + 2 < nst; ++s) {
-    if (kRelRegs && s == 1 && chain.related &&
-        (uint32_t)__builtin_amdgcn_readfirstlane((int)*chain.related) != chain.tag) {
-      wait_vmcnt<0>();  // as below
-      return false;
-    }
+    if constexpr (kRelRegs)
+      if (s == 1 && chain.related &&
+          (uint32_t)__builtin_amdgcn_readfirstlane((int)*chain.related) != chain.tag) {
+        wait_vmcnt<0>();  // as below
+        return false;
+      }
     stage(std::integral_constant<int, 0>{}, s);
   }
   if (nst >= 2) stage(std::integral_constant<int, 1>{}, s++);
@@ -1260,12 +1261,12 @@ template <int BM, int HB, int EPI = 0>
 struct MfmaLds {
   uint32_t ring[MRing<BM>::value * 2 * BM * kMStageU32] __attribute__((aligned(16)));
   uint32_t rel[BM == 128 ? 1 : BM * BM / 32];  // relation bits of the tile's pairs (i < j);
-                                              // 128-row tiles keep theirs in registers
+                                              // 128-row tiles keep theirs in registers, and
+                                              // here the tag of a tile that has any (TileChain)
   // d'Alembertian: phi of the tile's rows; c_0 .. c_3, 0; the lower wave row's column sums
   double phis[EPI == 1 ? BM + 8 + (BM == 128 ? BM : 0) : 1];
   uint32_t hist[HB + 64];      // bins, then one spare word per lane (never flushed)
   uint32_t maxbin;
-  uint32_t related;            // TileChain
   int slot;
 };
 template <int HB>
@@ -1304,8 +1305,9 @@ __global__ __launch_bounds__(kThreads, WM == 4 ? 1 : 2) void k_count_mfma(const 
       L.phis[BM + threadIdx.x] = threadIdx.x == 0 ? f.c0 : threadIdx.x == 1 ? f.c1
                                  : threadIdx.x == 2 ? f.c2 : threadIdx.x == 3 ? f.c3 : 0.0;
   uint32_t tmax = FITS ? (uint32_t)(n - 2) : 0u;  // FITS: flush every bin
-  uint32_t tag = 0;
-  if (threadIdx.x == 0) L.related = 0;  // before the first tile's barrier
+  [[maybe_unused]] uint32_t tag = 0;
+  if constexpr (WM == 2)
+    if (threadIdx.x == 0) L.rel[0] = 0;  // before the first tile's barrier
   int64_t pairs_in_lds = 0;
   TileArgs ta{(const uint32_t*)S, 2 * ld, n, 0, 0, hist, f};
   // 256-row tiles: rectangle queues per XCD while the table fits and there are enough tiles
@@ -1352,7 +1354,7 @@ __global__ __launch_bounds__(kThreads, WM == 4 ? 1 : 2) void k_count_mfma(const 
     ta.J0 = J * BM;
     TileChain one;
     if constexpr (WM == 2) {
-      one.related = &L.related;
+      one.related = L.rel;
       one.tag = ++tag;
     }
     if (mfma_tile<WM, HB, FP4, EPI, FITS>(ta, L.ring, L.rel, L.hist, tmax, L.phis, one))
